@@ -14,7 +14,7 @@
 //   6. induced-subgraph edge compaction in original edge order (local ids
 //      from a 32-byte-per-64-nodes rank table, per-tile counts, ballots);
 //   7. stable LSD radix sorts by (dst, r) and (src, r) give the CSR and CSC;
-//      row pointers from run-length counts; csc_scale = 1/deg_r(dst);
+//      row pointers read off the sorted keys; csc_scale = 1/deg_r(dst);
 //   8. the execution plan: per-relation active-source lists and the chunked
 //      work list of the atomic-free transposed SpMM.
 #include <vector>
@@ -41,7 +41,7 @@ __device__ __forceinline__ int64_t cdiv_dev(int64_t a, int64_t b) { return (a + 
 
 // Device counters written by the build.
 enum : int { C_ERR = 0, C_NSUB, C_ESUB, C_MSEL, C_ITEMS, C_HEAVY, C_PARTS, C_CPRIME, C_BASE, C_FHEAVY, C_FPARTS,
-             C_ASLOTS, C_COUNT };
+             C_ASLOTS, C_GAP_CSR, C_GAP_CSC, C_COUNT };
 
 // The row-indexed layout of the relation transforms is kept when nq rows cost
 // at most kRowLayoutMaxSpread times the a active ones.
@@ -794,79 +794,72 @@ __global__ void k_edge_compact(const int32_t* __restrict__ src, const int32_t* _
   }
 }
 
-// Row lengths of sorted keys.  A block takes kRCChunk consecutive keys (16
-// contiguous ones per thread); a run of equal keys that lies inside the chunk
-// is counted by a plain store (no other block sees that key), the chunk's
-// first and last runs, which may continue into a neighbour, by an atomic
-// add.  A row of any length then costs at most one atomic per chunk it
-// touches (a hub's row of millions of entries no longer serialises one
-// atomic per wave on one counter).  cnt must be zero on entry.
-constexpr int kRCItems = 16;
-constexpr int kRCChunk = kBT * kRCItems;
-__global__ void __launch_bounds__(kBT) k_row_count(const uint32_t* __restrict__ keys, int64_t n,
-                                                   int32_t* __restrict__ cnt) {
-  __shared__ int32_t starts[kRCChunk + 1];
-  __shared__ int32_t wsum[kBT / 64];
-  const int t = threadIdx.x;
-  const int64_t base = (int64_t)blockIdx.x * kRCChunk;
-  const int m = (int)((n - base) < kRCChunk ? (n - base) : kRCChunk);
-  const int p0 = t * kRCItems;
-  uint32_t k[kRCItems];
-  if (p0 + kRCItems <= m) {
-    // 16 consecutive keys as four 16-byte loads (chunks start 64-byte aligned)
-    const uint4* kp = reinterpret_cast<const uint4*>(keys + base + p0);
-#pragma unroll
-    for (int j = 0; j < kRCItems / 4; ++j) {
-      const uint4 v = kp[j];
-      k[4 * j] = v.x;
-      k[4 * j + 1] = v.y;
-      k[4 * j + 2] = v.z;
-      k[4 * j + 3] = v.w;
-    }
-  } else {
-#pragma unroll
-    for (int j = 0; j < kRCItems; ++j) k[j] = (p0 + j < m) ? keys[base + p0 + j] : 0u;
+// Row pointers of sorted keys: ptr[q] = the number of keys below q, for q in
+// [0, nq].  Every position p whose key differs from its predecessor's owns the
+// rows (key[p - 1], key[p]] and the last position also those up to nq; one
+// thread takes kRpItems keys a block's width apart, so a wave's keys and most
+// of its pointers are consecutive.  A gap of more than kRpInline empty rows
+// goes to a list in pieces of kRpPiece rows, filled by k_row_gaps over the
+// whole grid (one thread would write a graph's whole tail of nodes without
+// out-edges by itself).  Bound by its bytes: at 200M keys and 50M rows 1.0 GB
+// in 0.27 ms a sort; counting the rows with LDS and atomics, then scanning the
+// 50M counts, took 0.75 ms (fill 0.06, counts 0.33, scan 0.36).
+constexpr int kRpItems = 8;
+constexpr int kRpInline = 64;
+constexpr int kRpPiece = 16384;
+
+__device__ __forceinline__ void row_gap(int32_t* __restrict__ ptr, int32_t lo, int32_t hi, int32_t p,
+                                        int4* __restrict__ gaps, int32_t* __restrict__ n_gaps) {
+  if (hi - lo <= kRpInline) {
+    for (int32_t q = lo; q < hi; ++q) ptr[q] = p;
+    return;
   }
-  uint32_t prev = (p0 > 0 && p0 - 1 < m) ? keys[base + p0 - 1] : ~k[0];
-  int nf = 0;
-#pragma unroll
-  for (int j = 0; j < kRCItems; ++j) {
-    nf += (p0 + j < m && (j == 0 ? k[0] != prev : k[j] != k[j - 1])) ? 1 : 0;
+  const int32_t np = (hi - lo - 1) / kRpPiece + 1;
+  const int32_t at = atomicAdd(n_gaps, np);
+  for (int32_t i = 0; i < np; ++i) {
+    const int32_t l = lo + i * kRpPiece;
+    gaps[at + i] = make_int4(l, hi - l < kRpPiece ? hi : l + kRpPiece, p, 0);
   }
-  // exclusive scan of the run-start counts over the block
-  int inc = nf;
+}
+
+__global__ void __launch_bounds__(kBT) k_row_ptr(const uint32_t* __restrict__ keys, int64_t n, int32_t nq,
+                                                 int32_t* __restrict__ ptr, int4* __restrict__ gaps,
+                                                 int32_t* __restrict__ n_gaps) {
+  const int64_t base = (int64_t)blockIdx.x * (kBT * kRpItems) + threadIdx.x;
+  const int lane = threadIdx.x & 63;
+  int32_t k[kRpItems], head[kRpItems];
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int v = __shfl_up(inc, o, 64);
-    if ((t & 63) >= o) inc += v;
+  for (int j = 0; j < kRpItems; ++j) {
+    const int64_t p = base + (int64_t)j * kBT;
+    k[j] = (int32_t)keys[p < n ? p : n - 1];
+    // the key before the wave's first one (-1 before the first key)
+    head[j] = -1;
+    if (lane == 0 && p > 0 && p < n) head[j] = (int32_t)keys[p - 1];
   }
-  if ((t & 63) == 63) wsum[t >> 6] = inc;
-  __syncthreads();
-  int off = 0, total = 0;
 #pragma unroll
-  for (int q = 0; q < kBT / 64; ++q) {
-    off += (q < (t >> 6)) ? wsum[q] : 0;
-    total += wsum[q];
-  }
-  int idx = off + inc - nf;
-#pragma unroll
-  for (int j = 0; j < kRCItems; ++j) {
-    if (p0 + j < m && (j == 0 ? k[0] != prev : k[j] != k[j - 1])) starts[idx++] = p0 + j;
-  }
-  if (t == 0) starts[total] = m;
-  __syncthreads();
-  const bool cont_in = base > 0 && m > 0 && keys[base - 1] == keys[base];
-  const bool cont_out = m > 0 && base + m < n && keys[base + m] == keys[base + m - 1];
-  for (int r = t; r < total; r += kBT) {
-    const int s0 = starts[r], len = starts[r + 1] - s0;
-    const uint32_t key = keys[base + s0];
-    if ((r == 0 && cont_in) || (r == total - 1 && cont_out)) {
-      atomicAdd(&cnt[key], len);
-    } else {
-      cnt[key] = len;
+  for (int j = 0; j < kRpItems; ++j) {
+    const int64_t p = base + (int64_t)j * kBT;
+    const int32_t up = __shfl_up(k[j], 1, 64);
+    const int32_t prev = lane == 0 ? head[j] : up;
+    if (p < n) {
+      if (k[j] != prev) row_gap(ptr, prev + 1, k[j] + 1, (int32_t)p, gaps, n_gaps);
+      if (p == n - 1) row_gap(ptr, k[j] + 1, nq + 1, (int32_t)n, gaps, n_gaps);
     }
   }
 }
+
+__global__ void __launch_bounds__(kBT) k_row_gaps(const int4* __restrict__ gaps, const int32_t* __restrict__ n_gaps,
+                                                  int32_t* __restrict__ ptr) {
+  const int32_t n = *n_gaps;
+  for (int32_t i = blockIdx.x; i < n; i += gridDim.x) {
+    const int4 g = gaps[i];
+    for (int32_t q = g.x + (int32_t)threadIdx.x; q < g.y; q += kBT) ptr[q] = g.z;
+  }
+}
+
+// Entries the gap list can hold: gaps longer than kRpInline rows, each a
+// piece more than its full pieces.
+inline int64_t gap_cap(int64_t nq) { return nq / kRpInline + nq / kRpPiece + 2; }
 
 // The CSC sort's input, taken from the CSR in its order: the key (source, r)
 // = csr_col[p] * R + r and, as the value, the destination with the in-degree
@@ -922,120 +915,217 @@ __global__ void k_gather_w(const int32_t* __restrict__ eid, const float* __restr
   GRID_STRIDE(p, n) out[p] = edge_w[eid[p]];
 }
 
-// Per CSC row q: relation digit for the active-source partition, work-item
-// counts, and the slot table's active mask and count of each 64 rows (one
-// wave covers 64 consecutive rows: the grid stride is a multiple of 64).
-__global__ void __launch_bounds__(kBT) k_active_digit(const int32_t* __restrict__ csc_ptr, int64_t nq, int32_t n_rel,
-                                                      uint8_t* __restrict__ digit, int32_t* __restrict__ srcid,
-                                                      int32_t* __restrict__ n_items, int32_t* __restrict__ n_heavy,
-                                                      int32_t* __restrict__ n_parts, SlotEnt* __restrict__ tab,
-                                                      int32_t* __restrict__ tab_cnt) {
-  const int lane = threadIdx.x & 63;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q - lane < nq; q += stride) {
-    const bool live = q < nq;
-    const int32_t len = live ? csc_ptr[q + 1] - csc_ptr[q] : 0;
-    if (live) {
-      digit[q] = len > 0 ? (uint8_t)(q % n_rel) : (uint8_t)255;
-      srcid[q] = (int32_t)(q / n_rel);
-      const int32_t nch = (len + kChunk - 1) / kChunk;
-      n_items[q] = nch;
-      n_heavy[q] = nch > 1 ? 1 : 0;
-      n_parts[q] = nch > 1 ? nch : 0;
-    }
+// ---- execution plan -----------------------------------------------------------
+// Tiles of kPN consecutive nodes (kPN * R rows of the CSC: whole 64-row groups
+// of the slot table).  k_plan_count writes, per tile, the number of active
+// rows, work items, split rows and their chunks, the long destination rows and
+// their chunks, and the active sources of every relation, as 6 + R streams of
+// one count per tile laid end to end; one scan of the whole turns a stream's
+// entry minus its first into the tile's offset (sums may wrap, differences do
+// not).  k_plan_fill forms the in-tile ranks again from ballots and writes the
+// plan.  Two reads of csc_ptr and the plan's own bytes bound it; digits, counts
+// and source ids per row (17 bytes a row) with four scans over all rows and a
+// partition by relation took 1.6 ms at 50M rows where this takes 0.3 ms.
+constexpr int kPN = kBT;
+constexpr int kPW = kPN / 64;
+enum : int { P_ACT = 0, P_ITEMS, P_HEAVY, P_PARTS, P_FHEAVY, P_FPARTS, P_REL };
+
+__device__ __forceinline__ int wave_sum(int v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+
+// Exclusive sum over the lanes of a wave.
+__device__ __forceinline__ int wave_before(int v) {
+  int inc = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int u = __shfl_up(inc, o, 64);
+    if ((int)(threadIdx.x & 63) >= o) inc += u;
+  }
+  return inc - v;
+}
+
+__device__ __forceinline__ int chunks_of(int32_t len) { return (len + kChunk - 1) / kChunk; }
+__device__ __forceinline__ int fwd_chunks_of(int32_t len) {
+  return len > kFwdChunk ? (len + kFwdChunk - 1) / kFwdChunk : 0;
+}
+
+// Bit of tile row w (w = node * R + r inside the tile) in the tile's masks.
+__device__ __forceinline__ bool tile_bit(const uint64_t* mask, int w) { return (mask[w >> 6] >> (w & 63)) & 1ull; }
+
+__global__ void __launch_bounds__(kBT) k_plan_count(const int32_t* __restrict__ csc_ptr,
+                                                    const int32_t* __restrict__ csr_ptr, int64_t ns, int32_t R,
+                                                    int64_t tiles, int32_t* __restrict__ cnt) {
+  __shared__ uint64_t mask[kPW * HG_MAX_REL];
+  __shared__ int32_t wcnt[kPW][HG_MAX_REL];
+  __shared__ int32_t wtot[kPW][6];
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  const int64_t tile = blockIdx.x, nq = ns * R;
+  int act = 0, items = 0, heavy = 0, parts = 0;
+  for (int g = 0; g < R; ++g) {  // the wave's 64 nodes: R groups of 64 rows
+    const int64_t q = (tile * kPN + 64 * w) * R + 64 * g + l;
+    const int32_t len = q < nq ? csc_ptr[q + 1] - csc_ptr[q] : 0;
     const uint64_t m = __ballot(len > 0);
-    if (lane == 0) {
-      tab[q >> 6].mask = m;
-      tab_cnt[q >> 6] = (int32_t)__popcll(m);
+    if (l == 0) mask[w * R + g] = m;
+    const int nch = chunks_of(len);
+    act += len > 0;
+    items += nch;
+    heavy += nch > 1;
+    parts += nch > 1 ? nch : 0;
+  }
+  const int64_t j = tile * kPN + threadIdx.x;
+  const int fch = j < ns ? fwd_chunks_of(csr_ptr[(j + 1) * R] - csr_ptr[j * R]) : 0;
+  const int v[6] = {act, items, heavy, parts, fch > 0, fch};
+#pragma unroll
+  for (int i = 0; i < 6; ++i) {
+    const int t = wave_sum(v[i]);
+    if (l == 0) wtot[w][i] = t;
+  }
+  // per relation, from the masks the wave's first lane wrote
+  __builtin_amdgcn_wave_barrier();
+  for (int r = 0; r < R; ++r) {
+    const uint64_t m = __ballot(tile_bit(mask, (64 * w + l) * R + r));
+    if (l == 0) wcnt[w][r] = (int32_t)__popcll(m);
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < 6 + R; i += kBT) {
+    int32_t t = 0;
+#pragma unroll
+    for (int q = 0; q < kPW; ++q) t += i < 6 ? wtot[q][i] : wcnt[q][i - 6];
+    cnt[(int64_t)i * tiles + tile] = t;
+  }
+  if (tile == 0 && threadIdx.x == 0) cnt[(int64_t)(6 + R) * tiles] = 0;  // the scan's end: the grand total
+}
+
+struct PlanOut {
+  int4 *items, *heavy, *fitems, *fheavy;
+  int32_t *act, *act_off, *act_slot, *slot_q;
+  SlotEnt* tab;
+};
+
+// Chunks of a split row by all lanes: item (x, begin, end, partial slot) c of
+// the row at out[c].
+__device__ __forceinline__ void wave_chunks(int4* __restrict__ out, int32_t x, int32_t beg, int32_t end, int32_t so,
+                                            int nch, int chunk) {
+  for (int c = threadIdx.x & 63; c < nch; c += 64) {
+    const int32_t b = beg + c * chunk;
+    out[c] = make_int4(x, b, end - b < chunk ? end : b + chunk, so + c);
+  }
+}
+
+__global__ void __launch_bounds__(kBT) k_plan_fill(const int32_t* __restrict__ csc_ptr,
+                                                   const int32_t* __restrict__ csr_ptr, int64_t ns, int32_t R,
+                                                   int64_t tiles, const int32_t* __restrict__ S, PlanOut o,
+                                                   int32_t* __restrict__ cnt) {
+  __shared__ uint64_t mask[kPW * HG_MAX_REL];
+  __shared__ int32_t before[kPW * HG_MAX_REL];  // active rows before each 64-row group
+  __shared__ int32_t wcnt[kPW][HG_MAX_REL];
+  __shared__ int32_t wtot[kPW][6];
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  const uint64_t lt = (l == 0) ? 0ull : (~0ull >> (64 - l));
+  const int64_t tile = blockIdx.x, nq = ns * R;
+  const bool by_row = row_layout(nq, S[tiles] - S[0]);
+  int act = 0, items = 0, heavy = 0, parts = 0;
+  for (int g = 0; g < R; ++g) {
+    const int64_t q = (tile * kPN + 64 * w) * R + 64 * g + l;
+    const int32_t len = q < nq ? csc_ptr[q + 1] - csc_ptr[q] : 0;
+    const uint64_t m = __ballot(len > 0);
+    if (l == 0) mask[w * R + g] = m;
+    const int nch = chunks_of(len);
+    act += len > 0;
+    items += nch;
+    heavy += nch > 1;
+    parts += nch > 1 ? nch : 0;
+  }
+  const int64_t j = tile * kPN + threadIdx.x;
+  const int32_t fbeg = j < ns ? csr_ptr[j * R] : 0, fend = j < ns ? csr_ptr[(j + 1) * R] : 0;
+  const int fch = fwd_chunks_of(fend - fbeg);
+  const int v[6] = {act, items, heavy, parts, fch > 0, fch};
+#pragma unroll
+  for (int i = 0; i < 6; ++i) {
+    const int t = wave_sum(v[i]);
+    if (l == 0) wtot[w][i] = t;
+  }
+  __builtin_amdgcn_wave_barrier();
+  for (int r = 0; r < R; ++r) {
+    const uint64_t m = __ballot(tile_bit(mask, (64 * w + l) * R + r));
+    if (l == 0) wcnt[w][r] = (int32_t)__popcll(m);
+  }
+  __syncthreads();
+  int32_t at[6];  // the wave's offset in each stream
+#pragma unroll
+  for (int i = 0; i < 6; ++i) {
+    at[i] = S[i * tiles + tile] - S[i * tiles];
+    for (int q = 0; q < w; ++q) at[i] += wtot[q][i];
+  }
+  for (int g = 0; g < R; ++g) {
+    const int64_t q = (tile * kPN + 64 * w) * R + 64 * g + l;
+    const bool live = q < nq;
+    const int32_t beg = live ? csc_ptr[q] : 0, end = live ? csc_ptr[q + 1] : 0;
+    const int nch = chunks_of(end - beg);
+    const uint64_t m = __ballot(nch > 0), hm = __ballot(nch > 1);
+    const int32_t rank = at[P_ACT] + (int32_t)__popcll(m & lt);
+    const int32_t sl = by_row ? (int32_t)q : rank;
+    if (l == 0) before[w * R + g] = at[P_ACT];
+    if (!by_row) {
+      if (nch > 0) o.slot_q[rank] = (int32_t)q;
+      if (l == 0 && live) o.tab[q >> 6] = SlotEnt{m, at[P_ACT], 0};
     }
-  }
-}
-
-// The count before each 64 rows; for the row-indexed layout the identity
-// (all rows marked, 64 b before block b), so that slot(q) = q.
-__global__ void k_slot_pack(const int32_t* __restrict__ pre, int64_t nb, int64_t nq,
-                            const int32_t* __restrict__ a_total, SlotEnt* __restrict__ tab) {
-  const bool by_row = row_layout(nq, *a_total);
-  GRID_STRIDE(b, nb) {
-    if (by_row) tab[b].mask = ~0ull;
-    tab[b].pre = by_row ? (int32_t)(64 * b) : pre[b];
-    tab[b].pad = 0;
-  }
-}
-
-// Work items of the CSC rows (first field: the row's slot) and the slot ->
-// row map.
-__global__ void k_plan_items(const int32_t* __restrict__ csc_ptr, int64_t nq,
-                             const int32_t* __restrict__ item_off, const int32_t* __restrict__ heavy_off,
-                             const int32_t* __restrict__ part_off, const SlotEnt* __restrict__ tab,
-                             const int32_t* __restrict__ a_total, int4* __restrict__ items, int4* __restrict__ heavy,
-                             int32_t* __restrict__ slot_q) {
-  const bool by_row = row_layout(nq, *a_total);
-  GRID_STRIDE(q, nq) {
-    const int32_t beg = csc_ptr[q], end = csc_ptr[q + 1];
-    const int32_t len = end - beg;
-    if (len <= 0) continue;
-    const int32_t sl = slot_of(tab, q);
-    if (!by_row) slot_q[sl] = (int32_t)q;
-    const int32_t nch = (len + kChunk - 1) / kChunk;
-    const int32_t io = item_off[q];
-    if (nch == 1) {
-      items[io] = make_int4(sl, beg, end, -1);
-    } else {
-      const int32_t so = part_off[q];
-      for (int32_t c = 0; c < nch; ++c) {
-        const int32_t b = beg + c * kChunk;
-        const int32_t e2 = min(end, b + kChunk);
-        items[io + c] = make_int4(sl, b, e2, so + c);
+    const int32_t io = at[P_ITEMS] + wave_before(nch);
+    if (nch == 1) o.items[io] = make_int4(sl, beg, end, -1);
+    if (hm) {
+      const int32_t so = at[P_PARTS] + wave_before(nch > 1 ? nch : 0);
+      if (nch > 1) o.heavy[at[P_HEAVY] + (int32_t)__popcll(hm & lt)] = make_int4(sl, so, nch, 0);
+      for (uint64_t left = hm; left; left &= left - 1) {
+        const int u = __ffsll((unsigned long long)left) - 1;
+        wave_chunks(o.items + __shfl(io, u, 64), __shfl(sl, u, 64), __shfl(beg, u, 64), __shfl(end, u, 64),
+                    __shfl(so, u, 64), __shfl(nch, u, 64), kChunk);
       }
-      heavy[heavy_off[q]] = make_int4(sl, so, nch, 0);
+      at[P_PARTS] += wave_sum(nch > 1 ? nch : 0);
+      at[P_HEAVY] += (int32_t)__popcll(hm);
+    }
+    at[P_ACT] += (int32_t)__popcll(m);
+    at[P_ITEMS] += hm ? wave_sum(nch) : (int32_t)__popcll(m);
+  }
+  // active sources of every relation, ascending, with their slots
+  __builtin_amdgcn_wave_barrier();
+  for (int r = 0; r < R; ++r) {
+    const int row = (64 * w + l) * R + r;
+    const bool on = tile_bit(mask, row);
+    const uint64_t m = __ballot(on);
+    if (on) {
+      int32_t p = S[(int64_t)(P_REL + r) * tiles + tile] - S[(int64_t)P_REL * tiles];
+      for (int q = 0; q < w; ++q) p += wcnt[q][r];
+      p += (int32_t)__popcll(m & lt);
+      o.act[p] = (int32_t)j;
+      o.act_slot[p] = by_row ? (int32_t)(j * R + r)
+                             : before[row >> 6] + (int32_t)__popcll(mask[row >> 6] & ((1ull << (row & 63)) - 1ull));
     }
   }
-}
-
-// Destination rows longer than kFwdChunk entries: per node j a 0/1 flag
-// and its number of chunks (0 for the rows one wave walks).
-__global__ void k_fwd_counts(const int32_t* __restrict__ csr_ptr, int64_t ns, int32_t n_rel,
-                             int32_t* __restrict__ heavy_flag, int32_t* __restrict__ n_parts) {
-  GRID_STRIDE(j, ns) {
-    const int32_t len = csr_ptr[(j + 1) * n_rel] - csr_ptr[j * n_rel];
-    const int32_t nch = len > kFwdChunk ? (len + kFwdChunk - 1) / kFwdChunk : 0;
-    heavy_flag[j] = nch > 0 ? 1 : 0;
-    n_parts[j] = nch;
-  }
-}
-
-// The chunks of the long destination rows (each chunk is one partial slot)
-// and one entry per long row.
-__global__ void k_fwd_items(const int32_t* __restrict__ csr_ptr, int64_t ns, int32_t n_rel,
-                            const int32_t* __restrict__ heavy_off, const int32_t* __restrict__ part_off,
-                            int4* __restrict__ items, int4* __restrict__ heavy) {
-  GRID_STRIDE(j, ns) {
-    const int32_t beg = csr_ptr[j * n_rel], end = csr_ptr[(j + 1) * n_rel];
-    const int32_t len = end - beg;
-    if (len <= kFwdChunk) continue;
-    const int32_t nch = (len + kFwdChunk - 1) / kFwdChunk;
-    const int32_t so = part_off[j];
-    for (int32_t c = 0; c < nch; ++c) {
-      const int32_t b = beg + c * kFwdChunk;
-      items[so + c] = make_int4((int32_t)j, b, min(end, b + kFwdChunk), so + c);
+  // long destination rows
+  const uint64_t fm = __ballot(fch > 0);
+  if (fm) {
+    const int32_t so = at[P_FPARTS] + wave_before(fch);
+    if (fch > 0) o.fheavy[at[P_FHEAVY] + (int32_t)__popcll(fm & lt)] = make_int4((int32_t)j, so, fch, 0);
+    for (uint64_t left = fm; left; left &= left - 1) {
+      const int u = __ffsll((unsigned long long)left) - 1;
+      const int32_t so_u = __shfl(so, u, 64);
+      wave_chunks(o.fitems + so_u, (int32_t)(tile * kPN + 64 * w + u), __shfl(fbeg, u, 64), __shfl(fend, u, 64), so_u,
+                  __shfl(fch, u, 64), kFwdChunk);
     }
-    heavy[heavy_off[j]] = make_int4((int32_t)j, so, nch, 0);
   }
-}
-
-// Slot of each entry of the per-relation active-source lists.
-__global__ void k_act_slot(const int32_t* __restrict__ act, const int32_t* __restrict__ act_off, int32_t n_rel,
-                           int64_t cap, const SlotEnt* __restrict__ tab, int32_t* __restrict__ act_slot) {
-  const int64_t n = act_off[n_rel];
-  GRID_STRIDE(k, cap) {
-    if (k >= n) break;
-    int32_t lo = 0, hi = n_rel;  // act_off[lo] <= k < act_off[hi]
-    while (hi - lo > 1) {
-      const int32_t mid = (lo + hi) >> 1;
-      if (act_off[mid] <= k) lo = mid; else hi = mid;
+  if (tile == 0) {
+    for (int r = threadIdx.x; r <= R; r += kBT) o.act_off[r] = S[(int64_t)(P_REL + r) * tiles] - S[(int64_t)P_REL * tiles];
+    if (threadIdx.x == 0) {
+      cnt[C_ASLOTS] = S[tiles] - S[0];
+      cnt[C_ITEMS] = S[2 * tiles] - S[tiles];
+      cnt[C_HEAVY] = S[3 * tiles] - S[2 * tiles];
+      cnt[C_PARTS] = S[4 * tiles] - S[3 * tiles];
+      cnt[C_FHEAVY] = S[5 * tiles] - S[4 * tiles];
+      cnt[C_FPARTS] = S[6 * tiles] - S[5 * tiles];
     }
-    act_slot[k] = slot_of(tab, (int64_t)act[k] * n_rel + lo);
   }
 }
 
@@ -1061,14 +1151,17 @@ int bits_for(int64_t nvals) {
   return b;
 }
 
+// Counts of the plan's tiles: 6 + R streams and the end of the scan.
+inline int64_t plan_counts(int64_t n, int64_t R) { return (6 + R) * cdiv(n > 0 ? n : 1, kPN) + 1; }
+
 // Workspace layout, shared by the sizing and the run.
 template <class A>
 struct BuildWs {
   int32_t *cnt, *outdeg, *first, *key, *flag, *pos, *list, *iota, *hoff, *hist;
   uint8_t *sel, *digit;
   SelectState* st;
-  int32_t *keep, *vsrc, *vdst, *veid, *alt1, *alt2, *alt3, *rowcnt, *q_items, *q_heavy, *q_parts,
-      *q_src, *scratch, *bcnt;
+  int32_t *keep, *vsrc, *vdst, *veid, *alt1, *alt2, *alt3, *pcnt, *scratch, *bcnt;
+  int4* gaps;
   int32_t* vw;                // weighted graphs: edge weights (float bits) of the kept edges in edge order
   int32_t *vsc, *vsc_alt;     // unpacked CSC sort: the scales (float bits) and their ping-pong buffer
   uint32_t *kcsr, *kcsc, *kalt, *bbits, *mbits;
@@ -1095,7 +1188,7 @@ struct BuildWs {
     rc0 = a.template take<int32_t>(N / kRankGroup + 2);
     rc1 = a.template take<int32_t>(N / kRankGroup + 2);
     tile_cnt = a.template take<int32_t>(E / kETile + 2);
-    digit = a.template take<uint8_t>(NQ > N ? NQ : N);
+    digit = a.template take<uint8_t>(N);
     st = a.template take<SelectState>(1);
     keep = a.template take<int32_t>(E + 1);
     kcsr = a.template take<uint32_t>(E);
@@ -1107,20 +1200,29 @@ struct BuildWs {
     alt1 = a.template take<int32_t>(E);
     alt2 = a.template take<int32_t>(E);
     alt3 = a.template take<int32_t>(E);
-    rowcnt = a.template take<int32_t>(NQ);
-    q_items = a.template take<int32_t>(NQ);
-    q_heavy = a.template take<int32_t>(NQ);
-    q_parts = a.template take<int32_t>(NQ);
-    q_src = a.template take<int32_t>(NQ);
+    gaps = a.template take<int4>(gap_cap(NQ));
+    pcnt = a.template take<int32_t>(plan_counts(N, R));
     vw = a.template take<int32_t>(weighted ? E : 0);
     const bool unpacked = weighted || N >= kPackedMaxNodes;
     vsc = a.template take<int32_t>(unpacked ? E : 0);
     vsc_alt = a.template take<int32_t>(unpacked ? E : 0);
-    int64_t sc = scan_scratch_elems(E + N + NQ + 1);
-    int64_t rs = radix_scratch_elems(E > NQ ? E : NQ);
+    const int64_t longest = E + N + 1 > plan_counts(N, R) ? E + N + 1 : plan_counts(N, R);
+    int64_t sc = scan_scratch_elems(longest);
+    int64_t rs = radix_scratch_elems(E > N ? E : N);
     scratch = a.template take<int32_t>(sc > rs ? sc : rs);
   }
 };
+
+int row_pointers(const uint32_t* keys, int64_t n, int64_t nq, int32_t* ptr, int4* gaps, int32_t* n_gaps,
+                 hipStream_t s) {
+  if (n <= 0) return fill_i32(ptr, 0, nq + 1, s);
+  HG_LAUNCH("build_row_ptr", k_row_ptr, dim3((unsigned)cdiv(n, kBT * kRpItems)), dim3(kBT), 0, s, keys, n, (int32_t)nq,
+            ptr, gaps, n_gaps);
+  const int64_t cap = gap_cap(nq), most = 4 * (int64_t)num_cus();
+  HG_LAUNCH("build_row_gaps", k_row_gaps, dim3((unsigned)(cap < most ? cap : most)), dim3(kBT), 0, s,
+            (const int4*)gaps, (const int32_t*)n_gaps, ptr);
+  return HG_OK;
+}
 
 struct PlanLayout {
   size_t s_off, soff_off, aslot_off, slotq_off, cslot_off, tab_off, items_off, heavy_off, fitems_off, fheavy_off,
@@ -1483,11 +1585,7 @@ extern "C" int hg_build_csr(const hg_graph_desc* g, const hg_overlap_desc* o, hg
     if (want_eid && weighted && ES > 0)
       HG_LAUNCH("build_csr_w", k_gather_w, dim3(grid_for(ES)), dim3(kBT), 0, s, (const int32_t*)out->csr_eid,
                 g->edge_w, ES, out->csr_w);
-    HG_TRY(fill_i32(w.rowcnt, 0, NQ + 1, s));
-    if (ES > 0)
-      HG_LAUNCH("build_row_count", k_row_count, dim3((unsigned)cdiv(ES, kRCChunk)), dim3(kBT), 0, s,
-                (const uint32_t*)ko, ES, w.rowcnt);
-    HG_TRY(scan_exclusive_i32(w.rowcnt, out->csr_ptr, NQ + 1, nullptr, w.scratch, s));
+    HG_TRY(row_pointers(ko, ES, NQ, out->csr_ptr, w.gaps, w.cnt + C_GAP_CSR, s));
   }
   {
     // the CSC sort's input from the CSR in its order (the CSR keys stay
@@ -1509,11 +1607,7 @@ extern "C" int hg_build_csr(const hg_graph_desc* g, const hg_overlap_desc* o, hg
       HG_HIP_TRY(hipMemcpyAsync(out->csc_row, v1o, sizeof(int32_t) * ES, hipMemcpyDeviceToDevice, s));
       HG_HIP_TRY(hipMemcpyAsync(scale_bits, v2o, sizeof(int32_t) * ES, hipMemcpyDeviceToDevice, s));
     }
-    HG_TRY(fill_i32(w.rowcnt, 0, NQ + 1, s));
-    if (ES > 0)
-      HG_LAUNCH("build_row_count", k_row_count, dim3((unsigned)cdiv(ES, kRCChunk)), dim3(kBT), 0, s,
-                (const uint32_t*)ko, ES, w.rowcnt);
-    HG_TRY(scan_exclusive_i32(w.rowcnt, out->csc_ptr, NQ + 1, nullptr, w.scratch, s));
+    HG_TRY(row_pointers(ko, ES, NQ, out->csc_ptr, w.gaps, w.cnt + C_GAP_CSC, s));
   }
   // 8. plan: active-source lists and backward work items
   PlanLayout pl(N, E, R);
@@ -1527,39 +1621,25 @@ extern "C" int hg_build_csr(const hg_graph_desc* g, const hg_overlap_desc* o, hg
   int32_t* csr_slot = reinterpret_cast<int32_t*>(pb + pl.cslot_off);
   SlotEnt* tab = reinterpret_cast<SlotEnt*>(pb + pl.tab_off);
   if (NQ > 0) {
-    const int64_t nb = NQ / 64 + 1;  // w.rowcnt (NQ + 1 entries) is free: it holds the slot counts
-    HG_TRY(fill_i32(w.rowcnt, 0, nb, s));
-    HG_LAUNCH("build_active_digit", k_active_digit, dim3(grid_for(NQ)), dim3(kBT), 0, s,
-              (const int32_t*)out->csc_ptr, NQ, (int32_t)R, w.digit, w.q_src, w.q_items, w.q_heavy,
-              w.q_parts, tab, w.rowcnt);
-    HG_TRY(scan_exclusive_i32(w.rowcnt, w.rowcnt, nb, w.cnt + C_ASLOTS, w.scratch, s));
-    HG_LAUNCH("build_slot_pack", k_slot_pack, dim3(grid_for(nb)), dim3(kBT), 0, s, (const int32_t*)w.rowcnt, nb,
-              NQ, (const int32_t*)(w.cnt + C_ASLOTS), tab);
-    HG_TRY(bucket_partition(w.digit, w.q_src, NQ, (int)R, act, act_off, w.scratch, s));
-    HG_TRY(scan_exclusive_i32(w.q_items, w.q_items, NQ, w.cnt + C_ITEMS, w.scratch, s));
-    HG_TRY(scan_exclusive_i32(w.q_heavy, w.q_heavy, NQ, w.cnt + C_HEAVY, w.scratch, s));
-    HG_TRY(scan_exclusive_i32(w.q_parts, w.q_parts, NQ, w.cnt + C_PARTS, w.scratch, s));
-    HG_LAUNCH("build_plan_items", k_plan_items, dim3(grid_for(NQ)), dim3(kBT), 0, s,
-              (const int32_t*)out->csc_ptr, NQ, (const int32_t*)w.q_items, (const int32_t*)w.q_heavy,
-              (const int32_t*)w.q_parts, (const SlotEnt*)tab, (const int32_t*)(w.cnt + C_ASLOTS), items, heavy,
-              slot_q);
-    const int64_t cap_a = NQ < ES ? NQ : ES;
-    if (cap_a > 0)
-      HG_LAUNCH("build_act_slot", k_act_slot, dim3(grid_for(cap_a)), dim3(kBT), 0, s, (const int32_t*)act,
-                (const int32_t*)act_off, (int32_t)R, cap_a, (const SlotEnt*)tab, act_slot);
+    const int64_t tiles = cdiv(NS, kPN);
+    const PlanOut po{items,
+                     heavy,
+                     reinterpret_cast<int4*>(pb + pl.fitems_off),
+                     reinterpret_cast<int4*>(pb + pl.fheavy_off),
+                     act,
+                     act_off,
+                     act_slot,
+                     slot_q,
+                     tab};
+    HG_LAUNCH("build_plan_count", k_plan_count, dim3((unsigned)tiles), dim3(kBT), 0, s, (const int32_t*)out->csc_ptr,
+              (const int32_t*)out->csr_ptr, NS, (int32_t)R, tiles, w.pcnt);
+    HG_TRY(scan_exclusive_i32(w.pcnt, w.pcnt, (6 + R) * tiles + 1, nullptr, w.scratch, s));
+    HG_LAUNCH("build_plan_fill", k_plan_fill, dim3((unsigned)tiles), dim3(kBT), 0, s, (const int32_t*)out->csc_ptr,
+              (const int32_t*)out->csr_ptr, NS, (int32_t)R, tiles, (const int32_t*)w.pcnt, po, w.cnt);
     if (ES > 0)
       HG_LAUNCH("build_csr_slot", k_csr_slot, dim3(grid_for(ES)), dim3(kBT), 0, s, (const int32_t*)out->csr_col,
                 (const uint32_t*)csr_keys, ES, (int32_t)R, NQ, (const int32_t*)(w.cnt + C_ASLOTS),
                 (const SlotEnt*)tab, csr_slot);
-    // long destination rows and their chunks (w.q_items, w.q_heavy are free again)
-    int4* fitems = reinterpret_cast<int4*>(pb + pl.fitems_off);
-    int4* fheavy = reinterpret_cast<int4*>(pb + pl.fheavy_off);
-    HG_LAUNCH("build_fwd_counts", k_fwd_counts, dim3(grid_for(NS)), dim3(kBT), 0, s, (const int32_t*)out->csr_ptr,
-              NS, (int32_t)R, w.q_heavy, w.q_items);
-    HG_TRY(scan_exclusive_i32(w.q_heavy, w.q_heavy, NS, w.cnt + C_FHEAVY, w.scratch, s));
-    HG_TRY(scan_exclusive_i32(w.q_items, w.q_items, NS, w.cnt + C_FPARTS, w.scratch, s));
-    HG_LAUNCH("build_fwd_items", k_fwd_items, dim3(grid_for(NS)), dim3(kBT), 0, s, (const int32_t*)out->csr_ptr, NS,
-              (int32_t)R, (const int32_t*)w.q_heavy, (const int32_t*)w.q_items, fitems, fheavy);
   } else {
     HG_TRY(fill_i32(act_off, 0, R + 1, s));
     HG_TRY(fill_i32(w.cnt + C_ITEMS, 0, 3, s));
