@@ -17,6 +17,7 @@
 //      row pointers read off the sorted keys; csc_scale = 1/deg_r(dst);
 //   8. the execution plan: per-relation active-source lists and the chunked
 //      work list of the atomic-free transposed SpMM.
+#include <algorithm>
 #include <vector>
 
 #include "hg_internal.h"
@@ -58,13 +59,24 @@ __host__ __device__ inline bool dense_build(int64_t n_base, int64_t budget, int6
   return 4 * (n_base + b) >= 3 * n_nodes;
 }
 
+// TopM takes the smallest composites (key, splitmix64(seed ^ gid)); the hash is
+// a bijection of the gid, so composites are unique.  The search narrows the
+// range [lo, hi] that holds the last one taken, a digit of up to 11 bits at a
+// time; the selected set is then every candidate up to (khi, hhi).
+constexpr int kSelBins = 2048;   // values of a digit
+constexpr int kSelSmall = 1024;  // a range this small is ranked by one block
+enum : uint32_t { S_SEARCH = 0, S_DONE, S_NONE, S_COLLECT, S_RANK };
 struct SelectState {
-  uint32_t k_rem;   // how many more to take from the current prefix bucket
-  uint32_t mode;    // 0 = searching, 1 = done (take composite prefix <= digits), 2 = take none
-  uint32_t npass;   // number of fixed leading digits
+  uint64_t hlo, hhi;  // hash range, when klo == khi
+  uint32_t klo, khi;  // key range
+  uint32_t k_rem;     // how many to take from the range
+  uint32_t mode;      // S_DONE: all of the range; S_NONE: no candidate; S_COLLECT, S_RANK: the range is small
+  uint32_t level;     // digit of the next histogram
+  uint32_t done;      // blocks of the current launch that have finished
+  uint32_t n_small;
   uint32_t pad;
-  uint32_t digits[16];
-  int32_t hist[256];
+  uint64_t small[kSelSmall][2];  // (key, hash) of a small range
+  int32_t hist[kSelBins];
 };
 
 __device__ __forceinline__ uint64_t splitmix64_first(uint64_t state) {
@@ -76,28 +88,66 @@ __device__ __forceinline__ uint64_t splitmix64_first(uint64_t state) {
   return z ^ (z >> 31);
 }
 
-// Byte p (0 = most significant) of the 128-bit composite (key, hash, gid).
-__device__ __forceinline__ uint32_t composite_digit(uint32_t key, uint64_t h, uint32_t gid, int p) {
-  uint32_t w;
-  switch (p >> 2) {
-    case 0: w = key; break;
-    case 1: w = (uint32_t)(h >> 32); break;
-    case 2: w = (uint32_t)h; break;
-    default: w = gid; break;
+// Digit of a level: small keys whole (0; larger ones share its last value),
+// larger keys in three digits (1-3), then the hash from the top (4-9).
+__device__ __forceinline__ uint32_t select_digit(uint32_t level, uint32_t key, uint64_t h) {
+  switch (level) {
+    case 0: return key < kSelBins - 1 ? key : kSelBins - 1;
+    case 1: return key >> 21;
+    case 2: return (key >> 10) & 2047u;
+    case 3: return key & 1023u;
+    case 9: return (uint32_t)(h & 511u);
+    default: return (uint32_t)(h >> (53 - 11 * (level - 4))) & 2047u;
   }
-  return (w >> (8 * (3 - (p & 3)))) & 0xFFu;
 }
 
-// bits[v / 32] bit v % 32 = pred(v); one wave covers 64 nodes (two words).
-// Also |V_k|, as one partial count per block (summed by k_sum_counts).
-__global__ void __launch_bounds__(kBT) k_base_bits(const int32_t* __restrict__ part, int32_t k, int64_t n,
-                                                   uint32_t* __restrict__ bits, int32_t* __restrict__ block_cnt) {
-  __shared__ int32_t wc[kBT / 64];
-  int32_t c = 0;  // the same in every lane of a wave
+// The range left by digit d of a level, and the next level.
+__device__ __forceinline__ void select_narrow(SelectState* st, uint32_t level, uint32_t d) {
+  if (level == 0) {
+    st->klo = d;
+    st->khi = d < kSelBins - 1 ? d : ~0u;
+    st->level = d < kSelBins - 1 ? 4 : 1;
+  } else if (level <= 3) {
+    const int sh = level == 1 ? 21 : (level == 2 ? 10 : 0);
+    const uint32_t top = level == 1 ? 0u : st->khi & ~((1u << (level == 2 ? 21 : 10)) - 1u);
+    const uint32_t lo = top | (d << sh);
+    st->klo = lo > st->klo ? lo : st->klo;
+    st->khi = lo | ((1u << sh) - 1u);
+    st->level = level + 1;
+    if (level == 3) st->klo = st->khi;
+  } else {
+    const int sh = level == 9 ? 0 : 53 - 11 * ((int)level - 4);
+    st->hlo |= (uint64_t)d << sh;
+    st->hhi = st->hlo | ((1ull << sh) - 1ull);
+    st->level = level + 1;
+  }
+}
+
+__device__ __forceinline__ bool select_in_range(const SelectState* st, uint32_t key, uint64_t h) {
+  if (key < st->klo || key > st->khi) return false;
+  return st->klo != st->khi || (h >= st->hlo && h <= st->hhi);
+}
+
+// Every node's start: base_bits[v / 32] bit v % 32 = (part[v] == k) (one wave
+// covers 64 nodes, two words), first[v] = n_edges, outdeg[v] = 0, the range
+// check of its type; |V_k| and the check as one word per block (count, and bit
+// 31 for a type out of range), summed by k_init_counts.
+__global__ void __launch_bounds__(kBT) k_init_nodes(const int32_t* __restrict__ part, int32_t k,
+                                                    const uint8_t* __restrict__ ntype, int32_t n_ntype, int64_t n,
+                                                    int32_t n_edges, uint32_t* __restrict__ bits,
+                                                    int32_t* __restrict__ first, int32_t* __restrict__ outdeg,
+                                                    uint32_t* __restrict__ block_cnt) {
+  __shared__ uint32_t wc[kBT / 64];
+  uint32_t c = 0;  // the same in every lane of a wave
   GRID_STRIDE(v0, cdiv_dev(n, 64) * 64) {
-    const bool in = v0 < n && part[v0] == k;
-    const uint64_t m = __ballot(in);
-    c += (int32_t)__popcll(m);
+    const bool live = v0 < n;
+    const uint64_t m = __ballot(live && part[v0] == k);
+    if (__ballot(live && ntype[v0] >= n_ntype)) c |= 0x80000000u;
+    c += (uint32_t)__popcll(m);
+    if (live) {
+      first[v0] = n_edges;
+      outdeg[v0] = 0;
+    }
     if ((threadIdx.x & 63) == 0) {
       const int64_t wd = v0 >> 5;
       bits[wd] = (uint32_t)m;
@@ -107,25 +157,50 @@ __global__ void __launch_bounds__(kBT) k_base_bits(const int32_t* __restrict__ p
   if ((threadIdx.x & 63) == 0) wc[threadIdx.x >> 6] = c;
   __syncthreads();
   if (threadIdx.x == 0) {
-    int32_t t = 0;
-    for (int q = 0; q < kBT / 64; ++q) t += wc[q];
-    block_cnt[blockIdx.x] = t;
+    uint32_t t = 0, bad = 0;
+    for (int q = 0; q < kBT / 64; ++q) {
+      t += wc[q] & 0x7FFFFFFFu;
+      bad |= wc[q] & 0x80000000u;
+    }
+    block_cnt[blockIdx.x] = t | bad;
   }
 }
 
-// out[0] = sum of the nb block counts (one block, fixed order).
-__global__ void __launch_bounds__(256) k_sum_counts(const int32_t* __restrict__ block_cnt, int nb,
-                                                    int32_t* __restrict__ out) {
-  __shared__ int32_t red[256];
-  int32_t t = 0;
-  for (int i = threadIdx.x; i < nb; i += 256) t += block_cnt[i];
+// One block: the counters' and the selection's start, and the sums of
+// k_init_nodes.
+__global__ void __launch_bounds__(256) k_init_counts(const uint32_t* __restrict__ block_cnt, int nb,
+                                                     int32_t* __restrict__ cnt, SelectState* __restrict__ st) {
+  __shared__ uint32_t red[256];
+  __shared__ uint32_t bad[256];
+  uint32_t t = 0, b = 0;
+  for (int i = threadIdx.x; i < nb; i += 256) {
+    t += block_cnt[i] & 0x7FFFFFFFu;
+    b |= block_cnt[i] >> 31;
+  }
   red[threadIdx.x] = t;
+  bad[threadIdx.x] = b;
+  for (int i = threadIdx.x; i < kSelBins; i += 256) st->hist[i] = 0;
   __syncthreads();
   for (int o = 128; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+    if ((int)threadIdx.x < o) {
+      red[threadIdx.x] += red[threadIdx.x + o];
+      bad[threadIdx.x] |= bad[threadIdx.x + o];
+    }
     __syncthreads();
   }
-  if (threadIdx.x == 0) out[0] = red[0];
+  if (threadIdx.x < C_COUNT)
+    cnt[threadIdx.x] = threadIdx.x == C_BASE ? (int32_t)red[0] : (threadIdx.x == C_ERR && bad[0] ? 2 : 0);
+  if (threadIdx.x == 0) {
+    st->hlo = 0;
+    st->hhi = ~0ull;
+    st->klo = 0;
+    st->khi = ~0u;
+    st->k_rem = 0;
+    st->mode = S_SEARCH;
+    st->level = 0;
+    st->done = 0;
+    st->n_small = 0;
+  }
 }
 
 // Membership of the subgraph's node set: base nodes and selected overlap nodes.
@@ -349,13 +424,6 @@ __global__ void __launch_bounds__(kAggBT) k_all_outdeg(const int32_t* __restrict
   deg.flush(outdeg);
 }
 
-__global__ void k_check_ntype(const uint8_t* __restrict__ ntype, int64_t n, int32_t n_ntype,
-                              int32_t* __restrict__ cnt) {
-  GRID_STRIDE(v, n) {
-    if (ntype[v] >= n_ntype) atomicOr(&cnt[C_ERR], 2);
-  }
-}
-
 // h-index histogram sizes: D+1 bins for every candidate of out-degree D.
 __global__ void k_hindex_sizes(const int32_t* __restrict__ outdeg, const int32_t* __restrict__ first,
                                int64_t n, int32_t n_edges, int32_t* __restrict__ sz) {
@@ -365,7 +433,9 @@ __global__ void k_hindex_sizes(const int32_t* __restrict__ outdeg, const int32_t
 __global__ void __launch_bounds__(kAggBT) k_hindex_hist(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
                                                     int64_t n_edges, const int32_t* __restrict__ outdeg,
                                                     const int32_t* __restrict__ first,
-                                                    const int32_t* __restrict__ hoff, int32_t* __restrict__ hist) {
+                                                    const int32_t* __restrict__ hoff, int32_t* __restrict__ hist,
+                                                    const int32_t* __restrict__ cnt) {
+  if (cnt[C_ERR]) return;  // an endpoint out of range
   __shared__ uint32_t lk[kAggSlots];
   __shared__ int32_t lv[kAggSlots];
   LdsAgg<false> agg{lk, lv};
@@ -405,126 +475,224 @@ __global__ void k_hindex_final(const int32_t* __restrict__ outdeg, const int32_t
   }
 }
 
-__global__ void k_copy_key(const int32_t* __restrict__ outdeg, int64_t n, int32_t* __restrict__ key) {
-  GRID_STRIDE(v, n) { key[v] = outdeg[v]; }
+// ---- TopM ---------------------------------------------------------------------
+// One launch per digit: each block adds its candidates' digits into an LDS
+// histogram and that into the state's; the block that finishes last picks the
+// digit holding the k_rem-th smallest and narrows the range.  The first launch
+// also finds the candidates (their list is in no order: the search needs only
+// the set).  With keys below 2047 two hash digits leave about a candidate in
+// four million, so kSelSteps launches and the ranking of a small range end
+// every search of real sizes; k_select_finish goes on by itself if they don't.
+// 8 launches of about 4 us where 16 digits of 8 bits took 33.
+constexpr int kSelSteps = 5;
+constexpr int kSelBT = 256;
+constexpr int kSelItems = 8;
+
+__device__ __forceinline__ uint32_t load_agent(const uint32_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__global__ void k_filter_flags(const int32_t* __restrict__ first, const int32_t* __restrict__ key,
-                               int64_t n, int32_t n_edges, int32_t theta, int32_t* __restrict__ flag) {
-  GRID_STRIDE(v, n) { flag[v] = (first[v] < n_edges && key[v] <= theta) ? 1 : 0; }
-}
-
-__global__ void k_compact_nodes(const int32_t* __restrict__ first, const int32_t* __restrict__ key,
-                                const int32_t* __restrict__ pos, int64_t n, int32_t n_edges,
-                                int32_t theta, int32_t* __restrict__ list) {
-  GRID_STRIDE(v, n) {
-    if (first[v] < n_edges && key[v] <= theta) list[pos[v]] = (int32_t)v;
-  }
-}
-
-__global__ void k_select_init(SelectState* st, const int32_t* __restrict__ cprime, int64_t budget) {
-  const int t = threadIdx.x;
-  st->hist[t] = 0;
-  if (t == 0) {
-    const int64_t c = *cprime;
-    const int64_t take = budget < c ? budget : c;
-    st->k_rem = (uint32_t)take;
-    st->npass = 0;
-    st->mode = (take == 0) ? 2u : ((take == c) ? 1u : 0u);
-  }
-  if (t < 16) st->digits[t] = 0;
-}
-
-__device__ __forceinline__ bool prefix_match(const SelectState* st, uint32_t key, uint64_t h,
-                                             uint32_t gid, int npass) {
-  for (int p = 0; p < npass; ++p)
-    if (composite_digit(key, h, gid, p) != st->digits[p]) return false;
-  return true;
-}
-
-__global__ void k_select_hist(SelectState* st, const int32_t* __restrict__ list,
-                              const int32_t* __restrict__ cprime, const int32_t* __restrict__ key,
-                              uint64_t seed) {
-  __shared__ int lh[256];
-  if (st->mode != 0) return;
-  lh[threadIdx.x] = 0;
+// Adds a block's histogram into the state's and tells, to all threads,
+// whether the block is the launch's last one.
+__device__ __forceinline__ bool select_add(SelectState* st, const int32_t* lh, int* flag) {
   __syncthreads();
-  const int npass = (int)st->npass;
-  const int64_t c = *cprime;
-  GRID_STRIDE(i, c) {
-    const uint32_t gid = (uint32_t)list[i];
-    const uint32_t kv = (uint32_t)key[gid];
-    const uint64_t h = splitmix64_first(seed ^ (uint64_t)gid);
-    if (prefix_match(st, kv, h, gid, npass)) atomicAdd(&lh[composite_digit(kv, h, gid, npass)], 1);
-  }
+  for (int b = threadIdx.x; b < kSelBins; b += kSelBT)
+    if (lh[b]) atomicAdd(&st->hist[b], lh[b]);
+  __threadfence();
   __syncthreads();
-  if (lh[threadIdx.x]) atomicAdd(&st->hist[threadIdx.x], lh[threadIdx.x]);
+  if (threadIdx.x == 0) *flag = atomicAdd(&st->done, 1u) == gridDim.x - 1;
+  __syncthreads();
+  __threadfence();
+  return *flag != 0;
 }
 
-// One block of 256 threads: pick the bucket holding the k_rem-th smallest.
-__global__ void k_select_pick(SelectState* st) {
-  __shared__ int cnt[256];
-  __shared__ int pre[256];
-  if (st->mode != 0) return;
-  const int t = threadIdx.x;
-  cnt[t] = st->hist[t];
+// The last block: the digit with the k-th smallest of the range.
+__device__ __forceinline__ void select_pick(SelectState* st, uint32_t k, int32_t* lh) {
+  constexpr int kPer = kSelBins / kSelBT;
+  const uint32_t level = st->level;
+  uint32_t c[kPer], sum = 0;
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    uint32_t* h = reinterpret_cast<uint32_t*>(&st->hist[threadIdx.x * kPer + i]);
+    c[i] = load_agent(h);
+    *h = 0;
+    sum += c[i];
+  }
+  uint32_t* acc = reinterpret_cast<uint32_t*>(lh);
+  acc[threadIdx.x] = sum;
   __syncthreads();
-  if (t == 0) {
-    int run = 0;
-    for (int b = 0; b < 256; ++b) {
-      pre[b] = run;
-      run += cnt[b];
+  for (int o = 1; o < kSelBT; o <<= 1) {  // inclusive sums
+    const uint32_t u = (int)threadIdx.x >= o ? acc[threadIdx.x - o] : 0u;
+    __syncthreads();
+    acc[threadIdx.x] += u;
+    __syncthreads();
+  }
+  uint32_t lo = acc[threadIdx.x] - sum;
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    if (c[i] > 0 && lo < k && k <= lo + c[i]) {  // one thread
+      select_narrow(st, level, (uint32_t)(threadIdx.x * kPer + i));
+      st->k_rem = k - lo;
+      st->mode = k - lo == c[i] ? S_DONE : (c[i] <= (uint32_t)kSelSmall ? S_COLLECT : S_SEARCH);
     }
+    lo += c[i];
   }
-  __syncthreads();
-  const uint32_t k = st->k_rem;
-  const uint32_t lo = (uint32_t)pre[t], c = (uint32_t)cnt[t];
-  __syncthreads();
-  if (c > 0 && lo < k && k <= lo + c) {
-    const uint32_t p = st->npass;
-    st->digits[p] = (uint32_t)t;
-    st->npass = p + 1;
-    st->k_rem = k - lo;
-    if (k - lo == c) st->mode = 1;
-  }
-  st->hist[t] = 0;
+  if (threadIdx.x == 0) st->done = 0;
 }
 
-__global__ void k_select_mark(const SelectState* st, const int32_t* __restrict__ list,
-                              const int32_t* __restrict__ cprime, const int32_t* __restrict__ key,
-                              uint64_t seed, uint8_t* __restrict__ sel) {
-  const uint32_t mode = st->mode;
-  if (mode == 2) return;
-  const int npass = (int)st->npass;
-  const int64_t c = *cprime;
-  GRID_STRIDE(i, c) {
-    const uint32_t gid = (uint32_t)list[i];
-    const uint32_t kv = (uint32_t)key[gid];
-    const uint64_t h = splitmix64_first(seed ^ (uint64_t)gid);
-    bool le = true;
-    for (int p = 0; p < npass; ++p) {
-      const uint32_t dg = composite_digit(kv, h, gid, p);
-      if (dg != st->digits[p]) {
-        le = dg < st->digits[p];
-        break;
+// Candidates with key <= theta: their list, their count and the histogram of
+// the first digit.
+__global__ void __launch_bounds__(kSelBT) k_candidates(const int32_t* __restrict__ first,
+                                                       const int32_t* __restrict__ key, int64_t n, int32_t n_edges,
+                                                       int32_t theta, int64_t budget, int32_t* __restrict__ list,
+                                                       int32_t* __restrict__ cnt, SelectState* __restrict__ st) {
+  __shared__ int32_t lh[kSelBins];
+  __shared__ int32_t wsum[kSelBT / 64];
+  __shared__ int32_t base_s;
+  __shared__ int flag;
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  const uint64_t lt = (l == 0) ? 0ull : (~0ull >> (64 - l));
+  for (int b = threadIdx.x; b < kSelBins; b += kSelBT) lh[b] = 0;
+  __syncthreads();
+  for (int64_t v0 = (int64_t)blockIdx.x * (kSelBT * kSelItems); v0 < n;
+       v0 += (int64_t)gridDim.x * (kSelBT * kSelItems)) {
+    bool in[kSelItems];
+    int32_t rank[kSelItems];
+    int32_t c = 0;
+#pragma unroll
+    for (int j = 0; j < kSelItems; ++j) {
+      const int64_t v = v0 + j * kSelBT + threadIdx.x;
+      in[j] = false;
+      if (v < n && first[v] < n_edges) {
+        const int32_t kv = key[v];
+        in[j] = kv <= theta;
+        if (in[j]) atomicAdd(&lh[select_digit(0, (uint32_t)kv, 0)], 1);
       }
+      const uint64_t m = __ballot(in[j]);
+      rank[j] = c + (int32_t)__popcll(m & lt);
+      c += (int32_t)__popcll(m);
     }
-    if (le) sel[gid] = 1;
+    if (l == 0) wsum[w] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      int32_t t = 0;
+#pragma unroll
+      for (int q = 0; q < kSelBT / 64; ++q) {
+        const int32_t x = wsum[q];
+        wsum[q] = t;
+        t += x;
+      }
+      base_s = t > 0 ? atomicAdd(&cnt[C_CPRIME], t) : 0;
+    }
+    __syncthreads();
+    const int32_t base = base_s + wsum[w];
+#pragma unroll
+    for (int j = 0; j < kSelItems; ++j)
+      if (in[j]) list[base + rank[j]] = (int32_t)(v0 + j * kSelBT + threadIdx.x);
+    __syncthreads();
+  }
+  if (!select_add(st, lh, &flag)) return;
+  const int64_t c = (int64_t)load_agent(reinterpret_cast<const uint32_t*>(&cnt[C_CPRIME]));
+  const int64_t take = budget < c ? budget : c;
+  if (take == 0 || take == c) {  // nothing, or every candidate (the range is all composites)
+    for (int b = threadIdx.x; b < kSelBins; b += kSelBT) st->hist[b] = 0;
+    if (threadIdx.x == 0) st->mode = take == 0 ? S_NONE : S_DONE;
+  } else {
+    select_pick(st, (uint32_t)take, lh);
   }
 }
 
-// Node-set digits for the relabel; in a sparse build the selected nodes'
-// first[] goes back to n_edges for the base-edge minimum of the induced-edge
-// pass.
-__global__ void k_member_digit(const int32_t* __restrict__ part, int32_t k,
-                               const uint8_t* __restrict__ sel, const uint8_t* __restrict__ ntype,
-                               int64_t n, int64_t n_edges, int64_t budget, const int32_t* __restrict__ cnt,
-                               uint8_t* __restrict__ digit, int32_t* __restrict__ iota, int32_t* __restrict__ first) {
-  const bool exact = dense_build(cnt[C_BASE], budget, n);
+// One round of the search by the launch's blocks.
+__device__ __forceinline__ void select_round(SelectState* st, const int32_t* __restrict__ list, int64_t c,
+                                             const int32_t* __restrict__ key, uint64_t seed, int32_t* lh, int* flag) {
+  const uint32_t mode = load_agent(&st->mode);
+  const uint32_t level = st->level;
+  for (int b = threadIdx.x; b < kSelBins; b += kSelBT) lh[b] = 0;
+  __syncthreads();
+  GRID_STRIDE(i, c) {
+    const uint32_t gid = (uint32_t)list[i];
+    const uint32_t kv = (uint32_t)key[gid];
+    if (kv < st->klo || kv > st->khi) continue;
+    const uint64_t h = splitmix64_first(seed ^ (uint64_t)gid);
+    if (!select_in_range(st, kv, h)) continue;
+    if (mode == S_COLLECT) {
+      const uint32_t at = atomicAdd(&st->n_small, 1u);
+      st->small[at][0] = kv;
+      st->small[at][1] = h;
+    } else {
+      atomicAdd(&lh[select_digit(level, kv, h)], 1);
+    }
+  }
+  if (!select_add(st, lh, flag)) return;
+  if (mode == S_COLLECT) {
+    if (threadIdx.x == 0) {
+      st->mode = S_RANK;
+      st->done = 0;
+    }
+  } else {
+    select_pick(st, st->k_rem, lh);
+  }
+}
+
+__global__ void __launch_bounds__(kSelBT) k_select_step(SelectState* __restrict__ st, const int32_t* __restrict__ list,
+                                                        const int32_t* __restrict__ cnt,
+                                                        const int32_t* __restrict__ key, uint64_t seed) {
+  __shared__ int32_t lh[kSelBins];
+  __shared__ int flag;
+  if (st->mode != S_SEARCH && st->mode != S_COLLECT) return;
+  select_round(st, list, cnt[C_CPRIME], key, seed, lh, &flag);
+}
+
+// One block: what is left of the search (each round narrows the range by a
+// digit, and there are ten), then the k_rem-th smallest of a small range.
+__global__ void __launch_bounds__(kSelBT) k_select_finish(SelectState* st, const int32_t* __restrict__ list,
+                                                          const int32_t* __restrict__ cnt,
+                                                          const int32_t* __restrict__ key, uint64_t seed) {
+  __shared__ int32_t lh[kSelBins];
+  __shared__ uint64_t comp[kSelSmall][2];
+  __shared__ int flag;
+  for (int round = 0; round < 12; ++round) {
+    const uint32_t mode = load_agent(&st->mode);
+    if (mode != S_SEARCH && mode != S_COLLECT) break;
+    select_round(st, list, cnt[C_CPRIME], key, seed, lh, &flag);
+    __threadfence();
+    __syncthreads();
+  }
+  if (load_agent(&st->mode) != S_RANK) return;
+  const int n = (int)st->n_small, k = (int)st->k_rem;
+  for (int i = threadIdx.x; i < n; i += kSelBT) {
+    comp[i][0] = st->small[i][0];
+    comp[i][1] = st->small[i][1];
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < n; i += kSelBT) {
+    const uint64_t a = comp[i][0], b = comp[i][1];
+    int less = 0;
+    for (int q = 0; q < n; ++q) less += comp[q][0] < a || (comp[q][0] == a && comp[q][1] < b);
+    if (less == k - 1) {  // composites are unique: one thread
+      st->khi = (uint32_t)a;
+      st->hhi = b;
+      st->mode = S_DONE;
+    }
+  }
+}
+
+// Whether a node outside V_k is selected.
+__device__ __forceinline__ bool selected(const SelectState* __restrict__ st, uint64_t seed, int32_t first, int32_t key,
+                                         int64_t v, int32_t n_edges, int32_t theta) {
+  if (first >= n_edges || key > theta || st->mode != S_DONE) return false;
+  const uint32_t kv = (uint32_t)key;
+  if (kv != st->khi) return kv < st->khi;
+  return st->hhi == ~0ull || splitmix64_first(seed ^ (uint64_t)v) <= st->hhi;
+}
+
+// Node-set digits for the relabel (more than two node types).
+__global__ void k_member_digit(const int32_t* __restrict__ part, int32_t k, const uint8_t* __restrict__ sel,
+                               const uint8_t* __restrict__ ntype, int64_t n, uint8_t* __restrict__ digit,
+                               int32_t* __restrict__ iota) {
   GRID_STRIDE(v, n) {
     digit[v] = (part[v] == k || sel[v]) ? ntype[v] : (uint8_t)255;
     iota[v] = (int32_t)v;
-    if (!exact && sel[v]) first[v] = (int32_t)n_edges;
   }
 }
 
@@ -543,19 +711,26 @@ __global__ void k_overlap_flags(const int32_t* __restrict__ l2g, const uint8_t* 
 
 __global__ void k_overlap_fill(const int32_t* __restrict__ l2g, const int32_t* __restrict__ flag,
                                const int32_t* __restrict__ pos, const int32_t* __restrict__ cnt,
-                               const int32_t* __restrict__ part, const int32_t* __restrict__ first,
-                               const uint8_t* __restrict__ rel, int32_t* __restrict__ overlap,
-                               int32_t* __restrict__ home, uint8_t* __restrict__ orel) {
+                               const int32_t* __restrict__ part, int32_t* __restrict__ overlap,
+                               int32_t* __restrict__ home) {
   const int64_t ns = cnt[C_NSUB];
   GRID_STRIDE(i, ns) {
     if (flag[i]) {
       const int32_t p = pos[i];
-      const int32_t g = l2g[i];
       overlap[p] = (int32_t)i;
-      home[p] = part[g];
-      orel[p] = rel[first[g]];
+      home[p] = part[l2g[i]];
     }
   }
+}
+
+// The relation of every overlap node's base edge (after the induced edges,
+// which find it in a sparse build).
+__global__ void k_overlap_rel(const int32_t* __restrict__ l2g, const int32_t* __restrict__ overlap,
+                              const int32_t* __restrict__ cnt, const int32_t* __restrict__ first,
+                              const uint8_t* __restrict__ rel, uint8_t* __restrict__ orel) {
+  if (cnt[C_ERR]) return;
+  const int64_t m = cnt[C_MSEL];
+  GRID_STRIDE(p, m) orel[p] = rel[first[l2g[overlap[p]]]];
 }
 
 // ---- induced edges from a rank table (node types 0 and 1) ------------------
@@ -571,32 +746,135 @@ struct __align__(16) RankEnt {
 };
 constexpr int kRankGroup = 32;
 
-// Masks and member counts of every 32-node group (one wave per two groups).
-__global__ void __launch_bounds__(kBT) k_rank_bits(const int32_t* __restrict__ part, int32_t k,
-                                                   const uint8_t* __restrict__ sel, const uint8_t* __restrict__ ntype,
-                                                   int64_t n, RankEnt* __restrict__ rt, int32_t* __restrict__ c0,
-                                                   int32_t* __restrict__ c1) {
-  GRID_STRIDE(v, cdiv_dev(n, 64) * 64) {
-    const bool in = v < n && (part[v] == k || sel[v]);
-    const bool t1 = in && ntype[v] == 1;
-    const uint64_t m = __ballot(in), m1 = __ballot(t1), m0 = m & ~m1;
-    const int l = threadIdx.x & 63;
-    if (l < 2) {  // lane h writes group 2 (v / 64) + h, the half h of the wave's 64 nodes
+// Tiles of kNTile nodes, kNTile / 4 consecutive ones per wave.  k_nodes_count
+// finds the selected nodes (and gives first[] of them back to n_edges in a
+// sparse build, for the base-edge minimum of the induced-edge pass), writes the
+// rank table's masks and the selected nodes' bits, and the tile's counts of
+// type-0 and type-1 members and of type-0 and type-1 selected nodes as four
+// streams of one count per tile; a scan of the four later, k_nodes_assign
+// writes local ids both ways, the overlap with its home blocks, the rank
+// table's counts and the type ranges.  Two passes over the nodes (25 bytes
+// each); a partition by type, a fill, flags and three scans over all nodes took
+// 0.25 ms more at 10M nodes, and 20 launches more at any size.
+constexpr int kNRounds = 8;
+constexpr int kNTile = kBT * kNRounds;
+
+__global__ void __launch_bounds__(kBT) k_nodes_count(const uint32_t* __restrict__ base_bits,
+                                                     const uint8_t* __restrict__ ntype, int32_t* __restrict__ first,
+                                                     const int32_t* __restrict__ key,
+                                                     const SelectState* __restrict__ st, uint64_t seed, int64_t n,
+                                                     int32_t n_edges, int32_t theta, int64_t budget,
+                                                     const int32_t* __restrict__ cnt, RankEnt* __restrict__ rt,
+                                                     uint64_t* __restrict__ sel_bits, uint8_t* __restrict__ sel,
+                                                     int64_t tiles, int32_t* __restrict__ tcnt) {
+  __shared__ int32_t wtot[kBT / 64][4];
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  const int64_t v00 = (int64_t)blockIdx.x * kNTile + w * (64 * kNRounds);
+  const bool sparse = !dense_build(cnt[C_BASE], budget, n);
+  int32_t c[4] = {0, 0, 0, 0};
+#pragma unroll 2
+  for (int j = 0; j < kNRounds; ++j) {
+    const int64_t v = v00 + 64 * j + l;
+    const bool live = v < n;
+    const bool base = live && bit_of(base_bits, (int32_t)v);
+    const bool s = live && !base && selected(st, seed, first[v], key[v], v, n_edges, theta);
+    const uint64_t m = __ballot(base || s), ms = __ballot(s);
+    const uint64_t m1 = __ballot(live && ntype[v] == 1) & m, m0 = m & ~m1;
+    if (sparse && s) first[v] = n_edges;
+    if (sel && live) sel[v] = s ? 1 : 0;
+    if (l < 2 && 64 * j + v00 < n) {  // lane h writes group 2 (v / 64) + h, the half h of the wave's 64 nodes
       const int64_t b = (v >> 6) * 2 + l;
-      const uint32_t g0 = (uint32_t)(m0 >> (32 * l)), g1 = (uint32_t)(m1 >> (32 * l));
-      rt[b].mem0 = g0;
-      rt[b].mem1 = g1;
-      c0[b] = __popc(g0);
-      c1[b] = __popc(g1);
+      rt[b].mem0 = (uint32_t)(m0 >> (32 * l));
+      rt[b].mem1 = (uint32_t)(m1 >> (32 * l));
+      if (l == 0) sel_bits[v >> 6] = ms;
     }
+    c[0] += (int32_t)__popcll(m0);
+    c[1] += (int32_t)__popcll(m1);
+    c[2] += (int32_t)__popcll(m0 & ms);
+    c[3] += (int32_t)__popcll(m1 & ms);
   }
+  if (l < 4) wtot[w][l] = l == 0 ? c[0] : (l == 1 ? c[1] : (l == 2 ? c[2] : c[3]));
+  __syncthreads();
+  if (threadIdx.x < 4) {
+    int32_t t = 0;
+#pragma unroll
+    for (int q = 0; q < kBT / 64; ++q) t += wtot[q][threadIdx.x];
+    tcnt[threadIdx.x * tiles + blockIdx.x] = t;
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) tcnt[4 * tiles] = 0;  // the scan's end
 }
 
-__global__ void k_rank_pack(const int32_t* __restrict__ pre0, const int32_t* __restrict__ pre1, int64_t nb,
-                            RankEnt* __restrict__ rt) {
-  GRID_STRIDE(b, nb) {
-    rt[b].pre0 = (uint32_t)pre0[b];
-    rt[b].pre1 = (uint32_t)pre1[b];
+__global__ void __launch_bounds__(kBT) k_nodes_assign(RankEnt* __restrict__ rt, const uint64_t* __restrict__ sel_bits,
+                                                      const int32_t* __restrict__ part, int64_t n, int32_t n_ntype,
+                                                      int64_t tiles, const int32_t* __restrict__ S,
+                                                      int32_t* __restrict__ l2g, int32_t* __restrict__ g2l,
+                                                      int32_t* __restrict__ type_off, int32_t* __restrict__ type_copy,
+                                                      int32_t* __restrict__ overlap, int32_t* __restrict__ home,
+                                                      int32_t* __restrict__ cnt) {
+  __shared__ int32_t wtot[kBT / 64][4];
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  const uint64_t lt = (l == 0) ? 0ull : (~0ull >> (64 - l));
+  const int64_t tile = blockIdx.x, v00 = tile * kNTile + w * (64 * kNRounds);
+  const int32_t n0 = S[tiles] - S[0], o0 = S[3 * tiles] - S[2 * tiles];
+  const int32_t ns = S[2 * tiles] - S[0], ms_all = S[4 * tiles] - S[2 * tiles];
+  // the wave's groups: lane j < kNRounds holds the masks of its nodes 64 j .. 64 j + 63
+  uint64_t g0 = 0, g1 = 0, gs = 0;
+  if (l < kNRounds && v00 + 64 * l < n) {
+    const uint4 a = reinterpret_cast<const uint4*>(rt)[((v00 >> 6) + l) * 2];
+    const uint4 b = reinterpret_cast<const uint4*>(rt)[((v00 >> 6) + l) * 2 + 1];
+    g0 = ((uint64_t)b.x << 32) | a.x;
+    g1 = ((uint64_t)b.y << 32) | a.y;
+    gs = sel_bits[(v00 >> 6) + l];
+  }
+  const int32_t pc[4] = {(int32_t)__popcll(g0), (int32_t)__popcll(g1), (int32_t)__popcll(g0 & gs),
+                         (int32_t)__popcll(g1 & gs)};
+  int32_t pre[4];  // in lane j: before group j, inside the wave
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    int32_t inc = pc[i];
+#pragma unroll
+    for (int o = 1; o < kNRounds; o <<= 1) {
+      const int32_t u = __shfl_up(inc, o, 64);
+      if (l >= o) inc += u;
+    }
+    pre[i] = inc - pc[i];
+    if (l == kNRounds - 1) wtot[w][i] = inc;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    pre[i] += S[i * tiles + tile] - S[i * tiles];
+    for (int q = 0; q < w; ++q) pre[i] += wtot[q][i];
+  }
+  if (l < kNRounds && v00 + 64 * l < n) {
+    RankEnt* e = rt + ((v00 >> 6) + l) * 2;
+    e[0].pre0 = (uint32_t)pre[0];
+    e[0].pre1 = (uint32_t)pre[1];
+    e[1].pre0 = (uint32_t)(pre[0] + __popc((uint32_t)g0));
+    e[1].pre1 = (uint32_t)(pre[1] + __popc((uint32_t)g1));
+  }
+#pragma unroll
+  for (int j = 0; j < kNRounds; ++j) {
+    const int64_t v = v00 + 64 * j + l;
+    const uint64_t m0 = __shfl(g0, j, 64), m1 = __shfl(g1, j, 64), ms = __shfl(gs, j, 64);
+    const int32_t p0 = __shfl(pre[0], j, 64), p1 = __shfl(pre[1], j, 64);
+    const int32_t q0 = __shfl(pre[2], j, 64), q1 = __shfl(pre[3], j, 64);
+    const bool t0 = (m0 >> l) & 1ull, t1 = (m1 >> l) & 1ull;
+    if (v < n) {
+      const int32_t id = t0 ? p0 + (int32_t)__popcll(m0 & lt) : (t1 ? n0 + p1 + (int32_t)__popcll(m1 & lt) : -1);
+      g2l[v] = id;
+      if (id >= 0) l2g[id] = (int32_t)v;
+      if ((ms >> l) & 1ull) {
+        const int32_t at = t0 ? q0 + (int32_t)__popcll(m0 & ms & lt) : o0 + q1 + (int32_t)__popcll(m1 & ms & lt);
+        overlap[at] = id;
+        home[at] = part[v];
+      }
+    }
+  }
+  if (tile == 0 && threadIdx.x == 0) {
+    cnt[C_NSUB] = ns;
+    cnt[C_MSEL] = ms_all;
+    for (int t = 0; t <= n_ntype; ++t) type_off[t] = type_copy[t] = t == 0 ? 0 : (t < n_ntype ? n0 : ns);
   }
 }
 
@@ -628,14 +906,17 @@ __global__ void __launch_bounds__(kBT) k_edge_ids(const int32_t* __restrict__ sr
                                                   const uint8_t* __restrict__ rel, int32_t n_rel,
                                                   const RankEnt* __restrict__ rt, const int32_t* __restrict__ type_off,
                                                   const uint32_t* __restrict__ base_bits, const int32_t* __restrict__ ts,
-                                                  int32_t t_cut, int64_t n_edges, int sparse,
+                                                  int32_t t_cut, int64_t n_edges, int64_t n_nodes, int64_t budget,
+                                                  const int32_t* __restrict__ cnt,
                                                   uint32_t* __restrict__ kcsr, int32_t* __restrict__ vsrc,
                                                   int32_t* __restrict__ veid, const float* __restrict__ edge_w,
                                                   int32_t* __restrict__ vw, uint64_t* __restrict__ keep_bits,
                                                   int32_t* __restrict__ tile_cnt, int32_t* __restrict__ first) {
   __shared__ int32_t wsum[kBT / 64];
+  if (cnt[C_ERR]) return;  // an endpoint out of range: no lookups
   const int64_t base = (int64_t)blockIdx.x * kETile;
   const int32_t off1 = type_off[1];
+  const bool sparse = !dense_build(cnt[C_BASE], budget, n_nodes);
   int32_t c = 0;
   // kEiItems rounds at a time, each phase's loads issued for all of them
   // before any is used: the endpoints (with relation, weight and timestamp),
@@ -762,7 +1043,9 @@ __global__ void __launch_bounds__(kBT) k_edge_emit(const uint32_t* __restrict__ 
 __global__ void k_edge_keep(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
                             const uint32_t* __restrict__ member, const uint32_t* __restrict__ base_bits,
                             const int32_t* __restrict__ ts, int32_t t_cut, int64_t n_edges,
-                            int32_t* __restrict__ keep, int32_t* __restrict__ first) {
+                            int32_t* __restrict__ keep, int32_t* __restrict__ first,
+                            const int32_t* __restrict__ cnt) {
+  if (cnt[C_ERR]) return;
   GRID_STRIDE(e, n_edges) {
     const int32_t s = src[e], d = dst[e];
     const bool in = bit_of(member, s) && bit_of(member, d);
@@ -782,7 +1065,9 @@ __global__ void k_edge_compact(const int32_t* __restrict__ src, const int32_t* _
                                const int32_t* __restrict__ g2l, const uint8_t* __restrict__ rel,
                                const int32_t* __restrict__ pos, int64_t n_edges, int32_t n_rel,
                                uint32_t* __restrict__ kcsr, int32_t* __restrict__ vsrc, int32_t* __restrict__ veid,
-                               const float* __restrict__ edge_w, int32_t* __restrict__ vw) {
+                               const float* __restrict__ edge_w, int32_t* __restrict__ vw,
+                               const int32_t* __restrict__ cnt) {
+  if (cnt[C_ERR]) return;
   GRID_STRIDE(e, n_edges) {
     const int32_t p = pos[e];
     if (pos[e + 1] != p) {
@@ -1001,7 +1286,7 @@ __global__ void __launch_bounds__(kBT) k_plan_count(const int32_t* __restrict__ 
 
 struct PlanOut {
   int4 *items, *heavy, *fitems, *fheavy;
-  int32_t *act, *act_off, *act_slot, *slot_q;
+  int32_t *act, *act_off, *act_off_copy, *act_slot, *slot_q;
   SlotEnt* tab;
 };
 
@@ -1117,7 +1402,8 @@ __global__ void __launch_bounds__(kBT) k_plan_fill(const int32_t* __restrict__ c
     }
   }
   if (tile == 0) {
-    for (int r = threadIdx.x; r <= R; r += kBT) o.act_off[r] = S[(int64_t)(P_REL + r) * tiles] - S[(int64_t)P_REL * tiles];
+    for (int r = threadIdx.x; r <= R; r += kBT)
+      o.act_off[r] = o.act_off_copy[r] = S[(int64_t)(P_REL + r) * tiles] - S[(int64_t)P_REL * tiles];
     if (threadIdx.x == 0) {
       cnt[C_ASLOTS] = S[tiles] - S[0];
       cnt[C_ITEMS] = S[2 * tiles] - S[tiles];
@@ -1160,17 +1446,19 @@ struct BuildWs {
   int32_t *cnt, *outdeg, *first, *key, *flag, *pos, *list, *iota, *hoff, *hist;
   uint8_t *sel, *digit;
   SelectState* st;
-  int32_t *keep, *vsrc, *vdst, *veid, *alt1, *alt2, *alt3, *pcnt, *scratch, *bcnt;
+  int32_t *keep, *vsrc, *vdst, *veid, *alt1, *alt2, *alt3, *pcnt, *tcnt, *scratch;
+  uint32_t* bcnt;
+  uint64_t* sel_bits;
   int4* gaps;
   int32_t* vw;                // weighted graphs: edge weights (float bits) of the kept edges in edge order
   int32_t *vsc, *vsc_alt;     // unpacked CSC sort: the scales (float bits) and their ping-pong buffer
   uint32_t *kcsr, *kcsc, *kalt, *bbits, *mbits;
   RankEnt* rt;
-  int32_t *rc0, *rc1, *tile_cnt;
+  int32_t* tile_cnt;
   void layout(A& a, int64_t N, int64_t E, int64_t R, bool hindex, bool weighted) {
     const int64_t NQ = N * R + 1;
-    cnt = a.template take<int32_t>(C_COUNT + 8);
-    bcnt = a.template take<int32_t>(16384);  // block counts of k_base_bits (grid_for caps it there)
+    cnt = a.template take<int32_t>(C_COUNT + HG_MAX_NTYPE + 1 + HG_MAX_REL + 1);
+    bcnt = a.template take<uint32_t>(16384);  // block counts of k_init_nodes (grid_for caps it there)
     outdeg = a.template take<int32_t>(N);
     first = a.template take<int32_t>(N);
     key = a.template take<int32_t>(N);
@@ -1185,8 +1473,8 @@ struct BuildWs {
     mbits = a.template take<uint32_t>(2 * (N / 64 + 1));
     // rank groups: cdiv(N, 64) * 2 <= N / 32 + 2
     rt = a.template take<RankEnt>(N / kRankGroup + 2);
-    rc0 = a.template take<int32_t>(N / kRankGroup + 2);
-    rc1 = a.template take<int32_t>(N / kRankGroup + 2);
+    sel_bits = a.template take<uint64_t>(N / 64 + 1);
+    tcnt = a.template take<int32_t>(4 * cdiv(N, kNTile) + 1);
     tile_cnt = a.template take<int32_t>(E / kETile + 2);
     digit = a.template take<uint8_t>(N);
     st = a.template take<SelectState>(1);
@@ -1378,7 +1666,7 @@ extern "C" int hg_node_keys(const hg_graph_desc* g, int32_t key, int32_t* keys, 
     HG_TRY(scan_exclusive_i32(w.flag, w.hoff, N + 1, nullptr, w.scratch, s));
     HG_TRY(fill_i32(w.hist, 0, E + N, s));
     HG_LAUNCH("keys_hindex_hist", k_hindex_hist, dim3(agg_grid(E)), dim3(kAggBT), 0, s, g->src, g->dst, E,
-              (const int32_t*)deg, (const int32_t*)w.first, (const int32_t*)w.hoff, w.hist);
+              (const int32_t*)deg, (const int32_t*)w.first, (const int32_t*)w.hoff, w.hist, (const int32_t*)w.cnt);
     HG_LAUNCH("keys_hindex_final", k_hindex_final, dim3(gN), dim3(kBT), 0, s, (const int32_t*)deg,
               (const int32_t*)w.first, (const int32_t*)w.hoff, (const int32_t*)w.hist, N, (int32_t)E, keys);
   }
@@ -1420,28 +1708,24 @@ extern "C" int hg_build_csr(const hg_graph_desc* g, const hg_overlap_desc* o, hg
   if (!arena.ok()) return fail(HG_ERR_CAPACITY, "workspace layout overflow");
 
   const unsigned gN = grid_for(N), gE = grid_for(E);
-  // 1. degrees, base-edge index, range checks
-  HG_TRY(fill_i32(w.cnt, 0, C_COUNT + 8, s));
-  HG_TRY(fill_i32(w.outdeg, 0, N, s));
-  HG_TRY(fill_i32(w.first, (int32_t)E, N, s));
-  HG_TRY(fill_u8(w.sel, 0, N, s));
+  // the type ranges and the offsets of the active lists beside the counters, for one copy to the host
+  int32_t* type_copy = w.cnt + C_COUNT;
+  int32_t* act_copy = type_copy + T + 1;
+  const int n_head = C_COUNT + (int)(T + 1 + R + 1);
+  // 1. degrees, base-edge index, range checks (kernels that index by an edge's
+  // ids end at once when one is out of range; the counts' copy below reports it)
   const unsigned gB = grid_for(cdiv(N, 64) * 64);
-  HG_LAUNCH("build_base_bits", k_base_bits, dim3(gB), dim3(kBT), 0, s, g->part, g->k, N, w.bbits, w.bcnt);
-  HG_LAUNCH("build_base_count", k_sum_counts, dim3(1), dim3(256), 0, s, (const int32_t*)w.bcnt, (int)gB,
-            w.cnt + C_BASE);
+  HG_LAUNCH("build_init_nodes", k_init_nodes, dim3(gB), dim3(kBT), 0, s, g->part, g->k, g->ntype, (int32_t)T, N,
+            (int32_t)E, w.bbits, w.first, w.outdeg, w.bcnt);
+  HG_LAUNCH("build_init_counts", k_init_counts, dim3(1), dim3(256), 0, s, (const uint32_t*)w.bcnt, (int)gB, w.cnt,
+            w.st);
   if (E > 0)
     HG_LAUNCH("build_edges_pass", k_edges_pass, dim3(agg_grid(E, kDegPerCu)), dim3(kAggBT), 0, s, g->src, g->dst,
               g->rel, (const uint32_t*)w.bbits, N, E, (int32_t)R, (hindex && !o->node_key) ? 1 : 0,
               (!hindex && !o->node_key) ? 1 : 0, o->budget_M, w.outdeg, w.first, w.cnt);
-  HG_LAUNCH("build_check_ntype", k_check_ntype, dim3(gN), dim3(kBT), 0, s, g->ntype, N, (int32_t)T, w.cnt);
-  {
-    int32_t herr = 0;
-    HG_HIP_TRY(hipMemcpyAsync(&herr, w.cnt + C_ERR, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    HG_HIP_TRY(hipStreamSynchronize(s));
-    if (herr) return fail(HG_ERR_RANGE, "input ids out of range (flags 0x%x)", herr);
-  }
-  // 2. keys (the caller's, when given: they do not depend on k)
-  const int32_t* key = o->node_key ? o->node_key : w.key;
+  // 2. keys: the caller's, when given (they do not depend on k); the h-index;
+  // or the out-degrees of the nodes outside V_k (every candidate among them)
+  const int32_t* key = o->node_key ? o->node_key : (hindex ? w.key : w.outdeg);
   if (hindex && !o->node_key) {
     HG_LAUNCH("build_hindex_sizes", k_hindex_sizes, dim3(gN), dim3(kBT), 0, s,
               (const int32_t*)w.outdeg, (const int32_t*)w.first, N, (int32_t)E, w.flag);
@@ -1450,70 +1734,63 @@ extern "C" int hg_build_csr(const hg_graph_desc* g, const hg_overlap_desc* o, hg
     HG_TRY(fill_i32(w.hist, 0, E + N, s));
     if (E > 0)
       HG_LAUNCH("build_hindex_hist", k_hindex_hist, dim3(agg_grid(E)), dim3(kAggBT), 0, s, g->src, g->dst, E,
-                (const int32_t*)w.outdeg, (const int32_t*)w.first, (const int32_t*)w.hoff, w.hist);
+                (const int32_t*)w.outdeg, (const int32_t*)w.first, (const int32_t*)w.hoff, w.hist,
+                (const int32_t*)w.cnt);
     HG_LAUNCH("build_hindex_final", k_hindex_final, dim3(gN), dim3(kBT), 0, s,
               (const int32_t*)w.outdeg, (const int32_t*)w.first, (const int32_t*)w.hoff,
               (const int32_t*)w.hist, N, (int32_t)E, w.key);
-  } else if (!o->node_key) {
-    // the out-degrees of the nodes outside V_k (every candidate among them)
-    HG_LAUNCH("build_copy_key", k_copy_key, dim3(gN), dim3(kBT), 0, s, (const int32_t*)w.outdeg, N, w.key);
   }
-  // 3. filtered candidates, compacted in gid order
-  HG_LAUNCH("build_filter_flags", k_filter_flags, dim3(gN), dim3(kBT), 0, s, (const int32_t*)w.first,
-            key, N, (int32_t)E, o->theta, w.flag);
-  HG_TRY(scan_exclusive_i32(w.flag, w.pos, N, w.cnt + C_CPRIME, w.scratch, s));
-  HG_LAUNCH("build_compact_nodes", k_compact_nodes, dim3(gN), dim3(kBT), 0, s, (const int32_t*)w.first,
-            key, (const int32_t*)w.pos, N, (int32_t)E, o->theta, w.list);
-  // 4. TopM by exact radix select over the 128-bit composite
-  {
-    const int64_t budget = o->budget_M;
-    HG_LAUNCH("build_select_init", k_select_init, dim3(1), dim3(256), 0, s, w.st,
-              (const int32_t*)(w.cnt + C_CPRIME), budget);
-    for (int p = 0; p < 16; ++p) {
-      HG_LAUNCH("build_select_hist", k_select_hist, dim3(grid_for(N, 2048)), dim3(256), 0, s, w.st,
-                (const int32_t*)w.list, (const int32_t*)(w.cnt + C_CPRIME), key,
-                o->seed);
-      HG_LAUNCH("build_select_pick", k_select_pick, dim3(1), dim3(256), 0, s, w.st);
-    }
-    HG_LAUNCH("build_select_mark", k_select_mark, dim3(grid_for(N, 2048)), dim3(256), 0, s,
-              (const SelectState*)w.st, (const int32_t*)w.list, (const int32_t*)(w.cnt + C_CPRIME),
-              key, o->seed, w.sel);
+  // 3, 4. filtered candidates and TopM
+  const unsigned gS = (unsigned)std::min<int64_t>(cdiv(N, kSelBT * kSelItems), 2 * (int64_t)num_cus());
+  HG_LAUNCH("build_candidates", k_candidates, dim3(gS), dim3(kSelBT), 0, s, (const int32_t*)w.first, key, N,
+            (int32_t)E, o->theta, o->budget_M, w.list, w.cnt, w.st);
+  for (int p = 0; p < kSelSteps; ++p)
+    HG_LAUNCH("build_select_step", k_select_step, dim3(gS), dim3(kSelBT), 0, s, w.st, (const int32_t*)w.list,
+              (const int32_t*)w.cnt, key, o->seed);
+  HG_LAUNCH("build_select_finish", k_select_finish, dim3(1), dim3(kSelBT), 0, s, w.st, (const int32_t*)w.list,
+            (const int32_t*)w.cnt, key, o->seed);
+  // 5. the node set and its local ids in (ntype, gid) order
+  const bool rank_path = T <= 2;
+  const int64_t ntiles_n = cdiv(N, kNTile);
+  HG_LAUNCH("build_nodes_count", k_nodes_count, dim3((unsigned)ntiles_n), dim3(kBT), 0, s, (const uint32_t*)w.bbits,
+            g->ntype, w.first, key, (const SelectState*)w.st, o->seed, N, (int32_t)E, o->theta, o->budget_M,
+            (const int32_t*)w.cnt, w.rt, w.sel_bits, rank_path ? nullptr : w.sel, ntiles_n, w.tcnt);
+  if (rank_path) {
+    HG_TRY(scan_exclusive_i32(w.tcnt, w.tcnt, 4 * ntiles_n + 1, nullptr, w.scratch, s));
+    HG_LAUNCH("build_nodes_assign", k_nodes_assign, dim3((unsigned)ntiles_n), dim3(kBT), 0, s, w.rt,
+              (const uint64_t*)w.sel_bits, g->part, N, (int32_t)T, ntiles_n, (const int32_t*)w.tcnt,
+              out->local2global, out->global2local, out->type_off, type_copy, out->overlap, out->overlap_home, w.cnt);
+  } else {
+    HG_LAUNCH("build_member_digit", k_member_digit, dim3(gN), dim3(kBT), 0, s, g->part, g->k,
+              (const uint8_t*)w.sel, g->ntype, N, w.digit, w.iota);
+    HG_TRY(bucket_partition(w.digit, w.iota, N, (int)T, out->local2global, out->type_off, w.scratch, s));
+    HG_TRY(fill_i32(out->global2local, -1, N, s));
+    HG_LAUNCH("build_global2local", k_global2local, dim3(gN), dim3(kBT), 0, s,
+              (const int32_t*)out->local2global, (const int32_t*)out->type_off, (int32_t)T,
+              out->global2local, w.cnt);
+    HG_LAUNCH("build_overlap_flags", k_overlap_flags, dim3(gN), dim3(kBT), 0, s,
+              (const int32_t*)out->local2global, (const uint8_t*)w.sel, (const int32_t*)w.cnt, N, w.flag);
+    HG_TRY(scan_exclusive_i32(w.flag, w.pos, N, w.cnt + C_MSEL, w.scratch, s));
+    if (o->budget_M > 0)
+      HG_LAUNCH("build_overlap_fill", k_overlap_fill, dim3(gN), dim3(kBT), 0, s,
+                (const int32_t*)out->local2global, (const int32_t*)w.flag, (const int32_t*)w.pos,
+                (const int32_t*)w.cnt, g->part, out->overlap, out->overlap_home);
   }
-  // 5. local ids in (ntype, gid) order
-  HG_LAUNCH("build_member_digit", k_member_digit, dim3(gN), dim3(kBT), 0, s, g->part, g->k,
-            (const uint8_t*)w.sel, g->ntype, N, E, o->budget_M, (const int32_t*)w.cnt, w.digit, w.iota, w.first);
-  HG_TRY(bucket_partition(w.digit, w.iota, N, (int)T, out->local2global, out->type_off, w.scratch, s));
-  HG_TRY(fill_i32(out->global2local, -1, N, s));
-  HG_LAUNCH("build_global2local", k_global2local, dim3(gN), dim3(kBT), 0, s,
-            (const int32_t*)out->local2global, (const int32_t*)out->type_off, (int32_t)T,
-            out->global2local, w.cnt);
   // 6. induced-subgraph edges in original order, and the base edges of the
   // selected nodes
   // the CSR sort carries the edge id if asked for, else a weighted graph's weight
   const bool emit_w = weighted && !want_eid;
   // with at most two node types the CSR entries are formed in edge order and
   // compacted only if some edge was dropped (below, once the count is known)
-  bool rank_path = false;
   const int64_t ntiles = cdiv(E, kETile);
   if (E > 0) {
-    int32_t nb_host = 0;
-    HG_HIP_TRY(hipMemcpyAsync(&nb_host, w.cnt + C_BASE, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    HG_HIP_TRY(hipStreamSynchronize(s));
-    const bool dense = dense_build(nb_host, o->budget_M, N);
-    if (T <= 2) {
-      rank_path = true;
-      const int64_t nb = cdiv(N, 64) * 2;
-      HG_LAUNCH("build_rank_bits", k_rank_bits, dim3(grid_for(nb * kRankGroup)), dim3(kBT), 0, s, g->part, g->k,
-                (const uint8_t*)w.sel, g->ntype, N, w.rt, w.rc0, w.rc1);
-      HG_TRY(scan_exclusive_i32(w.rc0, w.rc0, nb, nullptr, w.scratch, s));
-      HG_TRY(scan_exclusive_i32(w.rc1, w.rc1, nb, nullptr, w.scratch, s));
-      HG_LAUNCH("build_rank_pack", k_rank_pack, dim3(grid_for(nb)), dim3(kBT), 0, s, (const int32_t*)w.rc0,
-                (const int32_t*)w.rc1, nb, w.rt);
+    if (rank_path) {
 #define HG_EDGE_IDS(TS_, W_)                                                                                   \
   HG_LAUNCH("build_edge_ids", (k_edge_ids<TS_, W_>), dim3((unsigned)ntiles), dim3(kBT), 0, s, g->src, g->dst,     \
             g->rel, (int32_t)R, (const RankEnt*)w.rt, (const int32_t*)out->type_off, (const uint32_t*)w.bbits,    \
-            g->edge_ts, g->t_cut, E, dense ? 0 : 1, w.kcsr, w.vsrc, want_eid ? w.veid : nullptr, g->edge_w,       \
-            emit_w ? w.vw : nullptr, reinterpret_cast<uint64_t*>(w.keep), w.tile_cnt, w.first)
+            g->edge_ts, g->t_cut, E, N, o->budget_M, (const int32_t*)w.cnt, w.kcsr, w.vsrc,                       \
+            want_eid ? w.veid : nullptr, g->edge_w, emit_w ? w.vw : nullptr,                                      \
+            reinterpret_cast<uint64_t*>(w.keep), w.tile_cnt, w.first)
       if (g->edge_ts) {
         if (emit_w) HG_EDGE_IDS(true, true); else HG_EDGE_IDS(true, false);
       } else {
@@ -1526,31 +1803,25 @@ extern "C" int hg_build_csr(const hg_graph_desc* g, const hg_overlap_desc* o, hg
       HG_LAUNCH("build_member_bits", k_member_bits, dim3(gB), dim3(kBT), 0, s, g->part, g->k,
                 (const uint8_t*)w.sel, N, w.mbits);
       HG_LAUNCH("build_edge_keep", k_edge_keep, dim3(gE), dim3(kBT), 0, s, g->src, g->dst,
-                (const uint32_t*)w.mbits, (const uint32_t*)w.bbits, g->edge_ts, g->t_cut, E, w.keep, w.first);
+                (const uint32_t*)w.mbits, (const uint32_t*)w.bbits, g->edge_ts, g->t_cut, E, w.keep, w.first,
+                (const int32_t*)w.cnt);
       // keep[E] = 0, so the scan's entry E is the number of kept edges
       HG_TRY(fill_i32(w.keep + E, 0, 1, s));
       HG_TRY(scan_exclusive_i32(w.keep, w.keep, E + 1, w.cnt + C_ESUB, w.scratch, s));
       HG_LAUNCH("build_edge_compact", k_edge_compact, dim3(gE), dim3(kBT), 0, s, g->src, g->dst,
                 (const int32_t*)out->global2local, g->rel, (const int32_t*)w.keep, E, (int32_t)R, w.kcsr, w.vsrc,
-                want_eid ? w.veid : nullptr, g->edge_w, emit_w ? w.vw : nullptr);
+                want_eid ? w.veid : nullptr, g->edge_w, emit_w ? w.vw : nullptr, (const int32_t*)w.cnt);
     }
-  } else {
-    HG_TRY(fill_i32(w.cnt + C_ESUB, 0, 1, s));
+    if (o->budget_M > 0)
+      HG_LAUNCH("build_overlap_rel", k_overlap_rel, dim3(grid_for(o->budget_M < N ? o->budget_M : N)), dim3(kBT), 0, s,
+                (const int32_t*)out->local2global, (const int32_t*)out->overlap, (const int32_t*)w.cnt,
+                (const int32_t*)w.first, g->rel, out->overlap_rel);
   }
-  // overlap list (local ids ascending) with each node's home block and the
-  // relation of its base edge
-  HG_LAUNCH("build_overlap_flags", k_overlap_flags, dim3(gN), dim3(kBT), 0, s,
-            (const int32_t*)out->local2global, (const uint8_t*)w.sel, (const int32_t*)w.cnt, N, w.flag);
-  HG_TRY(scan_exclusive_i32(w.flag, w.pos, N, w.cnt + C_MSEL, w.scratch, s));
-  if (o->budget_M > 0)
-    HG_LAUNCH("build_overlap_fill", k_overlap_fill, dim3(gN), dim3(kBT), 0, s,
-              (const int32_t*)out->local2global, (const int32_t*)w.flag, (const int32_t*)w.pos,
-              (const int32_t*)w.cnt, g->part, (const int32_t*)w.first, g->rel, out->overlap,
-              out->overlap_home, out->overlap_rel);
   // counts needed to size the sorts
   int32_t hc[C_COUNT];
   HG_HIP_TRY(hipMemcpyAsync(hc, w.cnt, sizeof(hc), hipMemcpyDeviceToHost, s));
   HG_HIP_TRY(hipStreamSynchronize(s));
+  if (hc[C_ERR]) return fail(HG_ERR_RANGE, "input ids out of range (flags 0x%x)", hc[C_ERR]);
   const int64_t NS = hc[C_NSUB], ES = hc[C_ESUB];
   const int64_t NQ = NS * R;
   // 7. CSR: stable sort by dst*R + r; CSC: stable sort of the CSR-ordered entries by src*R + r
@@ -1628,6 +1899,7 @@ extern "C" int hg_build_csr(const hg_graph_desc* g, const hg_overlap_desc* o, hg
                      reinterpret_cast<int4*>(pb + pl.fheavy_off),
                      act,
                      act_off,
+                     act_copy,
                      act_slot,
                      slot_q,
                      tab};
@@ -1642,15 +1914,16 @@ extern "C" int hg_build_csr(const hg_graph_desc* g, const hg_overlap_desc* o, hg
                 (const SlotEnt*)tab, csr_slot);
   } else {
     HG_TRY(fill_i32(act_off, 0, R + 1, s));
-    HG_TRY(fill_i32(w.cnt + C_ITEMS, 0, 3, s));
-    HG_TRY(fill_i32(w.cnt + C_FHEAVY, 0, 3, s));
+    HG_TRY(fill_i32(act_copy, 0, R + 1, s));
   }
   // final sync: host counts
-  std::vector<int32_t> tof(T + 1), aof(R + 1);
-  HG_HIP_TRY(hipMemcpyAsync(hc, w.cnt, sizeof(hc), hipMemcpyDeviceToHost, s));
-  HG_HIP_TRY(hipMemcpyAsync(tof.data(), out->type_off, sizeof(int32_t) * (T + 1), hipMemcpyDeviceToHost, s));
-  HG_HIP_TRY(hipMemcpyAsync(aof.data(), act_off, sizeof(int32_t) * (R + 1), hipMemcpyDeviceToHost, s));
+  std::vector<int32_t> head(n_head);
+  HG_HIP_TRY(hipMemcpyAsync(head.data(), w.cnt, sizeof(int32_t) * n_head, hipMemcpyDeviceToHost, s));
+  if (!rank_path)
+    HG_HIP_TRY(hipMemcpyAsync(head.data() + C_COUNT, out->type_off, sizeof(int32_t) * (T + 1), hipMemcpyDeviceToHost, s));
   HG_HIP_TRY(hipStreamSynchronize(s));
+  std::copy(head.begin(), head.begin() + C_COUNT, hc);
+  const int32_t *tof = head.data() + C_COUNT, *aof = tof + T + 1;
   out->n_nodes = N;
   out->n_edges = E;
   out->n_sub = NS;
