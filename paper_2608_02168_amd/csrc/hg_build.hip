@@ -5,7 +5,8 @@
 //   1. one pass over the edges: range checks, out-degrees, and for every node
 //      outside V_k the smallest index of an edge joining it to V_k (either
 //      direction) -- a node is a candidate of C_k iff that index exists;
-//   2. node keys: out-degree, or the h-index of the out-neighbour multiset;
+//   2. node keys: out-degree, or the h-index of the out-neighbour multiset
+//      (edges sorted by source);
 //   3. C'_k = candidates with key <= theta, compacted in gid order;
 //   4. TopM: an exact radix select of the min(M, |C'_k|) smallest 128-bit
 //      composites (key, splitmix64(seed ^ gid), gid) -- unique by gid, so the
@@ -42,7 +43,8 @@ __device__ __forceinline__ int64_t cdiv_dev(int64_t a, int64_t b) { return (a + 
 
 // Device counters written by the build.
 enum : int { C_ERR = 0, C_NSUB, C_ESUB, C_MSEL, C_ITEMS, C_HEAVY, C_PARTS, C_CPRIME, C_BASE, C_FHEAVY, C_FPARTS,
-             C_ASLOTS, C_GAP_CSR, C_GAP_CSC, C_COUNT };
+             C_ASLOTS, C_GAP_CSR, C_GAP_CSC, C_GAP_HI, C_HI_BLOCK,
+             C_HI_LONG, C_HI_PARTS, C_COUNT };
 
 // The row-indexed layout of the relation transforms is kept when nq rows cost
 // at most kRowLayoutMaxSpread times the a active ones.
@@ -64,7 +66,7 @@ __host__ __device__ inline bool dense_build(int64_t n_base, int64_t budget, int6
 // range [lo, hi] that holds the last one taken, a digit of up to 11 bits at a
 // time; the selected set is then every candidate up to (khi, hhi).
 constexpr int kSelBins = 2048;   // values of a digit
-constexpr int kSelSmall = 1024;  // a range this small is ranked by one block
+constexpr int kSelSmall = 256;   // a range this small is ranked by one block
 enum : uint32_t { S_SEARCH = 0, S_DONE, S_NONE, S_COLLECT, S_RANK };
 struct SelectState {
   uint64_t hlo, hhi;  // hash range, when klo == khi
@@ -302,14 +304,13 @@ constexpr int kEpItems = 4;
 // by an edge gets first[v] < n_edges -- in a dense build the smallest index of
 // such an edge (block-aggregated atomic minimum), otherwise 0 (a plain store:
 // every writer stores the same value, and a node already marked is only
-// read).  Out-degrees: of every node when count_all (the h-index needs them),
-// else of the nodes outside V_k when count_out (the out-degree key of the
-// candidates, all of which lie outside V_k), else none (keys given by the
-// caller).
+// read).  Out-degrees: of the nodes outside V_k when count_out (the out-degree
+// key of the candidates, all of which lie outside V_k), else none (the h-index,
+// or keys given by the caller).
 __global__ void __launch_bounds__(kAggBT) k_edges_pass(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
                                                    const uint8_t* __restrict__ rel,
                                                    const uint32_t* __restrict__ base_bits, int64_t n_nodes,
-                                                   int64_t n_edges, int32_t n_rel, int count_all, int count_out,
+                                                   int64_t n_edges, int32_t n_rel, int count_out,
                                                    int64_t budget, int32_t* __restrict__ outdeg,
                                                    int32_t* __restrict__ first, int32_t* __restrict__ cnt) {
   __shared__ uint32_t lk[3][kAggSlots];
@@ -317,8 +318,7 @@ __global__ void __launch_bounds__(kAggBT) k_edges_pass(const int32_t* __restrict
   LdsAgg<false> deg{lk[0], lv[0]};
   LdsAgg<true> fs{lk[1], lv[1]}, fd{lk[2], lv[2]};
   const bool exact = dense_build(cnt[C_BASE], budget, n_nodes);
-  const bool counting = count_all || count_out;
-  if (counting) deg.init();
+  if (count_out) deg.init();
   if (exact) {
     fs.init();
     fd.init();
@@ -368,7 +368,7 @@ __global__ void __launch_bounds__(kAggBT) k_edges_pass(const int32_t* __restrict
       if (!ok[j]) continue;
       const int64_t e = e0 + j * stride;
       const int32_t s = sv[j], d = dv[j];
-      if (count_all || (count_out && !ps[j])) deg.put((uint32_t)s, 1, outdeg);
+      if (count_out && !ps[j]) deg.put((uint32_t)s, 1, outdeg);
       if (exact) {
         if (pd[j] && !ps[j]) fs.put((uint32_t)s, (int32_t)e, first);
         if (ps[j] && !pd[j]) fd.put((uint32_t)d, (int32_t)e, first);
@@ -379,11 +379,23 @@ __global__ void __launch_bounds__(kAggBT) k_edges_pass(const int32_t* __restrict
     }
   }
   __syncthreads();
-  if (counting) deg.flush(outdeg);
+  if (count_out) deg.flush(outdeg);
   if (exact) {
     fs.flush(first);
     fd.flush(first);
   }
+}
+
+// The range checks of the edge arrays alone.
+__global__ void __launch_bounds__(kBT) k_check_edges(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
+                                                     const uint8_t* __restrict__ rel, int64_t n_nodes,
+                                                     int64_t n_edges, int32_t n_rel, int32_t* __restrict__ cnt) {
+  bool bad = false;
+  GRID_STRIDE(e, n_edges) {
+    const int32_t s = src[e], d = dst[e];
+    bad |= s < 0 || s >= n_nodes || d < 0 || d >= n_nodes || rel[e] >= (uint32_t)n_rel;
+  }
+  if (bad) atomicOr(&cnt[C_ERR], 1);
 }
 
 // Out-degrees of every node, with the range checks of the edge arrays.
@@ -424,55 +436,382 @@ __global__ void __launch_bounds__(kAggBT) k_all_outdeg(const int32_t* __restrict
   deg.flush(outdeg);
 }
 
-// h-index histogram sizes: D+1 bins for every candidate of out-degree D.
-__global__ void k_hindex_sizes(const int32_t* __restrict__ outdeg, const int32_t* __restrict__ first,
-                               int64_t n, int32_t n_edges, int32_t* __restrict__ sz) {
-  GRID_STRIDE(v, n) { sz[v] = (first[v] < n_edges) ? outdeg[v] + 1 : 0; }
+// Row pointers of sorted keys: ptr[q] = the number of keys below q, for q in
+// [0, nq].  Every position p whose key differs from its predecessor's owns the
+// rows (key[p - 1], key[p]] and the last position also those up to nq; one
+// thread takes kRpItems keys a block's width apart, so a wave's keys and most
+// of its pointers are consecutive.  A gap of more than kRpInline empty rows
+// goes to a list in pieces of kRpPiece rows, filled by k_row_gaps over the
+// whole grid (one thread would write a graph's whole tail of nodes without
+// out-edges by itself).  Bound by its bytes: at 200M keys and 50M rows 1.0 GB
+// in 0.27 ms a sort; counting the rows with LDS and atomics, then scanning the
+// 50M counts, took 0.75 ms (fill 0.06, counts 0.33, scan 0.36).
+constexpr int kRpItems = 8;
+constexpr int kRpInline = 64;
+constexpr int kRpPiece = 16384;
+
+__device__ __forceinline__ void row_gap(int32_t* __restrict__ ptr, int32_t lo, int32_t hi, int32_t p,
+                                        int4* __restrict__ gaps, int32_t* __restrict__ n_gaps) {
+  if (hi - lo <= kRpInline) {
+    for (int32_t q = lo; q < hi; ++q) ptr[q] = p;
+    return;
+  }
+  const int32_t np = (hi - lo - 1) / kRpPiece + 1;
+  const int32_t at = atomicAdd(n_gaps, np);
+  for (int32_t i = 0; i < np; ++i) {
+    const int32_t l = lo + i * kRpPiece;
+    gaps[at + i] = make_int4(l, hi - l < kRpPiece ? hi : l + kRpPiece, p, 0);
+  }
 }
 
-__global__ void __launch_bounds__(kAggBT) k_hindex_hist(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
-                                                    int64_t n_edges, const int32_t* __restrict__ outdeg,
-                                                    const int32_t* __restrict__ first,
-                                                    const int32_t* __restrict__ hoff, int32_t* __restrict__ hist,
-                                                    const int32_t* __restrict__ cnt) {
-  if (cnt[C_ERR]) return;  // an endpoint out of range
-  __shared__ uint32_t lk[kAggSlots];
-  __shared__ int32_t lv[kAggSlots];
-  LdsAgg<false> agg{lk, lv};
-  agg.init();
-  __syncthreads();
-  GRID_STRIDE(e, n_edges) {
-    const int32_t s = src[e];
-    if (first[s] < (int32_t)n_edges) {
-      const int32_t ds = outdeg[s];
-      const int32_t c = min(outdeg[dst[e]], ds);
-      agg.put((uint32_t)(hoff[s] + c), 1, hist);  // hoff[s] + c < E + N < 2^31
+__global__ void __launch_bounds__(kBT) k_row_ptr(const uint32_t* __restrict__ keys, int64_t n, int32_t nq,
+                                                 int32_t* __restrict__ ptr, int4* __restrict__ gaps,
+                                                 int32_t* __restrict__ n_gaps, const int32_t* __restrict__ err) {
+  if (err && *err) return;  // keys may lie past nq
+  const int64_t base = (int64_t)blockIdx.x * (kBT * kRpItems) + threadIdx.x;
+  const int lane = threadIdx.x & 63;
+  int32_t k[kRpItems], head[kRpItems];
+#pragma unroll
+  for (int j = 0; j < kRpItems; ++j) {
+    const int64_t p = base + (int64_t)j * kBT;
+    k[j] = (int32_t)keys[p < n ? p : n - 1];
+    // the key before the wave's first one (-1 before the first key)
+    head[j] = -1;
+    if (lane == 0 && p > 0 && p < n) head[j] = (int32_t)keys[p - 1];
+  }
+#pragma unroll
+  for (int j = 0; j < kRpItems; ++j) {
+    const int64_t p = base + (int64_t)j * kBT;
+    const int32_t up = __shfl_up(k[j], 1, 64);
+    const int32_t prev = lane == 0 ? head[j] : up;
+    if (p < n) {
+      if (k[j] != prev) row_gap(ptr, prev + 1, k[j] + 1, (int32_t)p, gaps, n_gaps);
+      if (p == n - 1) row_gap(ptr, k[j] + 1, nq + 1, (int32_t)n, gaps, n_gaps);
     }
   }
-  __syncthreads();
-  agg.flush(hist);
 }
 
-// key[v] = max h with #{neighbour degrees >= h} >= h, scanning h upwards.
-__global__ void k_hindex_final(const int32_t* __restrict__ outdeg, const int32_t* __restrict__ first,
-                               const int32_t* __restrict__ hoff, const int32_t* __restrict__ hist,
-                               int64_t n, int32_t n_edges, int32_t* __restrict__ key) {
-  GRID_STRIDE(v, n) {
-    if (first[v] >= n_edges) continue;
-    const int32_t D = outdeg[v];
-    const int32_t* hv = hist + hoff[v];
-    int32_t h = 0, ge = D;  // ge = #{values >= h}
-    while (h < D) {
-      const int32_t nxt = ge - hv[h];
-      if (nxt >= h + 1) {
-        ++h;
-        ge = nxt;
-      } else {
-        break;
+__global__ void __launch_bounds__(kBT) k_row_gaps(const int4* __restrict__ gaps, const int32_t* __restrict__ n_gaps,
+                                                  int32_t* __restrict__ ptr) {
+  const int32_t n = *n_gaps;
+  for (int32_t i = blockIdx.x; i < n; i += gridDim.x) {
+    const int4 g = gaps[i];
+    for (int32_t q = g.x + (int32_t)threadIdx.x; q < g.y; q += kBT) ptr[q] = g.z;
+  }
+}
+
+// Entries the gap list can hold: gaps longer than kRpInline rows, each a
+// piece more than its full pieces.
+inline int64_t gap_cap(int64_t nq) { return nq / kRpInline + nq / kRpPiece + 2; }
+
+int row_pointers(const uint32_t* keys, int64_t n, int64_t nq, int32_t* ptr, int4* gaps, int32_t* n_gaps,
+                 const int32_t* err, hipStream_t s) {
+  if (n <= 0) return fill_i32(ptr, 0, nq + 1, s);
+  HG_LAUNCH("build_row_ptr", k_row_ptr, dim3((unsigned)cdiv(n, kBT * kRpItems)), dim3(kBT), 0, s, keys, n, (int32_t)nq,
+            ptr, gaps, n_gaps, err);
+  const int64_t cap = gap_cap(nq), most = 4 * (int64_t)num_cus();
+  HG_LAUNCH("build_row_gaps", k_row_gaps, dim3((unsigned)(cap < most ? cap : most)), dim3(kBT), 0, s,
+            (const int4*)gaps, (const int32_t*)n_gaps, ptr);
+  return HG_OK;
+}
+
+int bits_for(int64_t nvals) {
+  int b = 0;
+  while (b < 32 && ((int64_t)1 << b) < nvals) ++b;
+  return b;
+}
+
+// ---- h-index keys ---------------------------------------------------------------
+// key[v] = the largest h with at least h out-neighbours (one per edge) of
+// out-degree at least h.  The edges are sorted by source, so a node's
+// out-neighbours lie together and out-degrees are differences of row pointers;
+// one histogram bin per edge and node, filled by a global atomic per edge, took
+// 2.3 ms at 50M edges besides the 1.0 ms that counted the degrees, the sort and
+// the rows below take 1.5 ms.  h = max_i min(x_i, #{j : x_j >= x_i}), found
+//   - for up to kHiSmall neighbours by 16 lanes, all pairs;
+//   - up to kHiWave by one wave, a binary search over h on ballots;
+//   - up to kHiBlock by one block, longer rows by blocks of kHiPart neighbours
+//     each (parts): a histogram of the degrees below kHiBins (values below 8, most of
+//     them, counted by ballots), whose suffix sums meet h.
+// A row whose h is kHiBins or more is walked once more per kHiBins values.
+constexpr int kHiSmall = 16, kHiWave = 1024, kHiBlock = 16384, kHiPart = 8192;
+constexpr int kHiBins = 4096;
+constexpr int kHiBT = 1024;
+
+__device__ __forceinline__ int32_t deg_of(const int32_t* __restrict__ ptr, int32_t v) { return ptr[v + 1] - ptr[v]; }
+
+// Rows of up to kHiWave neighbours; the longer ones go to lists.  A caller that
+// filters by key <= theta needs no key above it: a row with theta + 1 = over
+// neighbours of at least that degree among its first 64 gets the key over (most
+// rows of more than 16 neighbours end here; at theta = 2 the h-index of 50M
+// edges takes 0.3 ms after the sort instead of 0.7).
+__global__ void __launch_bounds__(kBT) k_hindex_rows(const int32_t* __restrict__ ptr, const int32_t* __restrict__ col,
+                                                     const int32_t* __restrict__ first, int64_t n, int32_t n_edges,
+                                                     int32_t* __restrict__ key, int32_t* __restrict__ list_b,
+                                                     int32_t* __restrict__ list_l, int2* __restrict__ parts,
+                                                     int32_t* __restrict__ n_list, int32_t over,
+                                                     const int32_t* __restrict__ err) {
+  if (*err) return;
+  const int l = threadIdx.x & 63, sub = l & (kHiSmall - 1), grp = l >> 4;
+  const int64_t waves = (int64_t)gridDim.x * (kBT / 64);
+  for (int64_t b = (int64_t)blockIdx.x * (kBT / 64) + (threadIdx.x >> 6); b * 64 < n; b += waves) {
+    const int64_t v = b * 64 + l;
+    const bool want = v < n && (!first || first[v] < n_edges);
+    const int32_t beg = want ? ptr[v] : 0;
+    const int32_t D = want ? ptr[v + 1] - beg : 0;
+    if (want && D == 0) key[v] = 0;
+    // four nodes at a time
+    for (uint64_t left = __ballot(D > 0 && D <= kHiSmall); left;) {
+      int mine = -1;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if (left) {
+          const int u = __ffsll((unsigned long long)left) - 1;
+          left &= left - 1;
+          if (grp == q) mine = u;
+        }
       }
+      const int from = mine < 0 ? 0 : mine;
+      const int32_t mb = __shfl(beg, from, 64), fd = __shfl(D, from, 64), md = mine < 0 ? 0 : fd;
+      int32_t x = -1;
+      if (sub < md) x = deg_of(ptr, col[mb + sub]);
+      int ge = 0;
+#pragma unroll
+      for (int q = 0; q < kHiSmall; ++q) ge += __shfl(x, (l & ~(kHiSmall - 1)) + q, 64) >= x;
+      int h = sub < md ? (x < ge ? x : ge) : 0;
+#pragma unroll
+      for (int o = kHiSmall / 2; o > 0; o >>= 1) {
+        const int y = __shfl_xor(h, o, 64);
+        h = h > y ? h : y;
+      }
+      if (mine >= 0 && sub == 0) key[b * 64 + mine] = h;
     }
-    key[v] = h;
+    for (uint64_t left = __ballot(D > kHiSmall); left; left &= left - 1) {
+      const int u = __ffsll((unsigned long long)left) - 1;
+      const int32_t mb = __shfl(beg, u, 64), md = __shfl(D, u, 64);
+      if (over <= 64) {
+        const int32_t x = l < md ? deg_of(ptr, col[mb + l]) : -1;
+        if ((int)__popcll(__ballot(x >= over)) >= over) {
+          if (l == 0) key[b * 64 + u] = over;
+          continue;
+        }
+      }
+      if (md > kHiWave) {
+        if (l != u) continue;
+        if (md <= kHiBlock) {
+          list_b[atomicAdd(&n_list[0], 1)] = (int32_t)v;
+          continue;
+        }
+        const int32_t at = atomicAdd(&n_list[1], 1), np = (md - 1) / kHiPart + 1;
+        const int32_t p0 = atomicAdd(&n_list[2], np);
+        list_l[at] = (int32_t)v;
+        for (int32_t c = 0; c < np; ++c) parts[p0 + c] = make_int2(at, c);
+        continue;
+      }
+      int32_t x[kHiWave / 64];
+#pragma unroll
+      for (int q = 0; q < kHiWave / 64; ++q) x[q] = 64 * q + l < md ? col[mb + 64 * q + l] : -1;
+#pragma unroll
+      for (int q = 0; q < kHiWave / 64; ++q) x[q] = x[q] >= 0 ? deg_of(ptr, x[q]) : -1;
+      int lo = 0, hi = md;
+      while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        int c = 0;
+#pragma unroll
+        for (int q = 0; q < kHiWave / 64; ++q)
+          if (64 * q < md) c += (int)__popcll(__ballot(x[q] >= mid));
+        if (c >= mid) lo = mid; else hi = mid - 1;
+      }
+      if (l == 0) key[b * 64 + u] = lo;
+    }
   }
+}
+
+// Adds the degrees of neighbours [beg, end) into the block's histogram of
+// min(x - base, kHiBins) (values below base are left out).
+__device__ __forceinline__ void hindex_add(const int32_t* __restrict__ ptr, const int32_t* __restrict__ col,
+                                           int32_t beg, int32_t end, int32_t base, int32_t* lh) {
+  constexpr int kU = 4, kLow = 8;
+  int32_t low[kLow];
+#pragma unroll
+  for (int t = 0; t < kLow; ++t) low[t] = 0;
+  for (int32_t p0 = beg; p0 < end; p0 += kHiBT * kU) {
+    int32_t x[kU];
+#pragma unroll
+    for (int j = 0; j < kU; ++j) {
+      const int64_t p = (int64_t)p0 + j * kHiBT + threadIdx.x;
+      x[j] = p < end ? col[p] : -1;
+    }
+#pragma unroll
+    for (int j = 0; j < kU; ++j) x[j] = x[j] >= 0 ? deg_of(ptr, x[j]) - base : -1;
+#pragma unroll
+    for (int j = 0; j < kU; ++j) {
+#pragma unroll
+      for (int t = 0; t < kLow; ++t) low[t] += (int32_t)__popcll(__ballot(x[j] == t));
+      if (x[j] >= kLow) atomicAdd(&lh[x[j] < kHiBins ? x[j] : kHiBins], 1);
+    }
+  }
+  if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+    for (int t = 0; t < kLow; ++t)
+      if (low[t]) atomicAdd(&lh[t], low[t]);
+  }
+}
+
+// The largest t in [1, kHiBins] with #{x >= t + base} >= t + base, or 0, from
+// the histogram (to all threads of the block).
+__device__ __forceinline__ int hindex_meet(const int32_t* lh, int32_t base, int32_t* red, int* best) {
+  constexpr int kPer = kHiBins / kHiBT;
+  int32_t c[kPer], sum = 0;
+#pragma unroll
+  for (int i = kPer - 1; i >= 0; --i) {  // thread's values t = kPer tid + i + 1: counts of x >= t
+    sum += lh[threadIdx.x * kPer + i + 1];
+    c[i] = sum;
+  }
+  red[threadIdx.x] = sum;
+  if (threadIdx.x == 0) *best = 0;
+  __syncthreads();
+  for (int o = 1; o < kHiBT; o <<= 1) {  // inclusive suffix sums
+    const int32_t u = threadIdx.x + o < kHiBT ? red[threadIdx.x + o] : 0;
+    __syncthreads();
+    red[threadIdx.x] += u;
+    __syncthreads();
+  }
+  const int32_t after = red[threadIdx.x] - sum;
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    const int t = (int)threadIdx.x * kPer + i + 1;
+    if (c[i] + after >= t + base) atomicMax(best, t);
+  }
+  __syncthreads();
+  return *best;
+}
+
+// h of one row by a block, starting from a histogram that already holds the
+// whole row with base 0.
+__device__ __forceinline__ void hindex_finish(const int32_t* __restrict__ ptr, const int32_t* __restrict__ col,
+                                              int32_t v, int32_t* lh, int32_t* red, int* best,
+                                              int32_t* __restrict__ key) {
+  int32_t base = 0;
+  for (;;) {
+    const int t = hindex_meet(lh, base, red, best);
+    if (t < kHiBins) {  // also 0: h is the base itself
+      if (threadIdx.x == 0) key[v] = base + t;
+      __syncthreads();
+      return;
+    }
+    base += kHiBins;  // at most n_edges / kHiBins windows
+    __syncthreads();
+    for (int i = threadIdx.x; i <= kHiBins; i += kHiBT) lh[i] = 0;
+    __syncthreads();
+    hindex_add(ptr, col, ptr[v], ptr[v + 1], base, lh);
+    __syncthreads();
+  }
+}
+
+__global__ void __launch_bounds__(kHiBT) k_hindex_block(const int32_t* __restrict__ ptr,
+                                                        const int32_t* __restrict__ col,
+                                                        const int32_t* __restrict__ list,
+                                                        const int32_t* __restrict__ n_list,
+                                                        int32_t* __restrict__ key) {
+  __shared__ int32_t lh[kHiBins + 1];
+  __shared__ int32_t red[kHiBT];
+  __shared__ int best;
+  const int32_t n = n_list[0];
+  for (int32_t i = blockIdx.x; i < n; i += gridDim.x) {
+    const int32_t v = list[i];
+    for (int b = threadIdx.x; b <= kHiBins; b += kHiBT) lh[b] = 0;
+    __syncthreads();
+    hindex_add(ptr, col, ptr[v], ptr[v + 1], 0, lh);
+    __syncthreads();
+    hindex_finish(ptr, col, v, lh, red, &best, key);
+  }
+}
+
+// Long rows: their parts' histograms added into one of kHiBins + 1 words per
+// row (zeroed here first: phase 0), then met by a block per row.
+__global__ void __launch_bounds__(kHiBT) k_hindex_zero(const int32_t* __restrict__ n_list, int32_t* __restrict__ hist) {
+  const int64_t n = (int64_t)n_list[1] * (kHiBins + 1);
+  GRID_STRIDE(i, n) hist[i] = 0;
+}
+
+__global__ void __launch_bounds__(kHiBT) k_hindex_parts(const int32_t* __restrict__ ptr,
+                                                        const int32_t* __restrict__ col,
+                                                        const int32_t* __restrict__ list,
+                                                        const int2* __restrict__ parts,
+                                                        const int32_t* __restrict__ n_list,
+                                                        int32_t* __restrict__ hist) {
+  __shared__ int32_t lh[kHiBins + 1];
+  const int32_t n = n_list[2];
+  for (int32_t i = blockIdx.x; i < n; i += gridDim.x) {
+    const int2 pt = parts[i];
+    const int32_t v = list[pt.x], end = ptr[v + 1], p = ptr[v] + pt.y * kHiPart;
+    for (int b = threadIdx.x; b <= kHiBins; b += kHiBT) lh[b] = 0;
+    __syncthreads();
+    hindex_add(ptr, col, p, end - p < kHiPart ? end : p + kHiPart, 0, lh);
+    __syncthreads();
+    for (int b = threadIdx.x; b <= kHiBins; b += kHiBT)
+      if (lh[b]) atomicAdd(&hist[(int64_t)pt.x * (kHiBins + 1) + b], lh[b]);
+    __syncthreads();
+  }
+}
+
+__global__ void __launch_bounds__(kHiBT) k_hindex_long(const int32_t* __restrict__ ptr,
+                                                       const int32_t* __restrict__ col,
+                                                       const int32_t* __restrict__ list,
+                                                       const int32_t* __restrict__ n_list,
+                                                       const int32_t* __restrict__ hist, int32_t* __restrict__ key) {
+  __shared__ int32_t lh[kHiBins + 1];
+  __shared__ int32_t red[kHiBT];
+  __shared__ int best;
+  const int32_t n = n_list[1];
+  for (int32_t i = blockIdx.x; i < n; i += gridDim.x) {
+    for (int b = threadIdx.x; b <= kHiBins; b += kHiBT) lh[b] = hist[(int64_t)i * (kHiBins + 1) + b];
+    __syncthreads();
+    hindex_finish(ptr, col, list[i], lh, red, &best, key);
+  }
+}
+
+// Buffers of the h-index: the sort's ping-pong pairs (n_edges each), row
+// pointers (n_nodes + 1), the lists of long rows and the longest ones'
+// histograms.
+struct HindexBufs {
+  uint32_t *k0, *k1;
+  int32_t *v0, *v1, *ptr, *list_b, *list_l, *hist, *scratch;
+  int2* parts;
+  int4* gaps;
+  int32_t *n_gaps, *n_list;  // zero on entry (one and three words)
+};
+inline int64_t hindex_list_b(int64_t E) { return E / kHiWave + 1; }
+inline int64_t hindex_list_l(int64_t E) { return E / kHiBlock + 1; }
+inline int64_t hindex_parts(int64_t E) { return E / kHiPart + hindex_list_l(E); }
+inline int64_t hindex_hist_elems(int64_t E) { return hindex_list_l(E) * (kHiBins + 1); }
+
+// key[v] for every node with first[v] < n_edges (every node if first is
+// null); keys above theta may come out as any value above it.  err: device flag, non-zero when an endpoint is out of range (the
+// keys are then unspecified, and nothing is read or written out of bounds).
+int hindex_keys(const int32_t* src, const int32_t* dst, int64_t N, int64_t E, const int32_t* first, int32_t theta,
+                int32_t* key, const HindexBufs& b, const int32_t* err, hipStream_t s) {
+  uint32_t* ko;
+  int32_t *col, *none;
+  HG_TRY(radix_sort_pairs(b.k0, b.k1, b.v0, b.v1, nullptr, nullptr, E, bits_for(N), b.scratch, s, &ko, &col, &none,
+                          nullptr, nullptr, nullptr, reinterpret_cast<const uint32_t*>(src), dst));
+  HG_TRY(row_pointers(ko, E, N, b.ptr, b.gaps, b.n_gaps, err, s));
+  const unsigned cus = (unsigned)num_cus();
+  HG_LAUNCH("hindex_rows", k_hindex_rows, dim3(grid_for(N)), dim3(kBT), 0, s, (const int32_t*)b.ptr,
+            (const int32_t*)col, first, N, (int32_t)E, key, b.list_b, b.list_l, b.parts, b.n_list,
+            theta < HG_THETA_NONE ? theta + 1 : theta, err);
+  if (E > kHiWave)
+    HG_LAUNCH("hindex_block", k_hindex_block, dim3(2 * cus), dim3(kHiBT), 0, s, (const int32_t*)b.ptr,
+              (const int32_t*)col, (const int32_t*)b.list_b, (const int32_t*)b.n_list, key);
+  if (E > kHiBlock) {
+    HG_LAUNCH("hindex_zero", k_hindex_zero, dim3(cus), dim3(kHiBT), 0, s, (const int32_t*)b.n_list, b.hist);
+    HG_LAUNCH("hindex_parts", k_hindex_parts, dim3(2 * cus), dim3(kHiBT), 0, s, (const int32_t*)b.ptr,
+              (const int32_t*)col, (const int32_t*)b.list_l, (const int2*)b.parts, (const int32_t*)b.n_list, b.hist);
+    HG_LAUNCH("hindex_long", k_hindex_long, dim3(cus), dim3(kHiBT), 0, s, (const int32_t*)b.ptr,
+              (const int32_t*)col, (const int32_t*)b.list_l, (const int32_t*)b.n_list, (const int32_t*)b.hist, key);
+  }
+  return HG_OK;
 }
 
 // ---- TopM ---------------------------------------------------------------------
@@ -495,14 +834,17 @@ __device__ __forceinline__ uint32_t load_agent(const uint32_t* p) {
 // Adds a block's histogram into the state's and tells, to all threads,
 // whether the block is the launch's last one.
 __device__ __forceinline__ bool select_add(SelectState* st, const int32_t* lh, int* flag) {
+  // Everything one block hands to the last (histogram, list count, a small
+  // range's composites) goes through device-scope atomics, which are complete
+  // once each wave has waited for them; a full fence would write the block's
+  // L2 back (the step 42 us instead of 10 at 2M candidates).
   __syncthreads();
   for (int b = threadIdx.x; b < kSelBins; b += kSelBT)
     if (lh[b]) atomicAdd(&st->hist[b], lh[b]);
-  __threadfence();
+  __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
   if (threadIdx.x == 0) *flag = atomicAdd(&st->done, 1u) == gridDim.x - 1;
   __syncthreads();
-  __threadfence();
   return *flag != 0;
 }
 
@@ -617,8 +959,8 @@ __device__ __forceinline__ void select_round(SelectState* st, const int32_t* __r
     if (!select_in_range(st, kv, h)) continue;
     if (mode == S_COLLECT) {
       const uint32_t at = atomicAdd(&st->n_small, 1u);
-      st->small[at][0] = kv;
-      st->small[at][1] = h;
+      __hip_atomic_store(&st->small[at][0], (uint64_t)kv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(&st->small[at][1], h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     } else {
       atomicAdd(&lh[select_digit(level, kv, h)], 1);
     }
@@ -1079,73 +1421,6 @@ __global__ void k_edge_compact(const int32_t* __restrict__ src, const int32_t* _
   }
 }
 
-// Row pointers of sorted keys: ptr[q] = the number of keys below q, for q in
-// [0, nq].  Every position p whose key differs from its predecessor's owns the
-// rows (key[p - 1], key[p]] and the last position also those up to nq; one
-// thread takes kRpItems keys a block's width apart, so a wave's keys and most
-// of its pointers are consecutive.  A gap of more than kRpInline empty rows
-// goes to a list in pieces of kRpPiece rows, filled by k_row_gaps over the
-// whole grid (one thread would write a graph's whole tail of nodes without
-// out-edges by itself).  Bound by its bytes: at 200M keys and 50M rows 1.0 GB
-// in 0.27 ms a sort; counting the rows with LDS and atomics, then scanning the
-// 50M counts, took 0.75 ms (fill 0.06, counts 0.33, scan 0.36).
-constexpr int kRpItems = 8;
-constexpr int kRpInline = 64;
-constexpr int kRpPiece = 16384;
-
-__device__ __forceinline__ void row_gap(int32_t* __restrict__ ptr, int32_t lo, int32_t hi, int32_t p,
-                                        int4* __restrict__ gaps, int32_t* __restrict__ n_gaps) {
-  if (hi - lo <= kRpInline) {
-    for (int32_t q = lo; q < hi; ++q) ptr[q] = p;
-    return;
-  }
-  const int32_t np = (hi - lo - 1) / kRpPiece + 1;
-  const int32_t at = atomicAdd(n_gaps, np);
-  for (int32_t i = 0; i < np; ++i) {
-    const int32_t l = lo + i * kRpPiece;
-    gaps[at + i] = make_int4(l, hi - l < kRpPiece ? hi : l + kRpPiece, p, 0);
-  }
-}
-
-__global__ void __launch_bounds__(kBT) k_row_ptr(const uint32_t* __restrict__ keys, int64_t n, int32_t nq,
-                                                 int32_t* __restrict__ ptr, int4* __restrict__ gaps,
-                                                 int32_t* __restrict__ n_gaps) {
-  const int64_t base = (int64_t)blockIdx.x * (kBT * kRpItems) + threadIdx.x;
-  const int lane = threadIdx.x & 63;
-  int32_t k[kRpItems], head[kRpItems];
-#pragma unroll
-  for (int j = 0; j < kRpItems; ++j) {
-    const int64_t p = base + (int64_t)j * kBT;
-    k[j] = (int32_t)keys[p < n ? p : n - 1];
-    // the key before the wave's first one (-1 before the first key)
-    head[j] = -1;
-    if (lane == 0 && p > 0 && p < n) head[j] = (int32_t)keys[p - 1];
-  }
-#pragma unroll
-  for (int j = 0; j < kRpItems; ++j) {
-    const int64_t p = base + (int64_t)j * kBT;
-    const int32_t up = __shfl_up(k[j], 1, 64);
-    const int32_t prev = lane == 0 ? head[j] : up;
-    if (p < n) {
-      if (k[j] != prev) row_gap(ptr, prev + 1, k[j] + 1, (int32_t)p, gaps, n_gaps);
-      if (p == n - 1) row_gap(ptr, k[j] + 1, nq + 1, (int32_t)n, gaps, n_gaps);
-    }
-  }
-}
-
-__global__ void __launch_bounds__(kBT) k_row_gaps(const int4* __restrict__ gaps, const int32_t* __restrict__ n_gaps,
-                                                  int32_t* __restrict__ ptr) {
-  const int32_t n = *n_gaps;
-  for (int32_t i = blockIdx.x; i < n; i += gridDim.x) {
-    const int4 g = gaps[i];
-    for (int32_t q = g.x + (int32_t)threadIdx.x; q < g.y; q += kBT) ptr[q] = g.z;
-  }
-}
-
-// Entries the gap list can hold: gaps longer than kRpInline rows, each a
-// piece more than its full pieces.
-inline int64_t gap_cap(int64_t nq) { return nq / kRpInline + nq / kRpPiece + 2; }
-
 // The CSC sort's input, taken from the CSR in its order: the key (source, r)
 // = csr_col[p] * R + r and, as the value, the destination with the in-degree
 // of its row, read from csr_ptr while the row is at hand (rows arrive in
@@ -1431,24 +1706,19 @@ __global__ void k_csr_slot(const int32_t* __restrict__ csr_col, const uint32_t* 
 // destinations fit in 24 bits.
 constexpr int64_t kPackedMaxNodes = (int64_t)1 << 24;
 
-int bits_for(int64_t nvals) {
-  int b = 0;
-  while (b < 32 && ((int64_t)1 << b) < nvals) ++b;
-  return b;
-}
-
 // Counts of the plan's tiles: 6 + R streams and the end of the scan.
 inline int64_t plan_counts(int64_t n, int64_t R) { return (6 + R) * cdiv(n > 0 ? n : 1, kPN) + 1; }
 
 // Workspace layout, shared by the sizing and the run.
 template <class A>
 struct BuildWs {
-  int32_t *cnt, *outdeg, *first, *key, *flag, *pos, *list, *iota, *hoff, *hist;
+  int32_t *cnt, *outdeg, *first, *key, *flag, *pos, *list, *iota, *hptr, *list_b, *list_l, *hist;
   uint8_t *sel, *digit;
   SelectState* st;
   int32_t *keep, *vsrc, *vdst, *veid, *alt1, *alt2, *alt3, *pcnt, *tcnt, *scratch;
   uint32_t* bcnt;
   uint64_t* sel_bits;
+  int2* parts;
   int4* gaps;
   int32_t* vw;                // weighted graphs: edge weights (float bits) of the kept edges in edge order
   int32_t *vsc, *vsc_alt;     // unpacked CSC sort: the scales (float bits) and their ping-pong buffer
@@ -1466,8 +1736,11 @@ struct BuildWs {
     pos = a.template take<int32_t>(N + 1);
     list = a.template take<int32_t>(N);
     iota = a.template take<int32_t>(N);
-    hoff = a.template take<int32_t>(hindex ? N + 1 : 0);
-    hist = a.template take<int32_t>(hindex ? E + N : 0);
+    hptr = a.template take<int32_t>(hindex ? N + 1 : 0);
+    list_b = a.template take<int32_t>(hindex ? hindex_list_b(E) : 0);
+    list_l = a.template take<int32_t>(hindex ? hindex_list_l(E) : 0);
+    parts = a.template take<int2>(hindex ? hindex_parts(E) : 0);
+    hist = a.template take<int32_t>(hindex ? hindex_hist_elems(E) : 0);
     sel = a.template take<uint8_t>(N);
     bbits = a.template take<uint32_t>(N / 32 + 2);
     mbits = a.template take<uint32_t>(2 * (N / 64 + 1));
@@ -1500,17 +1773,6 @@ struct BuildWs {
     scratch = a.template take<int32_t>(sc > rs ? sc : rs);
   }
 };
-
-int row_pointers(const uint32_t* keys, int64_t n, int64_t nq, int32_t* ptr, int4* gaps, int32_t* n_gaps,
-                 hipStream_t s) {
-  if (n <= 0) return fill_i32(ptr, 0, nq + 1, s);
-  HG_LAUNCH("build_row_ptr", k_row_ptr, dim3((unsigned)cdiv(n, kBT * kRpItems)), dim3(kBT), 0, s, keys, n, (int32_t)nq,
-            ptr, gaps, n_gaps);
-  const int64_t cap = gap_cap(nq), most = 4 * (int64_t)num_cus();
-  HG_LAUNCH("build_row_gaps", k_row_gaps, dim3((unsigned)(cap < most ? cap : most)), dim3(kBT), 0, s,
-            (const int4*)gaps, (const int32_t*)n_gaps, ptr);
-  return HG_OK;
-}
 
 struct PlanLayout {
   size_t s_off, soff_off, aslot_off, slotq_off, cslot_off, tab_off, items_off, heavy_off, fitems_off, fheavy_off,
@@ -1596,16 +1858,25 @@ static int validate_build(const hg_graph_desc* g, const hg_overlap_desc* o) {
 namespace {
 
 struct KeyWs {
-  int32_t *cnt, *outdeg, *first, *hoff, *hist, *flag, *scratch;
+  int32_t *cnt, *hptr, *list_b, *list_l, *hist, *v0, *v1, *scratch;
+  uint32_t *k0, *k1;
+  int2* parts;
+  int4* gaps;
   template <class A>
   void layout(A& a, int64_t N, int64_t E, bool hindex) {
     cnt = a.template take<int32_t>(C_COUNT + 8);
-    outdeg = a.template take<int32_t>(hindex ? N : 0);
-    first = a.template take<int32_t>(hindex ? N : 0);
-    hoff = a.template take<int32_t>(hindex ? N + 1 : 0);
-    hist = a.template take<int32_t>(hindex ? E + N : 0);
-    flag = a.template take<int32_t>(hindex ? N + 1 : 0);
-    scratch = a.template take<int32_t>(hindex ? scan_scratch_elems(N + 1) : 0);
+    if (!hindex) return;
+    hptr = a.template take<int32_t>(N + 1);
+    list_b = a.template take<int32_t>(hindex_list_b(E));
+    list_l = a.template take<int32_t>(hindex_list_l(E));
+    parts = a.template take<int2>(hindex_parts(E));
+    hist = a.template take<int32_t>(hindex_hist_elems(E));
+    k0 = a.template take<uint32_t>(E);
+    k1 = a.template take<uint32_t>(E);
+    v0 = a.template take<int32_t>(E);
+    v1 = a.template take<int32_t>(E);
+    gaps = a.template take<int4>(gap_cap(N));
+    scratch = a.template take<int32_t>(radix_scratch_elems(E));
   }
 };
 
@@ -1645,31 +1916,22 @@ extern "C" int hg_node_keys(const hg_graph_desc* g, int32_t key, int32_t* keys, 
   KeyWs w;
   w.layout(arena, N, E, hindex);
   if (!arena.ok()) return fail(HG_ERR_CAPACITY, "workspace layout overflow");
-  const unsigned gN = grid_for(N);
-  int32_t* deg = hindex ? w.outdeg : keys;
   HG_TRY(fill_i32(w.cnt, 0, C_COUNT + 8, s));
   HG_TRY(fill_i32(keys, 0, N, s));
-  if (hindex) HG_TRY(fill_i32(deg, 0, N, s));
-  if (E > 0)
+  if (E > 0 && hindex) {
+    HG_LAUNCH("keys_check", k_check_edges, dim3(grid_for(E)), dim3(kBT), 0, s, g->src, g->dst, g->rel, N, E, g->n_rel,
+              w.cnt);
+    const HindexBufs hb{w.k0, w.k1, w.v0, w.v1, w.hptr, w.list_b, w.list_l, w.hist, w.scratch,
+                        w.parts, w.gaps, w.cnt + C_GAP_HI, w.cnt + C_HI_BLOCK};
+    HG_TRY(hindex_keys(g->src, g->dst, N, E, nullptr, HG_THETA_NONE, keys, hb, w.cnt + C_ERR, s));
+  } else if (E > 0) {
     HG_LAUNCH("keys_outdeg", k_all_outdeg, dim3(agg_grid(E, kDegPerCu)), dim3(kAggBT), 0, s, g->src, g->dst, g->rel, N, E,
-              g->n_rel, deg, w.cnt);
+              g->n_rel, keys, w.cnt);
+  }
   int32_t herr = 0;
   HG_HIP_TRY(hipMemcpyAsync(&herr, w.cnt + C_ERR, sizeof(int32_t), hipMemcpyDeviceToHost, s));
   HG_HIP_TRY(hipStreamSynchronize(s));
   if (herr) return fail(HG_ERR_RANGE, "input ids out of range (flags 0x%x)", herr);
-  if (hindex && E > 0) {
-    // every node is treated as a candidate: first[v] = 0 < E
-    HG_TRY(fill_i32(w.first, 0, N, s));
-    HG_LAUNCH("keys_hindex_sizes", k_hindex_sizes, dim3(gN), dim3(kBT), 0, s, (const int32_t*)deg,
-              (const int32_t*)w.first, N, (int32_t)E, w.flag);
-    HG_TRY(fill_i32(w.flag + N, 0, 1, s));
-    HG_TRY(scan_exclusive_i32(w.flag, w.hoff, N + 1, nullptr, w.scratch, s));
-    HG_TRY(fill_i32(w.hist, 0, E + N, s));
-    HG_LAUNCH("keys_hindex_hist", k_hindex_hist, dim3(agg_grid(E)), dim3(kAggBT), 0, s, g->src, g->dst, E,
-              (const int32_t*)deg, (const int32_t*)w.first, (const int32_t*)w.hoff, w.hist, (const int32_t*)w.cnt);
-    HG_LAUNCH("keys_hindex_final", k_hindex_final, dim3(gN), dim3(kBT), 0, s, (const int32_t*)deg,
-              (const int32_t*)w.first, (const int32_t*)w.hoff, (const int32_t*)w.hist, N, (int32_t)E, keys);
-  }
   return HG_OK;
 }
 
@@ -1721,24 +1983,17 @@ extern "C" int hg_build_csr(const hg_graph_desc* g, const hg_overlap_desc* o, hg
             w.st);
   if (E > 0)
     HG_LAUNCH("build_edges_pass", k_edges_pass, dim3(agg_grid(E, kDegPerCu)), dim3(kAggBT), 0, s, g->src, g->dst,
-              g->rel, (const uint32_t*)w.bbits, N, E, (int32_t)R, (hindex && !o->node_key) ? 1 : 0,
-              (!hindex && !o->node_key) ? 1 : 0, o->budget_M, w.outdeg, w.first, w.cnt);
+              g->rel, (const uint32_t*)w.bbits, N, E, (int32_t)R, (!hindex && !o->node_key) ? 1 : 0,
+              o->budget_M, w.outdeg, w.first, w.cnt);
   // 2. keys: the caller's, when given (they do not depend on k); the h-index;
   // or the out-degrees of the nodes outside V_k (every candidate among them)
   const int32_t* key = o->node_key ? o->node_key : (hindex ? w.key : w.outdeg);
   if (hindex && !o->node_key) {
-    HG_LAUNCH("build_hindex_sizes", k_hindex_sizes, dim3(gN), dim3(kBT), 0, s,
-              (const int32_t*)w.outdeg, (const int32_t*)w.first, N, (int32_t)E, w.flag);
-    HG_TRY(fill_i32(w.flag + N, 0, 1, s));
-    HG_TRY(scan_exclusive_i32(w.flag, w.hoff, N + 1, nullptr, w.scratch, s));
-    HG_TRY(fill_i32(w.hist, 0, E + N, s));
-    if (E > 0)
-      HG_LAUNCH("build_hindex_hist", k_hindex_hist, dim3(agg_grid(E)), dim3(kAggBT), 0, s, g->src, g->dst, E,
-                (const int32_t*)w.outdeg, (const int32_t*)w.first, (const int32_t*)w.hoff, w.hist,
-                (const int32_t*)w.cnt);
-    HG_LAUNCH("build_hindex_final", k_hindex_final, dim3(gN), dim3(kBT), 0, s,
-              (const int32_t*)w.outdeg, (const int32_t*)w.first, (const int32_t*)w.hoff,
-              (const int32_t*)w.hist, N, (int32_t)E, w.key);
+    if (E > 0) {
+      const HindexBufs hb{w.kcsr, w.kalt, w.vsrc, w.alt1, w.hptr, w.list_b, w.list_l, w.hist, w.scratch,
+                          w.parts, w.gaps, w.cnt + C_GAP_HI, w.cnt + C_HI_BLOCK};
+      HG_TRY(hindex_keys(g->src, g->dst, N, E, w.first, o->theta, w.key, hb, w.cnt + C_ERR, s));
+    }
   }
   // 3, 4. filtered candidates and TopM
   const unsigned gS = (unsigned)std::min<int64_t>(cdiv(N, kSelBT * kSelItems), 2 * (int64_t)num_cus());
@@ -1856,7 +2111,7 @@ extern "C" int hg_build_csr(const hg_graph_desc* g, const hg_overlap_desc* o, hg
     if (want_eid && weighted && ES > 0)
       HG_LAUNCH("build_csr_w", k_gather_w, dim3(grid_for(ES)), dim3(kBT), 0, s, (const int32_t*)out->csr_eid,
                 g->edge_w, ES, out->csr_w);
-    HG_TRY(row_pointers(ko, ES, NQ, out->csr_ptr, w.gaps, w.cnt + C_GAP_CSR, s));
+    HG_TRY(row_pointers(ko, ES, NQ, out->csr_ptr, w.gaps, w.cnt + C_GAP_CSR, nullptr, s));
   }
   {
     // the CSC sort's input from the CSR in its order (the CSR keys stay
@@ -1878,7 +2133,7 @@ extern "C" int hg_build_csr(const hg_graph_desc* g, const hg_overlap_desc* o, hg
       HG_HIP_TRY(hipMemcpyAsync(out->csc_row, v1o, sizeof(int32_t) * ES, hipMemcpyDeviceToDevice, s));
       HG_HIP_TRY(hipMemcpyAsync(scale_bits, v2o, sizeof(int32_t) * ES, hipMemcpyDeviceToDevice, s));
     }
-    HG_TRY(row_pointers(ko, ES, NQ, out->csc_ptr, w.gaps, w.cnt + C_GAP_CSC, s));
+    HG_TRY(row_pointers(ko, ES, NQ, out->csc_ptr, w.gaps, w.cnt + C_GAP_CSC, nullptr, s));
   }
   // 8. plan: active-source lists and backward work items
   PlanLayout pl(N, E, R);

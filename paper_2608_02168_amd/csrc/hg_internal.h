@@ -153,13 +153,16 @@ struct SortUnpack {
 // from every other buffer) receive the values of the last pass directly, so
 // *v1_out == v1_final whenever at least one pass ran.  With unpack (no v2,
 // v1_final given) at least one pass runs and its last pass unpacks v1 as
-// SortUnpack states.  Scratch: radix_scratch_elems(n).
+// SortUnpack states.  With keys_in and v1_in the first pass reads those (which
+// stay as they are) and the buffers only hold the later passes.  Scratch:
+// radix_scratch_elems(n).
 int64_t radix_scratch_elems(int64_t n);
 int radix_sort_pairs(uint32_t* keys, uint32_t* keys_alt, int32_t* v1, int32_t* v1_alt,
                      int32_t* v2, int32_t* v2_alt, int64_t n, int bits,
                      int32_t* scratch, hipStream_t s, uint32_t** keys_out,
                      int32_t** v1_out, int32_t** v2_out, int32_t* v1_final = nullptr,
-                     int32_t* v2_final = nullptr, const SortUnpack* unpack = nullptr);
+                     int32_t* v2_final = nullptr, const SortUnpack* unpack = nullptr,
+                     const uint32_t* keys_in = nullptr, const int32_t* v1_in = nullptr);
 
 // Stable partition of n items into `nbins` (<= 256) buckets by a digit array
 // (uint8, 255 = drop).  Writes out[off[bin] + rank] = val[i] and bin_off[0..nbins]

@@ -425,7 +425,9 @@ int radix_pass(const uint32_t* ka, uint32_t* kb, const int32_t* a1, int32_t* b1,
 int radix_sort_pairs(uint32_t* keys, uint32_t* keys_alt, int32_t* v1, int32_t* v1_alt,
                      int32_t* v2, int32_t* v2_alt, int64_t n, int bits, int32_t* scratch,
                      hipStream_t s, uint32_t** keys_out, int32_t** v1_out, int32_t** v2_out,
-                     int32_t* v1_final, int32_t* v2_final, const SortUnpack* unpack) {
+                     int32_t* v1_final, int32_t* v2_final, const SortUnpack* unpack, const uint32_t* keys_in,
+                     const int32_t* v1_in) {
+  if (keys_in && bits < 1) bits = 1;  // at least one pass, which reads the input
   *keys_out = keys;
   *v1_out = v1;
   if (v2_out) *v2_out = v2;
@@ -452,10 +454,12 @@ int radix_sort_pairs(uint32_t* keys, uint32_t* keys_alt, int32_t* v1, int32_t* v
       if (v2_final && v2) b2 = v2_final;
     }
     const SortUnpack* up = (unpack && last) ? unpack : nullptr;
+    const uint32_t* kr = p == 0 && keys_in ? keys_in : ka;
+    const int32_t* r1 = p == 0 && keys_in ? v1_in : a1;
     if (nb > 8) {
-      HG_TRY(radix_pass<512>(ka, kb, a1, b1, a2, b2, n, shift, dmask, scratch, s, up));
+      HG_TRY(radix_pass<512>(kr, kb, r1, b1, a2, b2, n, shift, dmask, scratch, s, up));
     } else {
-      HG_TRY(radix_pass<256>(ka, kb, a1, b1, a2, b2, n, shift, dmask, scratch, s, up));
+      HG_TRY(radix_pass<256>(kr, kb, r1, b1, a2, b2, n, shift, dmask, scratch, s, up));
     }
     shift += nb;
     uint32_t* tk = ka; ka = kb; kb = tk;

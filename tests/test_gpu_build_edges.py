@@ -92,3 +92,55 @@ def test_selection_by_given_keys(kind, budget):
     assert sub.m_sel == ref.size
     got = sub.view("local2global")[sub.view("overlap").long()].sort().values.cpu().numpy()
     assert np.array_equal(got, ref)
+
+
+def _hindex_graph(name):
+    """Edges whose out-neighbour lists have the lengths where the h-index
+    changes its way: 16 / 17, 1024 / 1025, 16384 / 16385 neighbours, several
+    parts, and an h-index past 4096 (a dense core of 4500 nodes)."""
+    rng = np.random.default_rng(9)
+    n = 30_001
+    if name == "lengths":
+        lengths = [0, 1, 2, 15, 16, 17, 63, 64, 65, 1_023, 1_024, 1_025, 5_000, 16_384, 16_385, 40_000]
+        src = np.repeat(np.arange(len(lengths)) * 1_700 + 3, lengths)
+        src = np.concatenate([src, rng.integers(0, n, 90_000)])  # degrees of the neighbours
+        dst = rng.integers(0, n, src.size)
+    else:
+        core = 4_500
+        a = np.arange(core)
+        src = np.concatenate([np.repeat(a, core), rng.integers(0, n, 50_000)])
+        dst = np.concatenate([np.tile(a, core), rng.integers(0, n, 50_000)])
+    order = rng.permutation(src.size)
+    return n, src[order].astype(np.int32), dst[order].astype(np.int32)
+
+
+@pytest.mark.parametrize("name", ["lengths", "core"])
+def test_hindex_lengths(name):
+    n, src, dst = _hindex_graph(name)
+    rel = np.zeros(src.size, np.uint8)
+    ref = select.out_hindex(n, src, dst)
+    got = api.hg_node_keys(_dev(src), _dev(dst), _dev(rel), n, 1, api.HG_KEY_HINDEX).cpu().numpy()
+    assert np.array_equal(got, ref)
+    part = (np.arange(n) % 3 == 0).astype(np.int32)
+    cand = select.candidates(part, 1, src, dst)
+    ntype = np.zeros(n, np.uint8)
+    for theta, budget in ((2, 500), (select.THETA_NONE, 4_000)):
+        sub = api.hg_build_csr(_dev(src), _dev(dst), _dev(rel), _dev(ntype), _dev(part), 1, 1, 1, budget,
+                               key=api.HG_KEY_HINDEX, theta=theta, seed=5)
+        over = sub.view("local2global")[sub.view("overlap").long()].sort().values.cpu().numpy()
+        assert np.array_equal(over, select.top_m(cand, ref, theta, budget, 5))
+
+
+def test_hindex_range_error():
+    n = 5_000
+    src = np.arange(n, dtype=np.int32)
+    dst = np.arange(n, dtype=np.int32)[::-1].copy()
+    rel, z = np.zeros(n, np.uint8), np.zeros(n, np.uint8)
+    for bad in (-1, n, 2**31 - 1):
+        s = src.copy()
+        s[1_234] = bad
+        with pytest.raises(api.HgError):
+            api.hg_node_keys(_dev(s), _dev(dst), _dev(rel), n, 1, api.HG_KEY_HINDEX)
+        with pytest.raises(api.HgError):
+            api.hg_build_csr(_dev(s), _dev(dst), _dev(rel), _dev(z), _dev(z.astype(np.int32)), 0, 1, 1, 7,
+                             key=api.HG_KEY_HINDEX)
