@@ -219,6 +219,36 @@ __global__ void k_member_bits(const int32_t* __restrict__ part, int32_t k, const
   }
 }
 
+// Summary of the base bitmap by groups of 2^sum_shift nodes, at most kSumGroups
+// of them: sum[g / 32] bit g % 32 of x: some node of the group is in V_k, of y:
+// some node is not.  Both lookups of an edge go to the bitmap only for groups
+// that hold nodes of both kinds, else they end in the summary, which the edge
+// pass keeps in LDS (8 KB).  The pass was bound by the lookups' L2 requests, one
+// per endpoint (1.9 of its 2.7 ms at 200M edges, 211 G requests/s): with a base
+// set of contiguous ids, as the prefix sets of the workloads or a partition by
+// id ranges, nearly all of them go; with a random partition none do, and the
+// LDS reads cost nothing beside the requests.
+constexpr int kSumGroups = 1 << 15;
+inline int sum_shift(int64_t n) {
+  int s = 6;
+  while ((n - 1) >> s >= kSumGroups) ++s;
+  return s;
+}
+
+__global__ void __launch_bounds__(kBT) k_base_summary(const uint32_t* __restrict__ bits, int64_t n, int shift,
+                                                      uint2* __restrict__ sum) {
+  const int64_t g = (int64_t)blockIdx.x * kBT + threadIdx.x, v0 = g << shift;
+  bool in = false, out = false;
+  for (int64_t v = v0; v < n && v < v0 + ((int64_t)1 << shift); v += 32) {
+    const uint32_t m = bits[v >> 5], all = n - v < 32 ? (1u << (n - v)) - 1u : ~0u;
+    in |= (m & all) != 0;
+    out |= (m & all) != all;
+  }
+  const uint64_t mi = __ballot(in), mo = __ballot(out);
+  const int h = threadIdx.x & 63;
+  if (h < 2 && (g & ~63ll) + 32 * h < kSumGroups) sum[((g & ~63ll) >> 5) + h] = make_uint2((uint32_t)(mi >> (32 * h)), (uint32_t)(mo >> (32 * h)));
+}
+
 __device__ __forceinline__ bool bit_of(const uint32_t* __restrict__ bits, int32_t v) {
   return (bits[v >> 5] >> (v & 31)) & 1u;
 }
@@ -311,13 +341,16 @@ __global__ void __launch_bounds__(kAggBT) k_edges_pass(const int32_t* __restrict
                                                    const uint8_t* __restrict__ rel,
                                                    const uint32_t* __restrict__ base_bits, int64_t n_nodes,
                                                    int64_t n_edges, int32_t n_rel, int count_out,
-                                                   int64_t budget, int32_t* __restrict__ outdeg,
+                                                   int64_t budget, const uint2* __restrict__ sum, int shift,
+                                                   int32_t* __restrict__ outdeg,
                                                    int32_t* __restrict__ first, int32_t* __restrict__ cnt) {
+  __shared__ uint2 ls[kSumGroups / 32];
   __shared__ uint32_t lk[3][kAggSlots];
   __shared__ int32_t lv[3][kAggSlots];
   LdsAgg<false> deg{lk[0], lv[0]};
   LdsAgg<true> fs{lk[1], lv[1]}, fd{lk[2], lv[2]};
   const bool exact = dense_build(cnt[C_BASE], budget, n_nodes);
+  for (int i = threadIdx.x; i < (int)(((n_nodes - 1) >> shift) >> 5) + 1; i += kAggBT) ls[i] = sum[i];
   if (count_out) deg.init();
   if (exact) {
     fs.init();
@@ -342,12 +375,21 @@ __global__ void __launch_bounds__(kAggBT) k_edges_pass(const int32_t* __restrict
       dv[j] = dst[ec];
       rv[j] = rel[ec];
     }
+    // word 0 of the bitmap stands in where the summary answers (one line for
+    // the whole wave)
     uint32_t is[kEpItems], id[kEpItems];
+    bool gs[kEpItems], gd[kEpItems], mixs[kEpItems], mixd[kEpItems];
 #pragma unroll
     for (int j = 0; j < kEpItems; ++j) {
-      const bool in_range = sv[j] >= 0 && sv[j] < n_nodes && dv[j] >= 0 && dv[j] < n_nodes;
-      is[j] = in_range ? (uint32_t)sv[j] >> 5 : 0u;
-      id[j] = in_range ? (uint32_t)dv[j] >> 5 : 0u;
+      ok[j] = sv[j] >= 0 && sv[j] < n_nodes && dv[j] >= 0 && dv[j] < n_nodes;
+      const uint32_t a = ok[j] ? (uint32_t)sv[j] >> shift : 0u, b = ok[j] ? (uint32_t)dv[j] >> shift : 0u;
+      const uint2 wa = ls[a >> 5], wb = ls[b >> 5];
+      gs[j] = (wa.x >> (a & 31)) & 1u;
+      gd[j] = (wb.x >> (b & 31)) & 1u;
+      mixs[j] = gs[j] && ((wa.y >> (a & 31)) & 1u);
+      mixd[j] = gd[j] && ((wb.y >> (b & 31)) & 1u);
+      is[j] = ok[j] && mixs[j] ? (uint32_t)sv[j] >> 5 : 0u;
+      id[j] = ok[j] && mixd[j] ? (uint32_t)dv[j] >> 5 : 0u;
     }
 #pragma unroll
     for (int j = 0; j < kEpItems; ++j) {
@@ -357,11 +399,10 @@ __global__ void __launch_bounds__(kAggBT) k_edges_pass(const int32_t* __restrict
 #pragma unroll
     for (int j = 0; j < kEpItems; ++j) {
       const int64_t e = e0 + j * stride;
-      const bool in_range = sv[j] >= 0 && sv[j] < n_nodes && dv[j] >= 0 && dv[j] < n_nodes;
-      ok[j] = e < n_edges && in_range && rv[j] < (uint32_t)n_rel;
+      ok[j] = e < n_edges && ok[j] && rv[j] < (uint32_t)n_rel;
       if (e < n_edges && !ok[j]) atomicOr(&cnt[C_ERR], 1);
-      ps[j] = ok[j] && ((ws[j] >> (sv[j] & 31)) & 1u);
-      pd[j] = ok[j] && ((wd[j] >> (dv[j] & 31)) & 1u);
+      ps[j] = ok[j] && (mixs[j] ? (ws[j] >> (sv[j] & 31)) & 1u : gs[j]);
+      pd[j] = ok[j] && (mixd[j] ? (wd[j] >> (dv[j] & 31)) & 1u : gd[j]);
     }
 #pragma unroll
     for (int j = 0; j < kEpItems; ++j) {
@@ -1242,7 +1283,10 @@ constexpr int kETile = kBT * kERounds;
 // otherwise k_edge_emit compacts them.  In a sparse build also the base edge
 // of every selected node: the smallest index of an edge of the node set
 // joining it to V_k (atomic minimum; the selected nodes are few and of small
-// key).
+// key).  Bound by the lookups' L2 requests (147 G/s at 200M edges); the edges and
+// entries pass by with non-temporal loads and stores, which leaves the cache to
+// the table (2.79 to 2.73 ms at 200M edges, 0.18 to 0.15 ms at 20M); half the
+// table would give 2.36 ms.
 template <bool kTs, bool kW>
 __global__ void __launch_bounds__(kBT) k_edge_ids(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
                                                   const uint8_t* __restrict__ rel, int32_t n_rel,
@@ -1277,9 +1321,9 @@ __global__ void __launch_bounds__(kBT) k_edge_ids(const int32_t* __restrict__ sr
       const int64_t e = base + (int64_t)(j0 + u) * kBT + threadIdx.x;
       in[u] = e < n_edges;
       const int64_t ec = in[u] ? e : n_edges - 1;
-      sv[u] = src[ec];
-      dv[u] = dst[ec];
-      rv[u] = rel[ec];
+      sv[u] = __builtin_nontemporal_load(src + ec);
+      dv[u] = __builtin_nontemporal_load(dst + ec);
+      rv[u] = __builtin_nontemporal_load(rel + ec);
       wv[u] = kW ? __float_as_int(edge_w[ec]) : 0;
       late[u] = kTs ? ts[ec] > t_cut : false;
     }
@@ -1309,8 +1353,8 @@ __global__ void __launch_bounds__(kBT) k_edge_ids(const int32_t* __restrict__ sr
       }
       const bool keep = !late[u] && a[u] >= 0 && b >= 0;
       if (keep) {
-        kcsr[e] = (uint32_t)b * (uint32_t)n_rel + rv[u];
-        vsrc[e] = a[u];
+        __builtin_nontemporal_store((uint32_t)b * (uint32_t)n_rel + rv[u], kcsr + e);
+        __builtin_nontemporal_store(a[u], vsrc + e);
         if (veid) veid[e] = (int32_t)e;
         if (kW) vw[e] = wv[u];
       }
@@ -1719,6 +1763,7 @@ struct BuildWs {
   uint32_t* bcnt;
   uint64_t* sel_bits;
   int2* parts;
+  uint2* bsum;
   int4* gaps;
   int32_t* vw;                // weighted graphs: edge weights (float bits) of the kept edges in edge order
   int32_t *vsc, *vsc_alt;     // unpacked CSC sort: the scales (float bits) and their ping-pong buffer
@@ -1743,6 +1788,7 @@ struct BuildWs {
     hist = a.template take<int32_t>(hindex ? hindex_hist_elems(E) : 0);
     sel = a.template take<uint8_t>(N);
     bbits = a.template take<uint32_t>(N / 32 + 2);
+    bsum = a.template take<uint2>(kSumGroups / 32);
     mbits = a.template take<uint32_t>(2 * (N / 64 + 1));
     // rank groups: cdiv(N, 64) * 2 <= N / 32 + 2
     rt = a.template take<RankEnt>(N / kRankGroup + 2);
@@ -1981,10 +2027,13 @@ extern "C" int hg_build_csr(const hg_graph_desc* g, const hg_overlap_desc* o, hg
             (int32_t)E, w.bbits, w.first, w.outdeg, w.bcnt);
   HG_LAUNCH("build_init_counts", k_init_counts, dim3(1), dim3(256), 0, s, (const uint32_t*)w.bcnt, (int)gB, w.cnt,
             w.st);
+  const int sshift = sum_shift(N);
+  HG_LAUNCH("build_base_summary", k_base_summary, dim3((unsigned)cdiv(((N - 1) >> sshift) + 1, kBT)), dim3(kBT), 0, s,
+            (const uint32_t*)w.bbits, N, sshift, w.bsum);
   if (E > 0)
     HG_LAUNCH("build_edges_pass", k_edges_pass, dim3(agg_grid(E, kDegPerCu)), dim3(kAggBT), 0, s, g->src, g->dst,
               g->rel, (const uint32_t*)w.bbits, N, E, (int32_t)R, (!hindex && !o->node_key) ? 1 : 0,
-              o->budget_M, w.outdeg, w.first, w.cnt);
+              o->budget_M, (const uint2*)w.bsum, sshift, w.outdeg, w.first, w.cnt);
   // 2. keys: the caller's, when given (they do not depend on k); the h-index;
   // or the out-degrees of the nodes outside V_k (every candidate among them)
   const int32_t* key = o->node_key ? o->node_key : (hindex ? w.key : w.outdeg);
