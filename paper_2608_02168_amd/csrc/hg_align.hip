@@ -4,30 +4,28 @@
 // three passes over the two views X = H[overlap] and Y = H_ref:
 //
 //   (d1) k_align_stats: per-column float64 sums of x and x^2 of both views,
-//        one partial row set per chunk of rows;
-//   (d2) k_align_gram: every block first reduces (d1) in a fixed order, so
-//        all blocks hold the same mean, 1/sigma and standardisation scale;
-//        then over its chunk of rows the Gram matrices Xh^T Xh and Yh^T Yh
-//        on the split-fp16 MFMA (only the blocks on and above the diagonal)
-//        and, in float64, the column sums the gradient and the loss need:
+//        one partial row set per chunk of rows; k_align_mean: mean, 1/sigma
+//        and standardisation scale of every column from them;
+//   (d2) k_align_gram: over its chunk of rows a block forms the Gram matrices
+//        Xh^T Xh and Yh^T Yh on the split-fp16 MFMA (only the blocks on and
+//        above the diagonal) and, in float64, the column sums the gradient
+//        and the loss need:
 //          v = sum Xh, w = sum Yh, u = sum o (Xh - Yh),
 //          p = sum o (Xh - Yh) Xh, q = sum o (Yh - Xh) Yh, l = sum o (Xh - Yh)^2
-//        (o the row weight).  The last block of every group of 16 chunks
-//        sums the group's partials in chunk order, and the last group to
-//        finish sums the groups in order, mirrors the Grams, and writes
-//        C' = Xh^T Xh - I (and of Y), the loss and the two column vectors of
-//        the standardisation backward: with G = 2 o (Xh - Yh) + 4 lambda Xh C'
-//        and g' = G / sqrt(M),
+//        (o the row weight); k_align_reduce sums the chunks, mirrors the Grams
+//        and writes C' = Xh^T Xh - I (and of Y);
+//   (d3) the gradient row GEMM Xh C' on the split-fp16 MFMA.  Its blocks form
+//        the two column vectors of the standardisation backward from C' and
+//        the sums: with G = 2 o (Xh - Yh) + 4 lambda Xh C' and g' = G / sqrt(M),
 //          S1 = sum_b g'_b = (2 u + 4 lambda v C') / sqrt(M),
 //          S2 = sum_b g'_b xt_b = 2 p + 4 lambda diag(C C')
-//        (xt = (x - mu) / sigma = Xh sqrt(M)), so G never reaches memory;
-//   (d3) the gradient row GEMM Xh C' on the split-fp16 MFMA whose epilogue
-//        forms G, the standardisation backward
+//        (xt = (x - mu) / sigma = Xh sqrt(M)), so G never reaches memory; the
+//        first block writes the loss.  The epilogue forms G, the
+//        standardisation backward
 //          dX = (1/sigma) (g' - S1 / M - xt S2 / (M - ddof))
 //        and writes dH[overlap] = base + scale * dX (rows are distinct: no
 //        atomics); the same for Y into dH_ref when it is requested.
 //
-// The counters of (d2) are zeroed by (d1), which runs first on the stream.
 // Every reduction has a fixed order: results are bitwise reproducible.
 #include <mutex>
 
@@ -38,7 +36,6 @@ namespace hg {
 
 namespace {
 
-constexpr int kAlignGroup = 16;       // chunks per first-level group of (d2)
 constexpr int kStatChunksMax = 128;   // chunks per view of (d1)
 constexpr float kGramScale = 16384.f;                      // 2^14
 constexpr float kGramUnscale = 1.0f / (16384.f * 16384.f);  // 2^-28
@@ -51,17 +48,27 @@ template <int D>
 struct AShape {
   static constexpr int QN = D / 64;                  // 64-feature quadrants per side
   static constexpr int NQ = QN * (QN + 1) / 2;       // quadrants with qi <= qj
-  static constexpr int BPC = D == 256 ? 2 : 1;       // blocks per chunk (one view each at d = 256)
-  static constexpr int GW = 2 * NQ / BPC;            // Gram waves per block
-  static constexpr int SW = 2;                       // column-sum waves
-  static constexpr int kThreads = 64 * (GW + SW);
-  static constexpr int kChunkCap = D == 64 ? 512 : (D == 128 ? 256 : 128);
+  // a block takes both views, at d = 256 one (two blocks per chunk): a thread
+  // stages 4 rows x 4 columns of each view it holds
+  static constexpr int VB = D == 256 ? 1 : 2;
+  static constexpr int BPC = 2 / VB;
+  static constexpr int kThreads = 2 * D;
+  static constexpr int NW = kThreads / 64;
+  static constexpr int TASKS = 2 * VB * NQ;          // half quadrants (32 x 64) of a block
+  static constexpr int TPW = (TASKS + NW - 1) / NW;  // of a wave: 2, 3 and 3
+  // two blocks per compute unit (one at d = 256) within the static scratch
+  // of the no-allocation entry point
+  static constexpr int kChunkCap = D == 64 ? 512 : (D == 128 ? 448 : 128);
   static constexpr int kGramFloats = 2 * NQ * 64 * 64;  // one chunk's partial Grams, both views
+  static constexpr int kRedGram = kGramFloats / 64;     // blocks of the reduction: Gram elements,
+  static constexpr int kRedSums = 6 * D / 16;           // column sums
 };
 
 struct AlignPlan {
-  int64_t m, nch1, rpc1, nchg, rpc2, ngroups, grid2;
+  int64_t m, nch1, rpc1, nchg, rpc2, grid2;
 };
+
+constexpr int kGramStep = 32;  // rows of a step
 
 template <int D>
 AlignPlan align_plan(int64_t m) {
@@ -69,17 +76,16 @@ AlignPlan align_plan(int64_t m) {
   p.m = m;
   p.nch1 = m > 0 ? (cdiv(m, 512) < kStatChunksMax ? cdiv(m, 512) : kStatChunksMax) : 1;
   p.rpc1 = m > 0 ? cdiv(m, p.nch1) : 1;
-  int64_t n = m > 0 ? cdiv(m, 128) : 1;
+  int64_t n = m > 0 ? cdiv(m, 2 * kGramStep) : 1;
   n = n < AShape<D>::kChunkCap ? n : AShape<D>::kChunkCap;
-  p.rpc2 = cdiv(cdiv(m > 0 ? m : 1, n), 64) * 64;
+  p.rpc2 = cdiv(cdiv(m > 0 ? m : 1, n), kGramStep) * kGramStep;
   p.nchg = m > 0 ? cdiv(m, p.rpc2) : 1;
-  p.ngroups = cdiv(p.nchg, kAlignGroup);
   p.grid2 = AShape<D>::BPC == 1 ? p.nchg : 16 * cdiv(p.nchg, 8);
   return p;
 }
 
-// finals: C' of both views, then per view mu, 1/sigma, the standardisation
-// scale 1/(sigma sqrt(M)), S1 and S2 ([2][D] each)
+// finals: C' of both views, then per view mu, 1/sigma and the standardisation
+// scale 1/(sigma sqrt(M)) ([2][D] each)
 template <int D>
 struct AlignFin {
   float* base;
@@ -87,9 +93,7 @@ struct AlignFin {
   __host__ __device__ float* mu(int v) const { return base + 2 * D * D + v * D; }
   __host__ __device__ float* is(int v) const { return base + 2 * D * D + 2 * D + v * D; }
   __host__ __device__ float* sh(int v) const { return base + 2 * D * D + 4 * D + v * D; }
-  __host__ __device__ float* s1(int v) const { return base + 2 * D * D + 6 * D + v * D; }
-  __host__ __device__ float* s2(int v) const { return base + 2 * D * D + 8 * D + v * D; }
-  static constexpr int64_t kFloats = 2 * D * D + 10 * D;
+  static constexpr int64_t kFloats = 2 * D * D + 6 * D;
 };
 
 template <int D>
@@ -97,14 +101,16 @@ struct AlignWs {
   double* stat;   // [nch1][2 views][2][D]
   float* gpart;   // [nchg][2 views][NQ][64 x 64]
   double* spart;  // [nchg][6][D]
-  int32_t* cnt;   // [ngroups + 1]
+  double* sums;   // [6][D]
+  double* lpart;  // [kRedGram] parts of L_dec
   float* fin;     // AlignFin
   template <class A>
   void layout(A& a, const AlignPlan& p) {
     stat = a.template take<double>(p.nch1 * 4 * D);
     gpart = a.template take<float>(p.nchg * (int64_t)AShape<D>::kGramFloats);
     spart = a.template take<double>(p.nchg * 6 * D);
-    cnt = a.template take<int32_t>(p.ngroups + 1);
+    sums = a.template take<double>(6 * D);
+    lpart = a.template take<double>(AShape<D>::kRedGram);
     fin = a.template take<float>(AlignFin<D>::kFloats);
   }
 };
@@ -113,18 +119,16 @@ struct AlignWs {
 // grid (chunks, 2 views), 16 waves; a row is D/4 lanes reading 16 bytes
 // (columns c..c+3), four rows per lane in flight (their overlap entries first).
 // Lanes of one column are combined by xor shuffles inside the wave, then the
-// waves in order.  Block (0, 0) zeroes the counters of (d2).
+// waves in order.
 constexpr int kStatThreads = 1024;
 template <int D, class T>
 __global__ void __launch_bounds__(kStatThreads) k_align_stats(int64_t m, int64_t rpc, const T* __restrict__ H,
                                                               const int32_t* __restrict__ ov,
-                                                              const T* __restrict__ Href, double* __restrict__ stat,
-                                                              int32_t* __restrict__ cnt, int ncnt) {
+                                                              const T* __restrict__ Href, double* __restrict__ stat) {
   constexpr int TPR = D / 4, RPI = kStatThreads / TPR, U = 4, NW = kStatThreads / 64;
   __shared__ double red[NW][8][TPR < 64 ? TPR : 64];
   const int t = threadIdx.x;
   const int view = blockIdx.y;
-  if (blockIdx.x == 0 && view == 0 && t < ncnt) cnt[t] = 0;
   const int c = (t % TPR) * 4, ph = t / TPR;
   const int64_t b0 = (int64_t)blockIdx.x * rpc;
   const int64_t b1 = (b0 + rpc < m) ? b0 + rpc : m;
@@ -213,46 +217,72 @@ __device__ __forceinline__ void quad_of(int q, int& qi, int& qj) {
   }
 }
 
-// ---- (d2) Grams, column sums, last-block reductions, loss and finals -----------
-// The rows of a step (64 rows of both views, 32 at d = 256 in float32) are
-// staged in LDS: every thread
-// loads its share of step s + 1 from HBM while step s is multiplied, and all
-// waves read their operands from LDS (each row leaves HBM once).  LDS: two
-// step buffers [2 views][32][D] of the storage type, then the stat arrays;
-// the end-of-chunk arrays reuse the step buffers.
+// Mean, 1/sigma and scale of both views from the chunks' sums: 16 columns x 16
+// runs of chunks per block, each run in order, then the runs in order.
+template <int D>
+__global__ void __launch_bounds__(256) k_align_mean(int64_t m, int64_t nch1, int32_t ddof, float eps,
+                                                    const double* __restrict__ stat, float* __restrict__ finp) {
+  __shared__ double rs[16][16], rq[16][16];
+  const int e = threadIdx.x & 15, grp = threadIdx.x >> 4;
+  const int vc = blockIdx.x * 16 + e, v = vc / D, c = vc % D;
+  const int64_t per = (nch1 + 15) / 16;
+  double s = 0.0, q = 0.0;
+  for (int64_t k = grp * per; k < (grp + 1) * per && k < nch1; ++k) {
+    s += stat[(k * 2 + v) * 2 * D + c];
+    q += stat[(k * 2 + v) * 2 * D + D + c];
+  }
+  rs[grp][e] = s;
+  rq[grp][e] = q;
+  __syncthreads();
+  if (grp) return;
+  for (int g = 1; g < 16; ++g) {
+    s += rs[g][e];
+    q += rq[g][e];
+  }
+  const double mean = s / (double)m;
+  double var = (q - s * mean) / (double)(m - ddof);
+  var = var > 0.0 ? var : 0.0;
+  const float sig = sqrtf((float)var + eps);
+  const AlignFin<D> fin{finp};
+  fin.mu(v)[c] = (float)mean;
+  fin.is(v)[c] = 1.0f / sig;
+  fin.sh(v)[c] = 1.0f / (sig * sqrtf((float)m));
+}
+
+// ---- (d2) Grams and column sums ------------------------------------------------
+// A step is 32 rows of the block's views.  Thread (row quarter of 8, 4 columns)
+// loads 4 rows x 4 columns of each view, standardises them, adds its share of
+// the float64 column sums and writes the values' two fp16 parts into LDS in the
+// MFMA's order (8 rows of one feature per 16 bytes), once per element; the next
+// step's rows are loaded while the waves multiply, and two LDS buffers leave one
+// barrier per step.  A wave owns TPW half quadrants of the upper triangles, so a
+// step's products are spread evenly over the waves.  Feature f sits at f ^ ((f /
+// 16) mod 4), which spreads the staging stores over the banks.
+// With the rows parked as stored, every wave that used an element standardised
+// and split it again, two waves summed the columns (a serial float64 chain per
+// step) and each block reduced the statistics first: 184 us at 100k rows, d =
+// 128, of which the last-block reductions took about 50, and 526 us at 800k. Now
+// 41 and 238 us, with the statistics (6) and the reduction (12) as launches of
+// their own; d = 256 in bf16 at 800k rows 1610 -> 666 us.
 template <int D, class T>
 struct GramLds {
-  // steps of 64 rows up to 512-byte rows (128 KB of LDS at most), except at
-  // d = 256, whose ten Gram waves per view spill with two 32-row blocks per
-  // step (32-row steps: 1.6 against 3.3 ms per bf16 step)
-  static constexpr int kStepRows = (D * sizeof(T) <= 512 && D < 256) ? 64 : 32;
-  static constexpr int kStep = 2 * kStepRows * D;               // elements of one step buffer
-  static constexpr size_t kRows = 2 * (size_t)kStep * sizeof(T);  // both step buffers, bytes
-  static constexpr size_t kTail = sizeof(double) * (128 * 25 + 1024 + 6 * D);
-  static constexpr size_t kBytes = (kRows > kTail ? kRows : kTail);
+  static constexpr size_t kFrag = sizeof(uint4) * 2 * AShape<D>::VB * 4 * D;  // one buffer
+  static constexpr size_t kTail = sizeof(double) * AShape<D>::kThreads * 25;  // the column sums after the walk
+  static constexpr size_t kBytes = 2 * kFrag > kTail ? 2 * kFrag : kTail;
 };
 
 template <int D, class T>
-__global__ void __launch_bounds__(AShape<D>::kThreads) k_align_gram(
-    int64_t m, int64_t nch1, int64_t rpc, int64_t nchg, int32_t ddof, float eps, float lambda_n,
-    const T* __restrict__ H, const int32_t* __restrict__ ov, const T* __restrict__ Href, const float* __restrict__ w,
-    const double* __restrict__ stat, float* __restrict__ gpart, double* __restrict__ spart, int32_t* __restrict__ cnt,
-    float* __restrict__ finp, float* __restrict__ loss3) {
+__global__ void __launch_bounds__(AShape<D>::kThreads, 2) k_align_gram(
+    int64_t m, int64_t rpc, int64_t nchg, const T* __restrict__ H, const int32_t* __restrict__ ov,
+    const T* __restrict__ Href, const float* __restrict__ w, const float* __restrict__ finp,
+    float* __restrict__ gpart, double* __restrict__ spart) {
   typedef AShape<D> S;
-  typedef GramLds<D, T> LY;
-  constexpr int NT = S::kThreads, QN = S::QN, NQ = S::NQ, GW = S::GW;
-  constexpr int TPR = D / 4, RPS = 128 / TPR;  // column-sum waves: lanes per row, rows per sweep
-  constexpr int CPR = D * (int)sizeof(T) / 16;  // 16-byte chunks per row
-  constexpr int SR = LY::kStepRows;
-  constexpr int ITEMS = 2 * SR * CPR;           // chunks per step, both views
-  constexpr int PER = (ITEMS + NT - 1) / NT;    // chunks per thread and step
+  constexpr int NQ = S::NQ, QN = S::QN, VB = S::VB, TPW = S::TPW, C4 = D / 4;
+  constexpr bool kPad = S::TASKS != S::NW * TPW;
+  typedef typename Elt<T>::raw4_t Raw;
   extern __shared__ __align__(16) unsigned char lds[];
-  T* rows = reinterpret_cast<T*>(lds);  // [2 buffers][2 views][SR][D]
-  double* sred = reinterpret_cast<double*>(lds);           // [128][25]   (after the walk)
-  double* red = sred + 128 * 25;                           // [1024]
-  double* sums = red + 1024;                               // [6][D]
-  __shared__ float st_mu[2][D], st_sh[2][D], st_is[2][D];
-  __shared__ int s_last;
+  uint4* frag = reinterpret_cast<uint4*>(lds);  // [2 buffers][hi, lo][VB][4 K groups][D]
+  auto slot = [](int buf, int part, int v) { return ((buf * 2 + part) * VB + v) * 4 * D; };
   const int tid = threadIdx.x;
   int64_t chunk;
   int y;
@@ -264,337 +294,231 @@ __global__ void __launch_bounds__(AShape<D>::kThreads) k_align_gram(
     y = (blockIdx.x >> 3) & 1;
     chunk = (int64_t)(((blockIdx.x >> 4) << 3) | (blockIdx.x & 7));
   }
-  if (chunk >= nchg) return;  // padding block: no part in the counts
-  const AlignFin<D> fin{finp};
-  // mean, 1/sigma and scale of both views from the (d1) partials, fixed order
-  for (int e = tid; e < 2 * D; e += NT) {
-    const int v = e / D, c = e % D;
-    double s = 0.0, q = 0.0;
-#pragma unroll 16
-    for (int64_t k = 0; k < nch1; ++k) {
-      s += stat[(k * 2 + v) * 2 * D + c];
-      q += stat[(k * 2 + v) * 2 * D + D + c];
-    }
-    const double mean = s / (double)m;
-    double var = (q - s * mean) / (double)(m - ddof);
-    var = var > 0.0 ? var : 0.0;
-    const float sig = sqrtf((float)var + eps);
-    st_mu[v][c] = (float)mean;
-    st_is[v][c] = 1.0f / sig;
-    st_sh[v][c] = 1.0f / (sig * sqrtf((float)m));
-  }
-  const int64_t r_beg = chunk * rpc;
-  const int64_t r_end = (r_beg + rpc < m) ? r_beg + rpc : m;
-  // loader: chunk j of a step is (view, row, 16-byte piece); its HBM row id
-  // comes from the overlap list for view 0
-  auto row_id = [&](int64_t r0, int j) -> int64_t {
-    const int v = j / (SR * CPR), r = (j / CPR) % SR;
-    const int64_t rr = r0 + r;
-    if (rr >= r_end) return -1;
-    return v ? rr : (int64_t)ov[rr];
+  if (chunk >= nchg) return;  // a padding block
+  const int64_t r_beg = chunk * rpc, r_end = (r_beg + rpc < m) ? r_beg + rpc : m;
+  const AlignFin<D> fin{const_cast<float*>(finp)};
+  // staging role
+  const int rq = tid / C4, col = 4 * (tid % C4);  // rows 4 rq .. + 3 of a step
+  const bool useX = VB == 2 || y == 0, csum = y == 0;
+  // mean and scale of the thread's columns, read from LDS where they are used
+  __shared__ float k_st[4][D];  // mu, scale of X, then of Y
+  for (int e = tid; e < 4 * D; e += S::kThreads)
+    k_st[e / D][e % D] = (e / D) & 1 ? fin.sh(e / (2 * D))[e % D] : fin.mu(e / (2 * D))[e % D];
+  __syncthreads();
+  int32_t id[4];
+  Raw xr[4], yr[4];
+  float om[4];
+  // rows past the end are read from the last one and zeroed before use
+  auto row_at = [&](int64_t r0, int e) -> int64_t {
+    const int64_t r = r0 + 4 * rq + e;
+    return r < r_end ? r : r_end - 1;
   };
-  auto fetch = [&](int64_t r0, const int64_t (&id)[PER], uint4 (&x)[PER]) {
+  auto ids = [&](int64_t r0) {
 #pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      const int j = tid + k * NT;
-      x[k] = uint4{0u, 0u, 0u, 0u};
-      if (j < ITEMS && id[k] >= 0) {
-        const T* base = (j / (SR * CPR)) ? Href : H;
-        x[k] = *reinterpret_cast<const uint4*>(base + id[k] * D + (j % CPR) * (16 / (int)sizeof(T)));
+    for (int e = 0; e < 4; ++e) id[e] = VB == 2 || useX ? ov[row_at(r0, e)] : 0;
+  };
+  auto fetch = [&](int64_t r0) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (VB == 2 || useX) xr[e] = Elt<T>::raw4(H + (int64_t)id[e] * D + col);
+      yr[e] = Elt<T>::raw4(Href + row_at(r0, e) * D + col);
+      om[e] = w ? w[row_at(r0, e)] : 1.f;
+    }
+  };
+  double cs[6][4];
+#pragma unroll
+  for (int k = 0; k < 6; ++k)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) cs[k][q] = 0.0;
+  // fp16 parts of 4 rows of one column: pairs of words
+  auto put = [&](int buf, int v, int q, const float (&x)[4]) {
+    uint2 h, lo;
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const float a = x[2 * p] * kGramScale, b = x[2 * p + 1] * kGramScale;
+      const auto hp = __builtin_amdgcn_cvt_pkrtz(a, b);
+      const auto lp = __builtin_amdgcn_cvt_pkrtz(a - (float)hp[0], b - (float)hp[1]);
+      (p ? h.y : h.x) = __builtin_bit_cast(uint32_t, hp);
+      (p ? lo.y : lo.x) = __builtin_bit_cast(uint32_t, lp);
+    }
+    const int f = (rq >> 1) * D + col + (q ^ ((col >> 4) & 3));
+    reinterpret_cast<uint2*>(frag + slot(buf, 0, v) + f)[rq & 1] = h;
+    reinterpret_cast<uint2*>(frag + slot(buf, 1, v) + f)[rq & 1] = lo;
+  };
+  // one column at a time (the barriers and the constants in LDS keep the
+  // compiler from holding all four columns' values at once, which spilled 55
+  // registers at d = 128 and doubled the pass's time)
+  auto park = [&](int buf, int64_t r0) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float mx = k_st[0][col + q], sx = k_st[1][col + q], my = k_st[2][col + q], sy = k_st[3][col + q];
+      float xh[4], yh[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const bool ok = r0 + 4 * rq + e < r_end;
+        xh[e] = (VB == 2 || useX) && ok ? (Elt<T>::cook4(xr[e])[q] - mx) * sx : 0.f;
+        yh[e] = ok ? (Elt<T>::cook4(yr[e])[q] - my) * sy : 0.f;
       }
-    }
-  };
-  auto park = [&](int buf, const uint4 (&x)[PER]) {
+      if (VB == 2 || csum) {
 #pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      const int j = tid + k * NT;
-      if (j < ITEMS) reinterpret_cast<uint4*>(rows + (int64_t)buf * LY::kStep)[j] = x[k];
+        for (int e = 0; e < 4; ++e) {
+          const double xv = (double)xh[e], yv = (double)yh[e], dl = xv - yv, od = (double)om[e] * dl;
+          cs[0][q] += xv;
+          cs[1][q] += yv;
+          cs[2][q] += od;
+          cs[3][q] += od * xv;
+          cs[4][q] -= od * yv;
+          cs[5][q] += od * dl;
+        }
+      }
+      if constexpr (VB == 2) {
+        put(buf, 0, q, xh);
+        put(buf, 1, q, yh);
+      } else {
+        if (y == 0) put(buf, 0, q, xh); else put(buf, 0, q, yh);
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
   };
-  auto ids = [&](int64_t r0, int64_t (&id)[PER]) {
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      const int j = tid + k * NT;
-      id[k] = (j < ITEMS && r0 < r_end) ? row_id(r0, j) : -1;
-    }
-  };
-  const int wv = tid >> 6, l = lane64();
+  // the wave's tasks, in scalar registers
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), l = lane64();
   const int g = l >> 4, c = l & 15;
-  // Gram wave
-  const int tile = y * GW + wv;
-  const int gview = tile / NQ, gq = tile % NQ;
-  int qi, qj;
-  quad_of<QN>(gq, qi, qj);
-  const bool gram = wv < GW, diag = qi == qj;
-  const int ca = 64 * qi + 4 * c, cb = 64 * qj + 4 * c;
-  // column-sum waves (block y = 0 only)
-  const bool csum = !gram && y == 0;
-  const int sl = tid - 64 * GW;  // 0..127 on the column-sum waves
-  const int scol = (sl % TPR) * 4, soff = sl / TPR;
-  int64_t idn[PER];
-  uint4 xr[PER];
-  ids(r_beg, idn);
-  fetch(r_beg, idn, xr);
-  ids(r_beg + SR, idn);
-  park(0, xr);
-  __syncthreads();  // stats and step 0 in LDS
-  // every wave walks the chunk's steps with the same loads, parks and
-  // barriers; body(sv, r0) works on step r0 staged at sv ([2 views][SR][D])
-  auto walk = [&](auto&& body) {
-    int buf = 0;
-    for (int64_t r0 = r_beg; r0 < r_end; r0 += SR, buf ^= 1) {
-      const bool more = r0 + SR < r_end;
-      if (more) fetch(r0 + SR, idn, xr);  // step s + 1 in flight while step s is used
-      if (more) ids(r0 + 2 * SR, idn);
-      body((const T*)(rows + (int64_t)buf * LY::kStep), r0);
-      if (more) park(buf ^ 1, xr);
-      __syncthreads();
+  f32x4 acc[TPW][2][4];
+  int tv[TPW], tq[TPW], fa[TPW], fb[TPW];  // view slot, quadrant, first feature of the two sides
+#pragma unroll
+  for (int t = 0; t < TPW; ++t) {
+    const int tk = wv * TPW + t;
+    tv[t] = tk < S::TASKS ? tk / (2 * NQ) : -1;
+    tq[t] = (tk >> 1) % NQ;
+    int qi, qj;
+    quad_of<QN>(tq[t], qi, qj);
+    fa[t] = 64 * qi + 32 * (tk & 1);
+    fb[t] = 64 * qj;
+#pragma unroll
+    for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+      for (int bj = 0; bj < 4; ++bj) acc[t][bi][bj] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  ids(r_beg);
+  fetch(r_beg);
+  ids(r_beg + kGramStep);
+  int buf = 0;
+  for (int64_t r0 = r_beg; r0 < r_end; r0 += kGramStep, buf ^= 1) {
+    park(buf, r0);
+    lds_barrier();
+    if (r0 + kGramStep < r_end) {
+      fetch(r0 + kGramStep);
+      ids(r0 + 2 * kGramStep);
     }
-  };
-  if (gram) {
-    f32x4 acc[4][4];
 #pragma unroll
-    for (int bi = 0; bi < 4; ++bi)
+    for (int t = 0; t < TPW; ++t) {
+      if (kPad && tv[t] < 0) continue;
+      uint4 ha[2], la[2];
 #pragma unroll
-      for (int bj = 0; bj < 4; ++bj) acc[bi][bj] = f32x4{0.f, 0.f, 0.f, 0.f};
-    walk([&](const T* sv, int64_t r0) {
-      const T* src = sv + gview * SR * D;
-      // operand rows: 8 rows x 4 columns per lane, standardised and scaled by 2^14
-      auto rows8 = [&](int kb, int col, f32x4 (&x)[8]) {
-        f32x4 mu4, sc4;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          mu4[k] = st_mu[gview][col + k];
-          sc4[k] = st_sh[gview][col + k] * kGramScale;
-        }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const int r = 32 * kb + 8 * g + e;
-          const f32x4 v = Elt<T>::load4(src + r * D + col);
-          x[e] = (r0 + r < r_end) ? (v - mu4) * sc4 : f32x4{0.f, 0.f, 0.f, 0.f};
-        }
-      };
-      for (int kb = 0; kb < SR / 32; ++kb) {
-        uint4 hb[4], lb[4];
-        {
-          f32x4 xb[8];
-          rows8(kb, cb, xb);
-#pragma unroll
-          for (int bj = 0; bj < 4; ++bj) {
-            float v[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = xb[e][bj];
-            split8(v, hb[bj], lb[bj]);
-          }
-        }
-        if (diag) {
-#pragma unroll
-          for (int bi = 0; bi < 4; ++bi)
-#pragma unroll
-            for (int bj = 0; bj < 4; ++bj) {
-              acc[bi][bj] = mfma_f16(hb[bi], hb[bj], acc[bi][bj]);
-              acc[bi][bj] = mfma_f16(hb[bi], lb[bj], acc[bi][bj]);
-              acc[bi][bj] = mfma_f16(lb[bi], hb[bj], acc[bi][bj]);
-            }
-        } else {
-          f32x4 xa[8];
-          rows8(kb, ca, xa);
-#pragma unroll
-          for (int bi = 0; bi < 4; ++bi) {
-            uint4 ha, la;
-            float v[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = xa[e][bi];
-            split8(v, ha, la);
-#pragma unroll
-            for (int bj = 0; bj < 4; ++bj) {
-              acc[bi][bj] = mfma_f16(ha, hb[bj], acc[bi][bj]);
-              acc[bi][bj] = mfma_f16(ha, lb[bj], acc[bi][bj]);
-              acc[bi][bj] = mfma_f16(la, hb[bj], acc[bi][bj]);
-            }
-          }
-        }
-      }
-    });
-    // partial Grams of this chunk: lane (c, g), register v of block (bi, bj)
-    // is element [4 (4 g + v) + bi][4 c + bj] of the quadrant
-    float* out = gpart + (chunk * (int64_t)S::kGramFloats) + (int64_t)(gview * NQ + gq) * 4096;
-#pragma unroll
-    for (int bi = 0; bi < 4; ++bi)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        f32x4 row4;
-#pragma unroll
-        for (int bj = 0; bj < 4; ++bj) row4[bj] = acc[bi][bj][v] * kGramUnscale;
-        *reinterpret_cast<f32x4*>(out + (4 * (4 * g + v) + bi) * 64 + 4 * c) = row4;
-      }
-  } else {
-    double cs[6][4];
-#pragma unroll
-    for (int k = 0; k < 6; ++k)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) cs[k][q] = 0.0;
-    walk([&](const T* sv, int64_t r0) {
-      if (!csum) return;
-      f32x4 smx, ssx, smy, ssy;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        smx[k] = st_mu[0][scol + k];
-        ssx[k] = st_sh[0][scol + k];
-        smy[k] = st_mu[1][scol + k];
-        ssy[k] = st_sh[1][scol + k];
+      for (int bi = 0; bi < 2; ++bi) {
+        // (f / 16) mod 4 of the feature: 2 (half) + bi on this side, bj on the other
+        const int f = fa[t] + 16 * bi + (c ^ (((fa[t] >> 4) & 2) + bi));
+        ha[bi] = frag[slot(buf, 0, tv[t]) + g * D + f];
+        la[bi] = frag[slot(buf, 1, tv[t]) + g * D + f];
       }
 #pragma unroll
-      for (int k = 0; k < SR / RPS; ++k) {
-        const int r = soff + k * RPS;
-        const int64_t rg = r0 + r;
-        if (rg < r_end) {
-          const f32x4 xh = (Elt<T>::load4(sv + r * D + scol) - smx) * ssx;
-          const f32x4 yh = (Elt<T>::load4(sv + SR * D + r * D + scol) - smy) * ssy;
-          const double om = w ? (double)w[rg] : 1.0;
+      for (int bj = 0; bj < 4; ++bj) {
+        const int f = fb[t] + 16 * bj + (c ^ bj);
+        const uint4 hb = frag[slot(buf, 0, tv[t]) + g * D + f];
+        const uint4 lb = frag[slot(buf, 1, tv[t]) + g * D + f];
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const double xv = (double)xh[q], yv = (double)yh[q], dl = xv - yv, od = om * dl;
-            cs[0][q] += xv;
-            cs[1][q] += yv;
-            cs[2][q] += od;
-            cs[3][q] += od * xv;
-            cs[4][q] -= od * yv;
-            cs[5][q] += od * dl;
-          }
+        for (int bi = 0; bi < 2; ++bi) {
+          acc[t][bi][bj] = mfma_f16(ha[bi], hb, acc[t][bi][bj]);
+          acc[t][bi][bj] = mfma_f16(ha[bi], lb, acc[t][bi][bj]);
+          acc[t][bi][bj] = mfma_f16(la[bi], hb, acc[t][bi][bj]);
         }
       }
-    });
-    if (csum) {
-#pragma unroll
-      for (int k = 0; k < 6; ++k)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) sred[sl * 25 + 4 * k + q] = cs[k][q];
+      __builtin_amdgcn_sched_barrier(0);  // one task's fragments at a time
     }
   }
-  __syncthreads();
-  if (y == 0 && tid < TPR) {
-    double* out = spart + chunk * 6 * D;
+  // partial Grams of this chunk: register v of block (bi, bj) is element
+  // [16 bi + 4 g + v][16 bj + c] of the half quadrant
 #pragma unroll
-    for (int k = 0; k < 6; ++k)
+  for (int t = 0; t < TPW; ++t) {
+    if (kPad && tv[t] < 0) continue;
+    const int view = VB == 2 ? tv[t] : y;
+    float* out = gpart + chunk * (int64_t)S::kGramFloats + (int64_t)(view * NQ + tq[t]) * 4096 + (fa[t] & 32) * 64;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        double s = 0.0;
-        for (int p = 0; p < RPS; ++p) s += sred[(p * TPR + tid) * 25 + 4 * k + q];
-        out[k * D + 4 * tid + q] = s;
-      }
+    for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int bj = 0; bj < 4; ++bj)
+          out[(16 * bi + 4 * g + v) * 64 + 16 * bj + c] = acc[t][bi][bj][v] * kGramUnscale;
   }
-  // ---- first level: the last block of the group sums its chunks in order ----
-  __threadfence();
-  __syncthreads();
-  const int64_t grp = chunk / kAlignGroup;
-  const int64_t c0 = grp * kAlignGroup, c1 = (c0 + kAlignGroup < nchg) ? c0 + kAlignGroup : nchg;
-  if (tid == 0) s_last = atomicAdd(&cnt[grp], 1) == S::BPC * (int)(c1 - c0) - 1;
-  __syncthreads();
-  if (!s_last) return;
-  __threadfence();
-  // all chunk loads of an element are issued before the in-order sum
-  for (int e4 = tid; e4 < S::kGramFloats / 4; e4 += NT) {
-    f32x4 v[kAlignGroup];
+  if (!csum) return;  // the whole block
+  __syncthreads();    // the last step's fragments have been read
+  double* sred = reinterpret_cast<double*>(lds);  // [threads][25]
 #pragma unroll
-    for (int k = 0; k < kAlignGroup; ++k)
-      v[k] = c0 + k < c1 ? *reinterpret_cast<const f32x4*>(gpart + (c0 + k) * S::kGramFloats + 4 * e4)
-                         : f32x4{0.f, 0.f, 0.f, 0.f};
-    f32x4 sum = v[0];
+  for (int k = 0; k < 6; ++k)
 #pragma unroll
-    for (int k = 1; k < kAlignGroup; ++k) sum += v[k];
-    *reinterpret_cast<f32x4*>(gpart + c0 * S::kGramFloats + 4 * e4) = sum;
+    for (int q = 0; q < 4; ++q) sred[tid * 25 + 4 * k + q] = cs[k][q];
+  __syncthreads();
+  for (int e = tid; e < 6 * D; e += S::kThreads) {
+    const int k = e / D, cc = e % D;
+    double t = 0.0;
+#pragma unroll
+    for (int p = 0; p < 8; ++p) t += sred[(p * C4 + cc / 4) * 25 + 4 * k + cc % 4];
+    spart[chunk * 6 * D + e] = t;
   }
-  for (int e = tid; e < 6 * D; e += NT) {
-    double v[kAlignGroup];
-#pragma unroll
-    for (int k = 0; k < kAlignGroup; ++k) v[k] = c0 + k < c1 ? spart[(c0 + k) * 6 * D + e] : 0.0;
-    double sum = v[0];
-#pragma unroll
-    for (int k = 1; k < kAlignGroup; ++k) sum += v[k];
-    spart[c0 * 6 * D + e] = sum;
+}
+
+// Reduction of the chunks: 16 elements (4 floats each, or one double) x 16 runs
+// of chunks per block, each run in order, then the runs in order.  Blocks below
+// kRedGram form C' = sum - I (both triangles) and their part of L_dec, the rest
+// the column sums.
+template <int D>
+__global__ void __launch_bounds__(256) k_align_reduce(int64_t nchg, const float* __restrict__ gpart,
+                                                      const double* __restrict__ spart, double* __restrict__ sums,
+                                                      double* __restrict__ lpart, float* __restrict__ finp) {
+  typedef AShape<D> S;
+  __shared__ f32x4 rf[16][16];
+  __shared__ double rd[16][16];
+  const int e = threadIdx.x & 15, grp = threadIdx.x >> 4;
+  const int64_t per = (nchg + 15) / 16, c0 = grp * per, c1 = c0 + per < nchg ? c0 + per : nchg;
+  if ((int)blockIdx.x >= S::kRedGram) {
+    const int el = (blockIdx.x - S::kRedGram) * 16 + e;
+    double t = 0.0;
+#pragma unroll 8
+    for (int64_t k = c0; k < c1; ++k) t += spart[k * 6 * D + el];
+    rd[grp][e] = t;
+    __syncthreads();
+    if (grp) return;
+    for (int g = 1; g < 16; ++g) t += rd[g][e];
+    sums[el] = t;
+    return;
   }
-  __threadfence();
+  const int e4 = blockIdx.x * 16 + e;
+  f32x4 t = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+  for (int64_t k = c0; k < c1; ++k) t += *reinterpret_cast<const f32x4*>(gpart + k * S::kGramFloats + 4 * e4);
+  rf[grp][e] = t;
   __syncthreads();
-  const int64_t ngroups = (nchg + kAlignGroup - 1) / kAlignGroup;
-  if (tid == 0) s_last = atomicAdd(&cnt[ngroups], 1) == (int)ngroups - 1;
-  __syncthreads();
-  if (!s_last) return;
-  __threadfence();
-  // ---- second level (one block): groups in order, then the finals ----------
-  constexpr int kMaxGroups = (S::kChunkCap + kAlignGroup - 1) / kAlignGroup;
+  if (grp) return;
+  for (int g = 1; g < 16; ++g) t += rf[g][e];
+  const AlignFin<D> fin{finp};
+  const int el = 4 * e4;
+  const int vw = el / (S::NQ * 4096), q = (el / 4096) % S::NQ, i = (el % 4096) / 64, j0 = el % 64;
+  int a, b;
+  quad_of<S::QN>(q, a, b);
+  const int gi = 64 * a + i;
   double ldec = 0.0;
-  for (int e4 = tid; e4 < S::kGramFloats / 4; e4 += NT) {
-    f32x4 v[kMaxGroups];
 #pragma unroll
-    for (int k = 0; k < kMaxGroups; ++k)
-      v[k] = k < ngroups ? *reinterpret_cast<const f32x4*>(gpart + (int64_t)k * kAlignGroup * S::kGramFloats + 4 * e4)
-                         : f32x4{0.f, 0.f, 0.f, 0.f};
-    f32x4 sum = v[0];
-#pragma unroll
-    for (int k = 1; k < kMaxGroups; ++k) sum += v[k];
-    const int e = 4 * e4;
-    const int vw = e / (NQ * 4096), q = (e / 4096) % NQ, i = (e % 4096) / 64, j0 = e % 64;
-    int a, b;
-    quad_of<QN>(q, a, b);
-    const int gi = 64 * a + i;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int gj = 64 * b + j0 + k;
-      const float cp = sum[k] - (gi == gj ? 1.f : 0.f);
-      fin.cp(vw)[gi * D + gj] = cp;
-      if (a != b) fin.cp(vw)[gj * D + gi] = cp;
-      ldec += (a != b ? 2.0 : 1.0) * (double)cp * (double)cp;
-    }
+  for (int k = 0; k < 4; ++k) {
+    const int gj = 64 * b + j0 + k;
+    const float cp = t[k] - (gi == gj ? 1.f : 0.f);
+    fin.cp(vw)[gi * D + gj] = cp;
+    if (a != b) fin.cp(vw)[gj * D + gi] = cp;
+    ldec += (a != b ? 2.0 : 1.0) * (double)cp * (double)cp;
   }
-  for (int e = tid; e < 6 * D; e += NT) {
-    double v[kMaxGroups];
 #pragma unroll
-    for (int k = 0; k < kMaxGroups; ++k) v[k] = k < ngroups ? spart[(int64_t)k * kAlignGroup * 6 * D + e] : 0.0;
-    double sum = v[0];
-#pragma unroll
-    for (int k = 1; k < kMaxGroups; ++k) sum += v[k];
-    sums[e] = sum;
-  }
-  for (int e = tid; e < 2 * D; e += NT) {
-    const int v = e / D, cc = e % D;
-    fin.mu(v)[cc] = st_mu[v][cc];
-    fin.is(v)[cc] = st_is[v][cc];
-    fin.sh(v)[cc] = st_sh[v][cc];
-  }
-  __threadfence();
-  __syncthreads();
-  const double L_dec = block_sum_d<NT>(ldec, red);
-  double linv = 0.0;
-  for (int cc = tid; cc < D; cc += NT) linv += sums[5 * D + cc];
-  const double L_inv = block_sum_d<NT>(linv, red);
-  const double inv_sqrt_m = 1.0 / sqrt((double)m);
-  for (int e = tid; e < 2 * D; e += NT) {
-    const int v = e / D, cc = e % D;
-    const float* P = fin.cp(v);
-    // column cc of C' (read by consecutive threads: coalesced), 16 loads in
-    // flight; C' is symmetric, so (C' C')_cc is the column's sum of squares
-    double t1 = 0.0, t2 = 0.0;
-    for (int k0 = 0; k0 < D; k0 += 16) {
-      float pk[16];
-#pragma unroll
-      for (int k = 0; k < 16; ++k) pk[k] = P[(k0 + k) * D + cc];
-#pragma unroll
-      for (int k = 0; k < 16; ++k) {
-        t1 += sums[v * D + k0 + k] * (double)pk[k];  // v C' (view X) or w C' (view Y)
-        t2 += (double)pk[k] * (double)pk[k];
-      }
-    }
-    const double u = v == 0 ? sums[2 * D + cc] : -sums[2 * D + cc];
-    const double pq = v == 0 ? sums[3 * D + cc] : sums[4 * D + cc];
-    fin.s1(v)[cc] = (float)((2.0 * u + 4.0 * (double)lambda_n * t1) * inv_sqrt_m);
-    fin.s2(v)[cc] = (float)(2.0 * pq + 4.0 * (double)lambda_n * (t2 + (double)P[cc * D + cc]));
-  }
-  if (tid == 0) {
-    loss3[0] = (float)L_inv;
-    loss3[1] = (float)L_dec;
-    loss3[2] = (float)(L_inv + (double)lambda_n * L_dec);
-  }
+  for (int o = 8; o > 0; o >>= 1) ldec += __shfl_xor(ldec, o, 64);
+  if (e == 0) lpart[blockIdx.x] = ldec;
 }
 
 // ---- (d3) the gradient pass ---------------------------------------------------
@@ -615,7 +539,10 @@ __global__ void __launch_bounds__(kGemmThreads) k_align_grad(int64_t m, const T*
                                                              const T* __restrict__ other, RowMap omap,
                                                              const float* __restrict__ finp, int view,
                                                              const float* __restrict__ w, const T* base, T* out,
-                                                             float scale, float lambda_n, int32_t ddof) {
+                                                             float scale, float lambda_n, int32_t ddof,
+                                                             const double* __restrict__ sums,
+                                                             const double* __restrict__ lpart,
+                                                             float* __restrict__ loss3) {
   constexpr int DN = F32Slice<D>::DN;
   constexpr int KB = D / 16, KB2 = D / 32, NB = DN / 16;
   constexpr int kWaves = kGemmThreads / 64;
@@ -629,17 +556,58 @@ __global__ void __launch_bounds__(kGemmThreads) k_align_grad(int64_t m, const T*
   const int tid = threadIdx.x;
   const int col0 = DN * blockIdx.y;
   {
+    // S1 and S2 of every column: a column of C' by kPer threads (C' is
+    // symmetric, so (C' C')_cc is the column's sum of squares)
+    constexpr int kPer = kGemmThreads / D, kRows = D / kPer;
+    __shared__ double r1[kPer][D], r2[kPer][D];
+    {
+      const int c = tid % D, part = tid / D;
+      double t1 = 0.0, t2 = 0.0;
+#pragma unroll 16
+      for (int k = part * kRows; k < (part + 1) * kRows; ++k) {
+        const double pk = (double)W[(int64_t)k * D + c];
+        t1 += sums[view * D + k] * pk;  // v C' (view X) or w C' (view Y)
+        t2 += pk * pk;
+      }
+      r1[part][c] = t1;
+      r2[part][c] = t2;
+    }
+    __syncthreads();
     const float rs = 1.0f / sqrtf((float)m);
+    const double inv_sqrt_m = 1.0 / sqrt((double)m);
     for (int c = tid; c < D; c += kGemmThreads) {
+      double t1 = 0.0, t2 = 0.0;
+#pragma unroll
+      for (int p = 0; p < kPer; ++p) {
+        t1 += r1[p][c];
+        t2 += r2[p][c];
+      }
+      const double u = view == 0 ? sums[2 * D + c] : -sums[2 * D + c];
+      const double pq = view == 0 ? sums[3 * D + c] : sums[4 * D + c];
+      const float S1 = (float)((2.0 * u + 4.0 * (double)lambda_n * t1) * inv_sqrt_m);
+      const float S2 = (float)(2.0 * pq + 4.0 * (double)lambda_n * (t2 + (double)W[(int64_t)c * D + c]));
       const float isg = fin.is(view)[c];
       k_mu[c] = fin.mu(view)[c];
       k_sh[c] = fin.sh(view)[c];
       k_muo[c] = fin.mu(1 - view)[c];
       k_sho[c] = fin.sh(1 - view)[c];
       k_x[c] = scale * isg * 2.0f * rs;
-      k_c[c] = scale * isg * fin.s1(view)[c] / (float)m;
-      k_e[c] = scale * isg * isg * fin.s2(view)[c] / (float)(m - ddof);
+      k_c[c] = scale * isg * S1 / (float)m;
+      k_e[c] = scale * isg * isg * S2 / (float)(m - ddof);
       k_a[c] = scale * isg * 4.0f * lambda_n * rs;
+    }
+    if (loss3 && blockIdx.x == 0 && blockIdx.y == 0) {  // the losses (the whole block)
+      double* lred = &r1[0][0];  // kPer * D = kGemmThreads words, read above
+      __syncthreads();
+      double ld = 0.0, li = 0.0;
+      for (int e = tid; e < AShape<D>::kRedGram; e += kGemmThreads) ld += lpart[e];
+      for (int e = tid; e < D; e += kGemmThreads) li += sums[5 * D + e];
+      const double L_dec = block_sum_d<kGemmThreads>(ld, lred), L_inv = block_sum_d<kGemmThreads>(li, lred);
+      if (tid == 0) {
+        loss3[0] = (float)L_inv;
+        loss3[1] = (float)L_dec;
+        loss3[2] = (float)(L_inv + (double)lambda_n * L_dec);
+      }
     }
     float mx = 0.f;
     for (int e = tid; e < D * D / 4; e += kGemmThreads) {
@@ -778,7 +746,7 @@ __global__ void __launch_bounds__(kGemmThreads) k_align_grad(int64_t m, const T*
 template <int D, class T>
 int launch_align_grad(int64_t m, const T* self, RowMap smap, const T* other, RowMap omap, const float* fin,
                       int view, const float* w, const T* base, T* out, float scale, float lambda_n, int32_t ddof,
-                      hipStream_t s) {
+                      const double* sums, const double* lpart, float* loss3, hipStream_t s) {
   constexpr int DN = F32Slice<D>::DN;
   const int64_t tiles = cdiv(m, 16 * (kGemmThreads / 64));
   const int64_t cap = (int64_t)num_cus() * (D > 128 ? 1 : 2);
@@ -794,7 +762,7 @@ int launch_align_grad(int64_t m, const T* self, RowMap smap, const T* other, Row
     }
   }
   HG_LAUNCH("align_grad", kern, dim3((unsigned)grid, D / DN), dim3(kGemmThreads), lds, s, m, self, smap, other,
-            omap, fin, view, w, base, out, scale, lambda_n, ddof);
+            omap, fin, view, w, base, out, scale, lambda_n, ddof, sums, lpart, loss3);
   return HG_OK;
 }
 
@@ -809,7 +777,9 @@ int align_impl(int64_t m, const T* H, const int32_t* overlap, const T* Href, con
   if (!a.ok()) return fail(HG_ERR_CAPACITY, "alignment workspace needs %zu bytes, got %zu", a.used, ws_bytes);
   // (d1)
   HG_LAUNCH("align_stats", (k_align_stats<D, T>), dim3((unsigned)p.nch1, 2), dim3(kStatThreads), 0, s, m, p.rpc1, H,
-            overlap, Href, q.stat, q.cnt, (int)(p.ngroups + 1));
+            overlap, Href, q.stat);
+  HG_LAUNCH("align_mean", (k_align_mean<D>), dim3(2 * D / 16), dim3(256), 0, s, m, p.nch1, ddof, eps,
+            (const double*)q.stat, q.fin);
   // (d2)
   {
     auto kern = k_align_gram<D, T>;
@@ -822,16 +792,18 @@ int align_impl(int64_t m, const T* H, const int32_t* overlap, const T* Href, con
         attr_set = true;
       }
     }
-    HG_LAUNCH("align_gram", kern, dim3((unsigned)p.grid2), dim3(AShape<D>::kThreads), lds, s, m, p.nch1, p.rpc2,
-              p.nchg, ddof, eps, lambda_n, H, overlap, Href, w, (const double*)q.stat, q.gpart, q.spart, q.cnt,
-              q.fin, loss3);
+    HG_LAUNCH("align_gram", kern, dim3((unsigned)p.grid2), dim3(AShape<D>::kThreads), lds, s, m, p.rpc2, p.nchg, H,
+              overlap, Href, w, (const float*)q.fin, q.gpart, q.spart);
   }
+  HG_LAUNCH("align_reduce", (k_align_reduce<D>), dim3(AShape<D>::kRedGram + AShape<D>::kRedSums), dim3(256), 0, s,
+            p.nchg, (const float*)q.gpart, (const double*)q.spart, q.sums, q.lpart, q.fin);
   // (d3)
   HG_TRY((launch_align_grad<D, T>(m, H, rows_list(overlap), Href, rows_contig(0), q.fin, 0, w,
-                                  dHbase ? dHbase : (const T*)dH, dH, scale, lambda_n, ddof, s)));
+                                  dHbase ? dHbase : (const T*)dH, dH, scale, lambda_n, ddof, q.sums,
+                                  q.lpart, loss3, s)));
   if (dHref)
     HG_TRY((launch_align_grad<D, T>(m, Href, rows_contig(0), H, rows_list(overlap), q.fin, 1, w, nullptr, dHref,
-                                    scale, lambda_n, ddof, s)));
+                                    scale, lambda_n, ddof, q.sums, q.lpart, nullptr, s)));
   return HG_OK;
 }
 
@@ -894,9 +866,8 @@ extern "C" int hg_align_loss_fwd_bwd(int64_t M, int32_t d, int32_t dtype, int64_
 // The same passes with the workspace in a file-scope device array.  In host
 // code `scratch` names a host-side stand-in, not device memory: its device
 // address is taken with hipGetSymbolAddress once per device (each device
-// holds its own copy) and only that address is passed to the kernels.  The
-// counters of the Gram pass are zeroed by the statistics pass of the same
-// call, so nothing has to be cleared between calls.
+// holds its own copy) and only that address is passed to the kernels.  Nothing
+// has to be cleared between calls.
 namespace hg {
 namespace {
 constexpr size_t kAlignScratchBytes = size_t(48) << 20;
