@@ -452,7 +452,8 @@ struct HgtBwdWs {
   float* mupart;                   // [T * R * T, kMuChunks]
   float *Watt, *Wmsg;              // [R, d, d] block-diagonal expansions
   float *gatt, *gmsg;              // [R, d, d] full gradients before the block extraction
-  float *splitk, *colsum;          // split-K partials
+  float *splitk, *colsum;          // split-K partials, tn rows
+  int64_t tn;
   float *Kt, *Vt;                  // lean layers: Kt and Vt computed again, [A, d]
   float* pdq;                      // [fwd parts, d]: dQ shares of the chunks of long destination rows
   template <class A>
@@ -480,8 +481,12 @@ void HgtBwdWs::layout(A& a, const hg_subgraph* s, int d, int S, bool lean) {
   Wmsg = a.template take<float>(R * d * d);
   gatt = a.template take<float>(R * d * d);
   gmsg = a.template take<float>(R * d * d);
-  splitk = a.template take<float>(splitk_max_chunks() * (int64_t)d * d);
-  colsum = a.template take<float>(splitk_max_chunks() * (int64_t)d);
+  int64_t self = 0, rel = 0;
+  for (int t = 0; t < s->n_ntype; ++t) self += 4 * tn_chunks(s->type_off_host[t + 1] - s->type_off_host[t]);
+  for (int r = 0; r < s->n_rel; ++r) rel += 2 * tn_chunks(s->n_active[r]);
+  tn = tn_rows(d, self > rel ? self : rel);
+  splitk = a.template take<float>(tn * d * d);
+  colsum = a.template take<float>(tn * d);
   const int64_t nr = lean ? n_slots(s) : 0;
   Kt = a.template take<float>(nr * d);
   Vt = a.template take<float>(nr * d);
@@ -1250,15 +1255,12 @@ int hgt_bwd_impl(const hg_subgraph* s, const hg_hgt_desc* L, const float* Hin, c
   if (lean) HG_TRY(rel_transforms<D>(s, pv, w.Watt, w.Wmsg, sv.K, sv.V, w.Kt, w.Vt, st));
   const float* Kt = lean ? w.Kt : sv.Kt;
   const float* Vt = lean ? w.Vt : sv.Vt;
-  // (1) dZ = G * mask (written by the A load), dh~ = dZ W_agg^T; dW_agg, db_agg
+  // (1) dZ = G * mask (written by the A load), dh~ = dZ W_agg^T
   for (int t = 0; t < T; ++t) {
     const int64_t lo = s->type_off_host[t], hi = s->type_off_host[t + 1];
     LoadMasked<D, float> la{G, mask, rows_contig(lo), w.dZ};
     HG_TRY((launch_gemm_rows_pp<D, true>("hgt_bwd_dht", hi - lo, W->W_agg + (int64_t)t * D * D, la,
                                          StoreRows<D, float>{w.dht, rows_contig(lo), nullptr, nullptr}, st)));
-    HG_TRY((launch_gemm_tn<D>("hgt_bwd_dw", hi - lo, LoadRows<D, float>{sv.ht, rows_contig(lo)},
-                              LoadRows<D, float>{w.dZ, rows_contig(lo)}, w.splitk, w.colsum,
-                              dW->W_agg + (int64_t)t * D * D, dW->b_agg ? dW->b_agg + (int64_t)t * D : nullptr, acc, st)));
   }
   // (2) destination pass, (3) source pass
   if (s->n_sub > 0) {
@@ -1312,6 +1314,7 @@ int hgt_bwd_impl(const hg_subgraph* s, const hg_hgt_desc* L, const float* Hin, c
     HG_TRY(fill_f32(w.dK, 0.f, s->n_sub * (int64_t)D, st));
     HG_TRY(fill_f32(w.dV, 0.f, s->n_sub * (int64_t)D, st));
   }
+  TnBatch<D, float, float, true, true> brel("hgt_bwd_dw_rel", w.splitk, w.colsum, w.tn, st);
   int64_t off = 0;
   for (int r = 0; r < R; ++r) {
     const int64_t n = s->n_active[r];
@@ -1324,14 +1327,14 @@ int hgt_bwd_impl(const hg_subgraph* s, const hg_hgt_desc* L, const float* Hin, c
                                            LoadRows<D, float>{w.dVt, rows_list(pv.act_slot + off)},
                                            StoreRows<D, float>{w.dV, rows_list(pv.active + off), nullptr, w.dV}, st)));
     }
-    HG_TRY((launch_gemm_tn<D>("hgt_bwd_dw", n, LoadRows<D, float>{sv.K, rows_list(pv.active + off)},
-                              LoadRows<D, float>{w.dKt, rows_list(pv.act_slot + off)}, w.splitk, w.colsum,
-                              w.gatt + wo, nullptr, 0, st)));
-    HG_TRY((launch_gemm_tn<D>("hgt_bwd_dw", n, LoadRows<D, float>{sv.V, rows_list(pv.active + off)},
-                              LoadRows<D, float>{w.dVt, rows_list(pv.act_slot + off)}, w.splitk, w.colsum,
-                              w.gmsg + wo, nullptr, 0, st)));
+    HG_TRY(brel.group(n, 2));
+    brel.add(LoadRows<D, float>{sv.K, rows_list(pv.active + off)}, LoadRows<D, float>{w.dKt, rows_list(pv.act_slot + off)},
+             w.gatt + wo, nullptr, 0);
+    brel.add(LoadRows<D, float>{sv.V, rows_list(pv.active + off)}, LoadRows<D, float>{w.dVt, rows_list(pv.act_slot + off)},
+             w.gmsg + wo, nullptr, 0);
     off += n;
   }
+  HG_TRY(brel.run());
   {
     const int64_t n = (int64_t)R * D * D / S;
     const unsigned g = (unsigned)(cdiv(n, 256) < 4096 ? cdiv(n, 256) : 4096);
@@ -1340,7 +1343,9 @@ int hgt_bwd_impl(const hg_subgraph* s, const hg_hgt_desc* L, const float* Hin, c
     HG_LAUNCH("hgt_diagblocks", k_diagblocks, dim3(g), dim3(256), 0, st, (const float*)w.gmsg, (int64_t)R, D, S, dW->W_msg,
               acc);
   }
-  // (5) dH = G (residual) + dK W_K^T + dQ W_Q^T + dV W_V^T per type; projection gradients
+  // (5) dH = G (residual) + dK W_K^T + dQ W_Q^T + dV W_V^T per type; projection and
+  // aggregation gradients
+  TnBatch<D, float, float, false, false> bproj("hgt_bwd_dw", w.splitk, w.colsum, w.tn, st);
   for (int t = 0; t < T; ++t) {
     const int64_t lo = s->type_off_host[t], hi = s->type_off_host[t + 1];
     const int64_t wo = (int64_t)t * D * D, bo = (int64_t)t * D;
@@ -1366,11 +1371,15 @@ int hgt_bwd_impl(const hg_subgraph* s, const hg_hgt_desc* L, const float* Hin, c
                                              StoreRows<D, float>{dHin, rows_contig(lo), nullptr, addend}, st)));
       }
     }
+    // dW_K, dW_Q and dW_V read the same rows of H: one group; dW_agg beside it
+    HG_TRY(bproj.group(hi - lo, 4));
     for (int k = 0; k < 3; ++k)
-      HG_TRY((launch_gemm_tn<D>("hgt_bwd_dw", hi - lo, LoadRows<D, float>{Hin, rows_contig(lo)},
-                                LoadRows<D, float>{srcs[k], rows_contig(lo)}, w.splitk, w.colsum, dWs[k] + wo,
-                                dbs[k] ? dbs[k] + bo : nullptr, acc, st)));
+      bproj.add(LoadRows<D, float>{Hin, rows_contig(lo)}, LoadRows<D, float>{srcs[k], rows_contig(lo)}, dWs[k] + wo,
+                dbs[k] ? dbs[k] + bo : nullptr, acc);
+    bproj.add(LoadRows<D, float>{sv.ht, rows_contig(lo)}, LoadRows<D, float>{w.dZ, rows_contig(lo)}, dW->W_agg + wo,
+              dW->b_agg ? dW->b_agg + bo : nullptr, acc);
   }
+  HG_TRY(bproj.run());
   // (6) dmu: per CSR row by source type, then per meta relation over each type range
   {
     const int64_t nq = s->n_sub * (int64_t)R;

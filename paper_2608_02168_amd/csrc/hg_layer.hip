@@ -461,14 +461,19 @@ struct BwdWs {
   T* dZ;
   float *dY, *dhacc, *splitk, *colsum;
   double* part;
+  int64_t tn;  // partial rows of the weight gradients
   template <class A>
   void layout(A& a, const hg_subgraph* s) {
     dZ = a.template take<T>(s->n_sub * (int64_t)D);
     dY = a.template take<float>(n_slots(s) * (int64_t)D);
     dhacc = a.template take<float>(sizeof(T) == 2 ? s->n_sub * (int64_t)D : 0);
     part = a.template take<double>(s->plan_partials * (int64_t)D);
-    splitk = a.template take<float>(splitk_max_chunks() * (int64_t)D * D);
-    colsum = a.template take<float>(splitk_max_chunks() * (int64_t)D);
+    int64_t self = 0, rel = 0;
+    for (int t = 0; t < s->n_ntype; ++t) self += tn_chunks(s->type_off_host[t + 1] - s->type_off_host[t]);
+    for (int r = 0; r < s->n_rel; ++r) rel += tn_chunks(s->n_active[r]);
+    tn = tn_rows(D, self > rel ? self : rel);
+    splitk = a.template take<float>(tn * D * D);
+    colsum = a.template take<float>(tn * D);
   }
 };
 
@@ -587,21 +592,25 @@ int layer_bwd_impl(const hg_subgraph* s, const hg_layer_desc* L, const T* Hin, c
       HG_TRY((rows_f32<D, true>("gemm_bwd_dx_rel", n, W_rel + (int64_t)r * D * D, la, ep, st)));
     }
   }
-  // (c) weight gradients, split-K
-  for (int t = 0; t < s->n_ntype; ++t) {
-    const int64_t lo = s->type_off_host[t], hi = s->type_off_host[t + 1];
-    LoadRows<D, T> la{Hin, rows_contig(lo)};
-    LoadRows<D, T> lb{w.dZ, rows_contig(lo)};
-    HG_TRY((launch_gemm_tn<D>("gemm_bwd_dw_self", hi - lo, la, lb, w.splitk, w.colsum,
-                              dW_self + (int64_t)t * D * D, dbias ? dbias + (int64_t)t * D : nullptr, acc, st)));
+  // (c) weight gradients, split-K: one launch over the types, one over the relations
+  {
+    TnBatch<D, T, T, false, false> b("gemm_bwd_dw_self", w.splitk, w.colsum, w.tn, st);
+    for (int t = 0; t < s->n_ntype; ++t) {
+      const int64_t lo = s->type_off_host[t], hi = s->type_off_host[t + 1];
+      HG_TRY(b.group(hi - lo, 1));
+      b.add(LoadRows<D, T>{Hin, rows_contig(lo)}, LoadRows<D, T>{w.dZ, rows_contig(lo)}, dW_self + (int64_t)t * D * D,
+            dbias ? dbias + (int64_t)t * D : nullptr, acc);
+    }
+    HG_TRY(b.run());
   }
+  TnBatch<D, T, float, true, true> b("gemm_bwd_dw_rel", w.splitk, w.colsum, w.tn, st);
   for (int r = 0; r < R; ++r) {
-    const int64_t n = s->n_active[r], off = act_off[r];
-    LoadRows<D, T> la{Hin, rows_list(pv.active + off)};
-    LoadRows<D, float> lb{w.dY, rows_list(pv.act_slot + off)};
-    HG_TRY((launch_gemm_tn<D>("gemm_bwd_dw_rel", n, la, lb, w.splitk, w.colsum, dW_rel + (int64_t)r * D * D,
-                              nullptr, acc, st)));
+    const int64_t off = act_off[r];
+    HG_TRY(b.group(s->n_active[r], 1));
+    b.add(LoadRows<D, T>{Hin, rows_list(pv.active + off)}, LoadRows<D, float>{w.dY, rows_list(pv.act_slot + off)},
+          dW_rel + (int64_t)r * D * D, nullptr, acc);
   }
+  HG_TRY(b.run());
   return HG_OK;
 }
 

@@ -1028,6 +1028,50 @@ inline unsigned tn_grid(int D, int64_t chunks) {
   return (unsigned)(D == 256 ? 4 * cdiv(chunks, 8) * 8 : chunks);
 }
 
+// Weight gradients of one launch: up to kTnJobs products A^T B of the same
+// storage types, in groups of jobs with the same row count (products that read
+// the same rows: the gates of one state, the projections of one input).  A
+// group takes T q blocks per chunk (T output tiles, q jobs), 8 apart in block
+// index, so they run on one XCD at about the same time and a row that several
+// of them read comes from HBM once.  Chunk c of a job writes partial row
+// chunk0[job] + c.
+constexpr int kTnJobs = 24;
+template <int D, class TA, class TB>
+struct TnJobs {
+  LoadRows<D, TA> la[kTnJobs];
+  LoadRows<D, TB> lb[kTnJobs];
+  int64_t n[kTnJobs];          // rows of a group's jobs (by group)
+  int32_t kc[kTnJobs];         // rows per chunk (by group)
+  int32_t block0[kTnJobs + 1]; // first block of a group
+  int32_t job0[kTnJobs + 1];   // first job of a group
+  int32_t chunk0[kTnJobs];     // first partial row of a job
+  int32_t groups;
+};
+
+// The block's job, tile and rows; false for a padding block.
+struct TnBlock {
+  int job, ti, tj;
+  int64_t row0;      // partial row
+  int64_t k_beg, k_end;
+};
+template <int D, class TA, class TB>
+__device__ __forceinline__ bool tn_find(const TnJobs<D, TA, TB>& J, TnBlock& b) {
+  constexpr int T = D == 256 ? 4 : 1;
+  const int blk = (int)blockIdx.x;
+  int g = 0;
+  while (g + 1 < J.groups && blk >= J.block0[g + 1]) ++g;
+  const int u = blk - J.block0[g], q = J.job0[g + 1] - J.job0[g];
+  const int v = u >> 3, sub = v % (q * T);
+  const int64_t chunk = (int64_t)(v / (q * T)) * 8 + (u & 7);
+  b.job = J.job0[g] + sub / T;
+  b.ti = (sub % T) >> 1;
+  b.tj = (sub % T) & 1;
+  b.k_beg = chunk * J.kc[g];
+  b.k_end = b.k_beg + J.kc[g] < J.n[g] ? b.k_beg + J.kc[g] : J.n[g];
+  b.row0 = J.chunk0[b.job] + chunk;
+  return b.k_beg < J.n[g];
+}
+
 // partial[chunk][i][j] = sum_{rows k of the chunk} A[k][i] * B[k][j]
 // colsum[chunk][j]    = sum_{rows k of the chunk} B[k][j]        (if colsum)
 // A wave owns a 64 x 64 block of the output (D = 128: wave w takes quadrant
@@ -1205,8 +1249,7 @@ __device__ __forceinline__ void split_bf3(float v0, float v1, uint32_t (&part)[3
 // float32-like products.  Same outputs, chunking, wave tiling and epilogue
 // as k_gemm_tn.
 template <int D, class TA, class TB, bool kListA, bool kListB>
-__global__ void __launch_bounds__(256, 2) k_gemm_tn_bf(int64_t n_rows, int64_t kc, LoadRows<D, TA> la,
-                                                       LoadRows<D, TB> lb, float* __restrict__ partial,
+__global__ void __launch_bounds__(256, 2) k_gemm_tn_bf(const TnJobs<D, TA, TB> J, float* __restrict__ partial,
                                                        float* __restrict__ colsum) {
   static_assert(D == 64 || D == 128 || D == 256, "gemm_tn_bf: d must be 64, 128 or 256");
   constexpr bool kQuad = (D >= 128);
@@ -1216,12 +1259,12 @@ __global__ void __launch_bounds__(256, 2) k_gemm_tn_bf(int64_t n_rows, int64_t k
   const int w = threadIdx.x >> 6;
   const int l = lane64();
   const int g = l >> 4, c = l & 15;
-  int64_t chunk;
-  int ti, tj;
-  tn_block<D>(chunk, ti, tj);
-  const int64_t k_beg = chunk * kc;
-  if (k_beg >= n_rows) return;  // a padding block (the whole block)
-  const int64_t k_end = (k_beg + kc < n_rows) ? k_beg + kc : n_rows;
+  TnBlock blk;
+  if (!tn_find(J, blk)) return;  // a padding block (the whole block)
+  const LoadRows<D, TA> la = J.la[blk.job];
+  const LoadRows<D, TB> lb = J.lb[blk.job];
+  const int ti = blk.ti, tj = blk.tj;
+  const int64_t chunk = blk.row0, k_beg = blk.k_beg, k_end = blk.k_end;
   const int qi = kQuad ? (w >> 1) : 0;
   const int qj = kQuad ? (w & 1) : 0;
   const int64_t step0 = kQuad ? 0 : 32 * w;
@@ -1417,36 +1460,43 @@ __global__ void __launch_bounds__(256, 2) k_gemm_tn_bf(int64_t n_rows, int64_t k
   }
 }
 
-template <class L>
-struct IsPlainRows : std::false_type {};
-template <int D, class T>
-struct IsPlainRows<LoadRows<D, T>> : std::true_type {};
-
-// Fixed-order reduction of nchunks partial arrays of n floats, in two stages:
-// group g sums chunks [g*per, (g+1)*per) in order into tmp[g], then the groups
-// are summed in order: out[i] (+)= sum_g tmp[g][i].
+// Fixed-order reduction of the chunks: out (+)= the sum of partial rows [c0, c1)
+// of D x D floats, and colsum (+)= that of the column sums.  One launch for all
+// outputs of a batch: 16 elements of 4 floats x kSplitGroups runs of chunks per
+// block, each run in order, then the runs in order.  (A grouped pass and a final
+// pass per gradient, and two more for its column sums, were 14 launches of 8-10
+// us per layer of four relations and 44 per attention layer.)
 constexpr int kSplitGroups = 16;
-
-static __global__ void k_sum_partials_grouped(const float* __restrict__ partial, int64_t nchunks,
-                                              int64_t n, int64_t per, float* __restrict__ tmp) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t grp = blockIdx.y;
-  if (i >= n) return;
-  const int64_t c0 = grp * per;
-  const int64_t c1 = (c0 + per < nchunks) ? c0 + per : nchunks;
-  float s = 0.f;
-  for (int64_t c = c0; c < c1; ++c) s += partial[c * n + i];
-  tmp[grp * n + i] = s;
-}
-
-// out[i] (+)= sum_{c < nchunks} partial[c][i]   (fixed order)
-static __global__ void k_sum_partials(const float* __restrict__ partial, int64_t nchunks, int64_t n,
-                                      float* __restrict__ out, int accumulate) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  float s = accumulate ? out[i] : 0.f;
-  for (int64_t c = 0; c < nchunks; ++c) s += partial[c * n + i];
-  out[i] = s;
+struct TnOut {
+  float *out, *colsum;
+  int32_t c0, c1, acc;
+};
+struct TnOuts {
+  TnOut o[kTnJobs];
+};
+template <int D>
+__global__ void __launch_bounds__(256) k_tn_reduce(const TnOuts outs, const float* __restrict__ partial,
+                                                   const float* __restrict__ colsum) {
+  __shared__ f32x4 red[kSplitGroups][16];
+  const TnOut o = outs.o[blockIdx.y];
+  const bool cs = blockIdx.x >= D * D / 64;
+  if (cs && !o.colsum) return;
+  const int e = threadIdx.x & 15, grp = threadIdx.x >> 4;
+  const int64_t stride = cs ? D : D * D, at = 64 * (int64_t)(cs ? blockIdx.x - D * D / 64 : blockIdx.x) + 4 * e;
+  const float* src = (cs ? colsum : partial) + at;
+  float* dst = (cs ? o.colsum : o.out) + at;
+  const int32_t per = (o.c1 - o.c0 + kSplitGroups - 1) / kSplitGroups;
+  const int32_t b = o.c0 + grp * per, end = b + per < o.c1 ? b + per : o.c1;
+  f32x4 t = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+  for (int32_t c = b; c < end; ++c) t += *reinterpret_cast<const f32x4*>(src + c * stride);
+  red[grp][e] = t;
+  __syncthreads();
+  if (grp) return;
+  for (int g = 1; g < kSplitGroups; ++g) t += red[g][e];
+  // the caller's gradients need only be aligned to a float
+#pragma unroll
+  for (int k = 0; k < 4; ++k) dst[k] = o.acc ? dst[k] + t[k] : t[k];
 }
 
 // gemm_tn on v_mfma_f32_16x16x32_bf16 for plain feature rows at d = 128 and
@@ -1481,8 +1531,7 @@ __device__ __forceinline__ void lds_barrier() {
 }
 
 template <int D, class TA, class TB, bool kListA, bool kListB>
-__global__ void __launch_bounds__(256, 2) k_gemm_tn_lds(int64_t n_rows, int64_t kc, LoadRows<D, TA> la,
-                                                        LoadRows<D, TB> lb, float* __restrict__ partial,
+__global__ void __launch_bounds__(256, 2) k_gemm_tn_lds(const TnJobs<D, TA, TB> J, float* __restrict__ partial,
                                                         float* __restrict__ colsum) {
   static_assert(D == 128 || D == 256, "gemm_tn_lds: d must be 128 or 256");
   constexpr bool kSplitA = sizeof(TA) == 4, kSplitB = sizeof(TB) == 4;
@@ -1500,12 +1549,12 @@ __global__ void __launch_bounds__(256, 2) k_gemm_tn_lds(int64_t n_rows, int64_t 
   __shared__ float cred[4][TT];
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
   const int g = l >> 4, c = l & 15;
-  int64_t chunk;
-  int ti, tj;
-  tn_block<D>(chunk, ti, tj);
-  const int64_t k_beg = chunk * kc;
-  if (k_beg >= n_rows) return;  // a padding block (the whole block)
-  const int64_t k_end = (k_beg + kc < n_rows) ? k_beg + kc : n_rows;
+  TnBlock blk;
+  if (!tn_find(J, blk)) return;  // a padding block (the whole block)
+  const LoadRows<D, TA> la = J.la[blk.job];
+  const LoadRows<D, TB> lb = J.lb[blk.job];
+  const int ti = blk.ti, tj = blk.tj;
+  const int64_t chunk = blk.row0, k_beg = blk.k_beg, k_end = blk.k_end;
   // staging role (uniform per wave)
   const bool sb = tid >= 128;
   const int u = tid & 127, sg = u >> 5, sf = 4 * (u & 31);
@@ -1685,78 +1734,120 @@ inline int64_t splitk_chunk(int64_t n) {
   kc = cdiv(kc, 64) * 64;
   return kc > 64 ? kc : 64;
 }
-inline int64_t splitk_max_chunks() { return (int64_t)num_cus() * kSplitPerCu + kSplitGroups + 1; }
-
-// partial must hold splitk_max_chunks() * D * D floats: the grouped stage
-// writes its kSplitGroups rows after the chunk rows.
-inline int reduce_partials(const float* partial, int64_t chunks, int64_t n, float* tmp, float* out,
-                           int accumulate, hipStream_t s) {
-  if (chunks <= 2 * kSplitGroups) {
-    HG_LAUNCH("splitk_reduce", k_sum_partials, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, s, partial,
-              chunks, n, out, accumulate);
-    return HG_OK;
-  }
-  const int64_t per = cdiv(chunks, kSplitGroups);
-  const int64_t groups = cdiv(chunks, per);
-  HG_LAUNCH("splitk_reduce", k_sum_partials_grouped, dim3((unsigned)cdiv(n, 256), (unsigned)groups), dim3(256),
-            0, s, partial, chunks, n, per, tmp);
-  HG_LAUNCH("splitk_reduce", k_sum_partials, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, s, (const float*)tmp,
-            groups, n, out, accumulate);
-  return HG_OK;
+inline int64_t tn_chunks(int64_t n) { return n > 0 ? cdiv(n, splitk_chunk(n)) : 0; }
+// at least tn_chunks(m) of every m <= n
+inline int64_t tn_chunks_upto(int64_t n) {
+  const int64_t c = cdiv(n > 0 ? n : 1, 512), cap = (int64_t)num_cus() * kSplitPerCu;
+  return c < cap ? c : cap;
 }
 
+// Partial rows a batch may hold at most (a longer batch runs in parts): one
+// job's at least, and about 270 MB.
+template <int D>
+constexpr int64_t tn_cap() {
+  return D == 64 ? 8192 : (D == 128 ? 4096 : 1024);
+}
+// Partial rows (of D x D and of D floats) for batches of `chunks` chunks.
+inline int64_t tn_rows(int D, int64_t chunks) {
+  const int64_t one = (int64_t)num_cus() * kSplitPerCu + 1;
+  const int64_t cap = D == 64 ? tn_cap<64>() : (D == 128 ? tn_cap<128>() : tn_cap<256>());
+  const int64_t most = cap > one ? cap : one;
+  return chunks < 1 ? 1 : (chunks < most ? chunks : most);
+}
+
+// Collects the products of a launch: group() starts a group of jobs over n
+// rows, add() adds A^T B to it, into out (and B's column sums into out_colsum,
+// if given); jobs added one after another with the same out are summed.  run()
+// launches what is there.  partial and colsum hold `rows` partial rows.
+template <int D, class TA, class TB, bool kListA, bool kListB>
+struct TnBatch {
+  const char* name;
+  float *partial, *colsum;
+  int64_t rows;
+  hipStream_t s;
+  TnJobs<D, TA, TB> J{};
+  TnOuts outs{};
+  int jobs = 0, n_out = 0;
+  int64_t used = 0, group_n = 0;
+  bool any_colsum = false;
+  TnBatch(const char* nm, float* p, float* c, int64_t r, hipStream_t st) : name(nm), partial(p), colsum(c), rows(r), s(st) {}
+
+  // q jobs of n rows follow
+  int group(int64_t n, int q) {
+    if (q > kTnJobs) return fail(HG_ERR_ARG, "%s: %d jobs in a group", name, q);
+    const int64_t need = q * tn_chunks(n);
+    if (n_out + q > kTnJobs || jobs + q > kTnJobs || (jobs > 0 && used + need > rows)) HG_TRY(run());
+    if (need > rows) return fail(HG_ERR_CAPACITY, "%s: %lld partial rows, %lld held", name, (long long)need, (long long)rows);
+    group_n = n;
+    if (n > 0) {
+      const int g = J.groups++;
+      J.n[g] = n;
+      J.kc[g] = (int32_t)splitk_chunk(n);
+      J.job0[g] = jobs;
+      J.job0[g + 1] = jobs;
+    }
+    return HG_OK;
+  }
+  void add(LoadRows<D, TA> la, LoadRows<D, TB> lb, float* out, float* out_colsum, int accumulate) {
+    const int64_t c = tn_chunks(group_n);
+    if (n_out > 0 && outs.o[n_out - 1].out == out) {
+      outs.o[n_out - 1].c1 += (int32_t)c;
+    } else {
+      outs.o[n_out++] = TnOut{out, out_colsum, (int32_t)used, (int32_t)(used + c), accumulate};
+      any_colsum |= out_colsum != nullptr;
+    }
+    if (group_n <= 0) return;
+    J.la[jobs] = la;
+    J.lb[jobs] = lb;
+    J.chunk0[jobs] = (int32_t)used;
+    used += c;
+    J.job0[J.groups] = ++jobs;
+  }
+  int run() {
+    constexpr int T = D == 256 ? 4 : 1;
+    if (J.groups > 0) {
+      int64_t blocks = 0;
+      for (int g = 0; g < J.groups; ++g) {
+        J.block0[g] = (int32_t)blocks;
+        blocks += 8 * cdiv(cdiv(J.n[g], J.kc[g]), 8) * (J.job0[g + 1] - J.job0[g]) * T;
+      }
+      J.block0[J.groups] = (int32_t)blocks;
+      float* cs = any_colsum ? colsum : nullptr;
+      if constexpr (D >= 128 && sizeof(TA) == sizeof(TB)) {
+        HG_LAUNCH(name, (k_gemm_tn_lds<D, TA, TB, kListA, kListB>), dim3((unsigned)blocks), dim3(256), 0, s, J, partial, cs);
+      } else {
+        HG_LAUNCH(name, (k_gemm_tn_bf<D, TA, TB, kListA, kListB>), dim3((unsigned)blocks), dim3(256), 0, s, J, partial, cs);
+      }
+    }
+    if (n_out > 0)
+      HG_LAUNCH("splitk_reduce", k_tn_reduce<D>, dim3(D * D / 64 + (any_colsum ? D / 64 : 0), (unsigned)n_out), dim3(256),
+                0, s, outs, (const float*)partial, (const float*)colsum);
+    J.groups = 0;
+    jobs = n_out = 0;
+    used = 0;
+    any_colsum = false;
+    return HG_OK;
+  }
+};
+
+// One product whose B rows a loader forms (the head's dW1), on the float32 MFMA.
 template <int D, class LA, class LB>
 int launch_gemm_tn(const char* name, int64_t n_rows, LA la, LB lb, float* partial, float* colsum,
                    float* out, float* out_colsum, int accumulate, hipStream_t s) {
-  if (n_rows <= 0) {
-    if (!accumulate) {
-      HG_TRY(fill_f32(out, 0.f, (int64_t)D * D, s));
-      if (out_colsum) HG_TRY(fill_f32(out_colsum, 0.f, D, s));
-    }
-    return HG_OK;
-  }
-  const int64_t kc = splitk_chunk(n_rows);
-  const int64_t chunks = cdiv(n_rows, kc);
-  const bool list_a = la.map.list != nullptr, list_b = lb.map.list != nullptr;
+  const int64_t kc = splitk_chunk(n_rows), chunks = tn_chunks(n_rows);
+  TnOuts outs{};
+  outs.o[0] = TnOut{out, out_colsum, 0, (int32_t)chunks, accumulate};
   float* cs = out_colsum ? colsum : nullptr;
-  const dim3 grid(tn_grid(D, chunks));
-  if constexpr (IsPlainRows<LA>::value && IsPlainRows<LB>::value) {
-    // plain feature rows: the bf16 MFMA kernel
-    typedef typename std::remove_cv<typename std::remove_pointer<decltype(la.base)>::type>::type TA_;
-    typedef typename std::remove_cv<typename std::remove_pointer<decltype(lb.base)>::type>::type TB_;
-#define HG_TN_BF(LA_, LB_)                                                                                 \
-  do {                                                                                                     \
-    if constexpr (D >= 128 && sizeof(TA_) == sizeof(TB_)) {                                              \
-      HG_LAUNCH(name, (k_gemm_tn_lds<D, TA_, TB_, LA_, LB_>), grid, dim3(256), 0, s, n_rows, kc, la, lb, partial, \
-                cs);                                                                                       \
-    } else {                                                                                               \
-      HG_LAUNCH(name, (k_gemm_tn_bf<D, TA_, TB_, LA_, LB_>), grid, dim3(256), 0, s, n_rows, kc, la, lb, partial, \
-                cs);                                                                                       \
-    }                                                                                                      \
-  } while (0)
-    if (list_a && list_b) {
-      HG_TN_BF(true, true);
-    } else if (!list_a && !list_b) {
-      HG_TN_BF(false, false);
-    } else if (list_a) {
-      HG_TN_BF(true, false);
+  if (chunks > 0) {
+    const dim3 grid(tn_grid(D, chunks));
+    if (la.map.list) {
+      HG_LAUNCH(name, (k_gemm_tn<D, LA, LB, true, false>), grid, dim3(256), 0, s, n_rows, kc, la, lb, partial, cs);
     } else {
-      HG_TN_BF(false, true);
+      HG_LAUNCH(name, (k_gemm_tn<D, LA, LB, false, false>), grid, dim3(256), 0, s, n_rows, kc, la, lb, partial, cs);
     }
-#undef HG_TN_BF
-  } else if (list_a && list_b) {
-    HG_LAUNCH(name, (k_gemm_tn<D, LA, LB, true, true>), grid, dim3(256), 0, s, n_rows, kc, la, lb, partial, cs);
-  } else if (!list_a && !list_b) {
-    HG_LAUNCH(name, (k_gemm_tn<D, LA, LB, false, false>), grid, dim3(256), 0, s, n_rows, kc, la, lb, partial, cs);
-  } else if (list_a) {
-    HG_LAUNCH(name, (k_gemm_tn<D, LA, LB, true, false>), grid, dim3(256), 0, s, n_rows, kc, la, lb, partial, cs);
-  } else {
-    HG_LAUNCH(name, (k_gemm_tn<D, LA, LB, false, true>), grid, dim3(256), 0, s, n_rows, kc, la, lb, partial, cs);
   }
-  const int64_t cap = (int64_t)num_cus() * kSplitPerCu + 1;
-  HG_TRY(reduce_partials(partial, chunks, (int64_t)D * D, partial + cap * D * D, out, accumulate, s));
-  if (out_colsum)
-    HG_TRY(reduce_partials(colsum, chunks, (int64_t)D, colsum + cap * D, out_colsum, accumulate, s));
+  HG_LAUNCH("splitk_reduce", k_tn_reduce<D>, dim3(D * D / 64 + (cs ? D / 64 : 0), 1), dim3(256), 0, s, outs,
+            (const float*)partial, (const float*)colsum);
   return HG_OK;
 }
 

@@ -235,8 +235,8 @@ struct HeadWs {
     dout = a.template take<float>(n);
     cnt = a.template take<int32_t>(kHeadBlocks);
     part = a.template take<float>((int64_t)kHeadBlocks * (d + 2));
-    splitk = a.template take<float>(splitk_max_chunks() * (int64_t)d * d);
-    colsum = a.template take<float>(splitk_max_chunks() * (int64_t)d);
+    splitk = a.template take<float>(tn_chunks_upto(n) * d * d);
+    colsum = a.template take<float>(tn_chunks_upto(n) * d);
   }
 };
 

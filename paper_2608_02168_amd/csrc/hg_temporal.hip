@@ -486,14 +486,16 @@ int64_t t_grid(int64_t n) {
 
 struct TempWs {
   float *Ht, *dG, *dpre, *dr_part, *splitk, *colsum;
+  int64_t tn;  // partial rows of the weight gradients
   template <class A>
   void layout(A& a, int64_t n, int w) {
     Ht = a.template take<float>(n * kTD);
     dG = a.template take<float>(4 * n * kTD);
     dpre = a.template take<float>((int64_t)w * n * kTD);
     dr_part = a.template take<float>((t_grid(n) > 0 ? t_grid(n) : 1) * kTD);
-    splitk = a.template take<float>(splitk_max_chunks() * (int64_t)kTD * kTD);
-    colsum = a.template take<float>(splitk_max_chunks() * (int64_t)kTD);
+    tn = tn_rows(kTD, (w > 6 ? w : 6) * tn_chunks(n));
+    splitk = a.template take<float>(tn * kTD * kTD);
+    colsum = a.template take<float>(tn * kTD);
   }
 };
 
@@ -569,31 +571,37 @@ int temporal_bwd_impl(int64_t n, int w, const T* h, const void* const* C, const 
     HG_TRY(s);
   }
   constexpr int64_t kDD = (int64_t)kTD * kTD;
-  // dWi[k] = h^T dG[:, k], dbi[k] = column sums of dG[:, k]
+  // dWi[k] = h^T dG[:, k], dbi[k] = column sums of dG[:, k];
+  // dWh[k] = Ht^T dG[:, k'] with k' = 0, 1, 3 (the new gate's hidden side is gated by r).
+  // The six products of float32 rows are one group: h, Ht and the shared gates
+  // are read from HBM once (bf16 states: the three of each side)
+  const auto gate = [&](int k) { return LoadRows<kTD, float>{wk.dG, RowMap{nullptr, 0, 4, k}}; };
+  const LoadRows<kTD, T> lh{h, rows_contig(0)};
+  const LoadRows<kTD, float> lt{wk.Ht, rows_contig(0)};
+  TnBatch<kTD, T, float, false, false> bi("temporal_dWi", wk.splitk, wk.colsum, wk.tn, st);
+  TnBatch<kTD, float, float, false, false> bh("temporal_dWh", wk.splitk, wk.colsum, wk.tn, st);
+  constexpr bool kOne = sizeof(T) == 4;
+  HG_TRY(bi.group(n, kOne ? 6 : 3));
+  if (!kOne) HG_TRY(bh.group(n, 3));
   for (int k = 0; k < 3; ++k) {
-    HG_TRY((launch_gemm_tn<kTD>("temporal_dWi", n, LoadRows<kTD, T>{h, rows_contig(0)},
-                                LoadRows<kTD, float>{wk.dG, RowMap{nullptr, 0, 4, k}}, wk.splitk, wk.colsum,
-                                G->Wi + k * kDD, G->bi ? G->bi + k * kTD : nullptr, accumulate, st)));
-  }
-  // dWh[k] = Ht^T dG[:, k'] with k' = 0, 1, 3 (the new gate's hidden side is gated by r)
-  for (int k = 0; k < 3; ++k) {
-    const int q = k < 2 ? k : 3;
-    HG_TRY((launch_gemm_tn<kTD>("temporal_dWh", n, LoadRows<kTD, float>{wk.Ht, rows_contig(0)},
-                                LoadRows<kTD, float>{wk.dG, RowMap{nullptr, 0, 4, q}}, wk.splitk, wk.colsum,
-                                G->Wh + k * kDD, G->bh ? G->bh + k * kTD : nullptr, accumulate, st)));
-  }
-  // dQ = sum_k dpre_k^T C_k
-  if (w == 0 || n == 0) {
-    if (!accumulate) HG_TRY(fill_f32(G->Q, 0.f, kDD, st));
-  }
-  if (n > 0) {
-    for (int k = 0; k < w; ++k) {
-      HG_TRY((launch_gemm_tn<kTD>("temporal_dQ", n, LoadRows<kTD, float>{wk.dpre + (int64_t)k * n * kTD,
-                                                                         rows_contig(0)},
-                                  LoadRows<kTD, T>{static_cast<const T*>(C[k]), rows_contig(0)}, wk.splitk,
-                                  wk.colsum, G->Q, nullptr, (k > 0 || accumulate) ? 1 : 0, st)));
+    bi.add(lh, gate(k), G->Wi + k * kDD, G->bi ? G->bi + k * kTD : nullptr, accumulate);
+    float *wh = G->Wh + k * kDD, *bias = G->bh ? G->bh + k * kTD : nullptr;
+    if constexpr (kOne) {
+      bi.add(lt, gate(k < 2 ? k : 3), wh, bias, accumulate);
+    } else {
+      bh.add(lt, gate(k < 2 ? k : 3), wh, bias, accumulate);
     }
   }
+  HG_TRY(bi.run());
+  if (!kOne) HG_TRY(bh.run());
+  // dQ = sum_k dpre_k^T C_k
+  TnBatch<kTD, float, T, false, false> bq("temporal_dQ", wk.splitk, wk.colsum, wk.tn, st);
+  HG_TRY(bq.group(w > 0 ? n : 0, w > 0 ? w : 1));
+  for (int k = 0; k < w; ++k)
+    bq.add(LoadRows<kTD, float>{wk.dpre + (int64_t)k * n * kTD, rows_contig(0)},
+           LoadRows<kTD, T>{static_cast<const T*>(C[k]), rows_contig(0)}, G->Q, nullptr, accumulate);
+  if (w == 0) bq.add(LoadRows<kTD, float>{}, LoadRows<kTD, T>{}, G->Q, nullptr, accumulate);
+  HG_TRY(bq.run());
   const int64_t blocks = n > 0 ? t_grid(n) : 0;
   HG_LAUNCH("temporal_dr", k_temporal_dr, dim3(1), dim3(kTD), 0, st, (const float*)wk.dr_part, blocks, G->r,
             accumulate);
