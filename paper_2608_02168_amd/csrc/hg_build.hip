@@ -28,7 +28,16 @@ namespace hg {
 namespace {
 
 constexpr int kBT = 256;  // threads per block for the elementwise passes
-constexpr int kChunk = 1024;  // max CSC entries handled by one backward work item
+// Most CSC entries that one backward work item (one wave) handles.  A wave walks
+// its entries serially, 16 or more rows in flight, so a hub's items are the
+// pass's tail: 1024 entries take about 45 us, which is all of the pass on a
+// graph whose edges would give each of the chip's 8192 waves a few dozen
+// (100k edges: 50 us at 1024, 14 at 64), and nothing beside it at 200M, where
+// short items would only cost partial rows.  E: the input graph's edges (the
+// plan's capacity follows from them).
+__host__ __device__ inline int plan_chunk(int64_t E) {
+  return E < ((int64_t)1 << 20) ? 64 : (E < ((int64_t)1 << 23) ? 256 : 1024);
+}
 
 inline unsigned grid_for(int64_t n, int64_t cap = 16384) {
   int64_t b = cdiv(n > 0 ? n : 1, kBT);
@@ -1551,7 +1560,7 @@ __device__ __forceinline__ int wave_before(int v) {
   return inc - v;
 }
 
-__device__ __forceinline__ int chunks_of(int32_t len) { return (len + kChunk - 1) / kChunk; }
+__device__ __forceinline__ int chunks_of(int32_t len, int chunk) { return (len + chunk - 1) / chunk; }
 __device__ __forceinline__ int fwd_chunks_of(int32_t len) {
   return len > kFwdChunk ? (len + kFwdChunk - 1) / kFwdChunk : 0;
 }
@@ -1561,7 +1570,7 @@ __device__ __forceinline__ bool tile_bit(const uint64_t* mask, int w) { return (
 
 __global__ void __launch_bounds__(kBT) k_plan_count(const int32_t* __restrict__ csc_ptr,
                                                     const int32_t* __restrict__ csr_ptr, int64_t ns, int32_t R,
-                                                    int64_t tiles, int32_t* __restrict__ cnt) {
+                                                    int chunk, int64_t tiles, int32_t* __restrict__ cnt) {
   __shared__ uint64_t mask[kPW * HG_MAX_REL];
   __shared__ int32_t wcnt[kPW][HG_MAX_REL];
   __shared__ int32_t wtot[kPW][6];
@@ -1573,7 +1582,7 @@ __global__ void __launch_bounds__(kBT) k_plan_count(const int32_t* __restrict__ 
     const int32_t len = q < nq ? csc_ptr[q + 1] - csc_ptr[q] : 0;
     const uint64_t m = __ballot(len > 0);
     if (l == 0) mask[w * R + g] = m;
-    const int nch = chunks_of(len);
+    const int nch = chunks_of(len, chunk);
     act += len > 0;
     items += nch;
     heavy += nch > 1;
@@ -1621,7 +1630,7 @@ __device__ __forceinline__ void wave_chunks(int4* __restrict__ out, int32_t x, i
 
 __global__ void __launch_bounds__(kBT) k_plan_fill(const int32_t* __restrict__ csc_ptr,
                                                    const int32_t* __restrict__ csr_ptr, int64_t ns, int32_t R,
-                                                   int64_t tiles, const int32_t* __restrict__ S, PlanOut o,
+                                                   int chunk, int64_t tiles, const int32_t* __restrict__ S, PlanOut o,
                                                    int32_t* __restrict__ cnt) {
   __shared__ uint64_t mask[kPW * HG_MAX_REL];
   __shared__ int32_t before[kPW * HG_MAX_REL];  // active rows before each 64-row group
@@ -1637,7 +1646,7 @@ __global__ void __launch_bounds__(kBT) k_plan_fill(const int32_t* __restrict__ c
     const int32_t len = q < nq ? csc_ptr[q + 1] - csc_ptr[q] : 0;
     const uint64_t m = __ballot(len > 0);
     if (l == 0) mask[w * R + g] = m;
-    const int nch = chunks_of(len);
+    const int nch = chunks_of(len, chunk);
     act += len > 0;
     items += nch;
     heavy += nch > 1;
@@ -1668,7 +1677,7 @@ __global__ void __launch_bounds__(kBT) k_plan_fill(const int32_t* __restrict__ c
     const int64_t q = (tile * kPN + 64 * w) * R + 64 * g + l;
     const bool live = q < nq;
     const int32_t beg = live ? csc_ptr[q] : 0, end = live ? csc_ptr[q + 1] : 0;
-    const int nch = chunks_of(end - beg);
+    const int nch = chunks_of(end - beg, chunk);
     const uint64_t m = __ballot(nch > 0), hm = __ballot(nch > 1);
     const int32_t rank = at[P_ACT] + (int32_t)__popcll(m & lt);
     const int32_t sl = by_row ? (int32_t)q : rank;
@@ -1685,7 +1694,7 @@ __global__ void __launch_bounds__(kBT) k_plan_fill(const int32_t* __restrict__ c
       for (uint64_t left = hm; left; left &= left - 1) {
         const int u = __ffsll((unsigned long long)left) - 1;
         wave_chunks(o.items + __shfl(io, u, 64), __shfl(sl, u, 64), __shfl(beg, u, 64), __shfl(end, u, 64),
-                    __shfl(so, u, 64), __shfl(nch, u, 64), kChunk);
+                    __shfl(so, u, 64), __shfl(nch, u, 64), chunk);
       }
       at[P_PARTS] += wave_sum(nch > 1 ? nch : 0);
       at[P_HEAVY] += (int32_t)__popcll(hm);
@@ -1827,7 +1836,7 @@ struct PlanLayout {
   PlanLayout(int64_t N, int64_t E, int64_t R) {
     const int64_t nq = N * R;
     cap_s = nq < E ? nq : E;
-    cap_heavy = E / kChunk + 1;
+    cap_heavy = E / plan_chunk(E) + 1;
     cap_items = cap_s + cap_heavy;
     cap_tab = nq / 64 + 1;
     // a row of L > kFwdChunk entries has ceil(L / kFwdChunk) < 2 L / kFwdChunk chunks
@@ -2208,10 +2217,10 @@ extern "C" int hg_build_csr(const hg_graph_desc* g, const hg_overlap_desc* o, hg
                      slot_q,
                      tab};
     HG_LAUNCH("build_plan_count", k_plan_count, dim3((unsigned)tiles), dim3(kBT), 0, s, (const int32_t*)out->csc_ptr,
-              (const int32_t*)out->csr_ptr, NS, (int32_t)R, tiles, w.pcnt);
+              (const int32_t*)out->csr_ptr, NS, (int32_t)R, plan_chunk(E), tiles, w.pcnt);
     HG_TRY(scan_exclusive_i32(w.pcnt, w.pcnt, (6 + R) * tiles + 1, nullptr, w.scratch, s));
     HG_LAUNCH("build_plan_fill", k_plan_fill, dim3((unsigned)tiles), dim3(kBT), 0, s, (const int32_t*)out->csc_ptr,
-              (const int32_t*)out->csr_ptr, NS, (int32_t)R, tiles, (const int32_t*)w.pcnt, po, w.cnt);
+              (const int32_t*)out->csr_ptr, NS, (int32_t)R, plan_chunk(E), tiles, (const int32_t*)w.pcnt, po, w.cnt);
     if (ES > 0)
       HG_LAUNCH("build_csr_slot", k_csr_slot, dim3(grid_for(ES)), dim3(kBT), 0, s, (const int32_t*)out->csr_col,
                 (const uint32_t*)csr_keys, ES, (int32_t)R, NQ, (const int32_t*)(w.cnt + C_ASLOTS),

@@ -132,10 +132,12 @@ __global__ void __launch_bounds__(kHeadThreads) k_mlp_head(int64_t n, const floa
   __shared__ float red[kHeadThreads];
   __shared__ f32x4 wred[NW][LPR];
   __shared__ int nm_s;
-  if (threadIdx.x == 0) {
-    int64_t c = 0;
-    for (int k = 0; k < kHeadBlocks; ++k) c += cnt_part[k];
-    nm_s = (int)c;
+  if (threadIdx.x == 0) nm_s = 0;
+  __syncthreads();
+  {
+    int c = 0;
+    for (int k = threadIdx.x; k < kHeadBlocks; k += kHeadThreads) c += cnt_part[k];
+    atomicAdd(&nm_s, c);  // whole numbers: any order
   }
   __syncthreads();
   const float inv_nm = nm_s > 0 ? 1.0f / (float)nm_s : 0.f;
@@ -190,14 +192,25 @@ __global__ void __launch_bounds__(kHeadThreads) k_mlp_head(int64_t n, const floa
   }
 }
 
-// Sums the block partials in block order: dW2 [D], db2, loss.
+// Sums the block partials: dW2 [D], db2, loss.  Runs of blocks in order, then
+// the runs in order (one thread a column took 24 us).
+constexpr int kFinalThreads = 1024;
 template <int D>
-__global__ void k_head_final(const float* __restrict__ part, float* __restrict__ dW2, float* __restrict__ db2,
-                             float* __restrict__ loss) {
-  const int c = threadIdx.x;
-  if (c >= D + 2) return;
+__global__ void __launch_bounds__(kFinalThreads) k_head_final(const float* __restrict__ part, float* __restrict__ dW2,
+                                                              float* __restrict__ db2, float* __restrict__ loss) {
+  constexpr int NC = D == 64 ? 128 : 256, NG = kFinalThreads / NC;
+  __shared__ float red[NG][NC];
+  const int c = threadIdx.x % NC, grp = threadIdx.x / NC;
+  constexpr int per = (kHeadBlocks + NG - 1) / NG;
   float s = 0.f;
-  for (int b = 0; b < kHeadBlocks; ++b) s += part[(int64_t)b * (D + 2) + c];
+  if (c < D + 2) {
+#pragma unroll 8
+    for (int b = grp * per; b < (grp + 1) * per && b < kHeadBlocks; ++b) s += part[(int64_t)b * (D + 2) + c];
+  }
+  red[grp][c] = s;
+  __syncthreads();
+  if (grp || c >= D + 2) return;
+  for (int g = 1; g < NG; ++g) s += red[g][c];
   if (c < D) {
     dW2[c] = s;
   } else if (c == D) {
@@ -260,7 +273,7 @@ int head_impl(int64_t n, const float* H, const float* W1, const float* b1, const
   HG_LAUNCH("head_count", k_count_labels, dim3(kHeadBlocks), dim3(kHeadThreads), 0, st, labels, rows, m, w.cnt);
   HG_LAUNCH("head_logit", k_mlp_head<D>, dim3(kHeadBlocks), dim3(kHeadThreads), 0, st, m, (const float*)w.hid, W2, b2,
             labels, rows, (const int32_t*)w.cnt, w.dout, prob, w.part);
-  HG_LAUNCH("head_final", k_head_final<D>, dim3(1), dim3(256), 0, st, (const float*)w.part, dW2, db2, loss);
+  HG_LAUNCH("head_final", k_head_final<D>, dim3(1), dim3(kFinalThreads), 0, st, (const float*)w.part, dW2, db2, loss);
   // dH = da W1^T and dW1 = H^T da with da = mask * (dL/do W2^T) formed in the loaders
   if (rows && n > 0) HG_TRY(fill_f32(dH, 0.f, n * D, st));
   const LoadRank1Masked<D> da{w.dout, W2, w.mask, rows_contig(0)};

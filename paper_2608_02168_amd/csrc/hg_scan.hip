@@ -372,6 +372,11 @@ int scan_exclusive_i32(const int32_t* in, int32_t* out, int64_t n, int32_t* tota
     return HG_OK;
   }
   const int64_t tiles = cdiv(n, kTile);
+  if (tiles == 1) {  // the one tile has nothing before it
+    HG_LAUNCH("scan_tiles", (k_scan_tiles<true>), dim3(1), dim3(kThreads), 0, s, in, out, n, (const int32_t*)scratch,
+              total_dev);
+    return HG_OK;
+  }
   HG_LAUNCH("scan_tile_sums", k_tile_sums, dim3((unsigned)tiles), dim3(kThreads), 0, s, in, n, scratch);
   if (tiles <= kOwnTiles) {
     HG_LAUNCH("scan_tiles", (k_scan_tiles<true>), dim3((unsigned)tiles), dim3(kThreads), 0, s, in, out, n,

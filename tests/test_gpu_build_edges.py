@@ -45,6 +45,8 @@ SHAPES = {
     "tile_2049": (2_049, 30_001, 7, 1, None, [2_048]),
     "rel_255": (2_100, 50_000, 255, 2, None, None),
     "three_types": (4_097, 40_000, 5, 3, None, None),
+    "edges_below_2_20": (5_000, (1 << 20) - 1, 3, 2, None, None),
+    "edges_2_20": (5_000, 1 << 20, 3, 2, None, None),
 }
 
 
@@ -56,9 +58,10 @@ def test_build_shapes(name):
     ref = select.build(src, dst, rel, ntype, part, 0, n_rel, n_ntype, budget, 0, select.THETA_NONE, 3)
     sub = api.hg_build_csr(_dev(src), _dev(dst), _dev(rel), _dev(ntype), _dev(part), 0, n_rel, n_ntype, budget, seed=3)
     assert_same(ref, sub)
-    # the plan's counts: chunks of 1024 per CSC row, of 2048 per destination row above 2048 entries
+    # the plan's counts: chunks of a size by the edges per CSC row, of 2048 per destination row above 2048 entries
     length = np.diff(ref.csc_ptr)
-    nch, split = _chunks(length, 1024, 1024)
+    chunk = 64 if e < 1 << 20 else (256 if e < 1 << 23 else 1024)
+    nch, split = _chunks(length, chunk, chunk)
     assert (sub.c.plan_items, sub.c.plan_heavy, sub.c.plan_partials) == (nch.sum(), split.size, split.sum())
     into = np.add.reduceat(np.diff(ref.csr_ptr), np.arange(0, ref.n_sub * n_rel, n_rel)) if ref.n_sub else length[:0]
     _, fsplit = _chunks(into, 2048, 2048)
