@@ -39,6 +39,33 @@ __host__ __device__ inline int plan_chunk(int64_t E) {
   return E < ((int64_t)1 << 20) ? 64 : (E < ((int64_t)1 << 23) ? 256 : 1024);
 }
 
+// How the long rows of the CSC are cut into work items.  A row of up to
+// `whole` entries is one item; one of more is m * blocks pieces of equal
+// length, m = ceil(len / (chunk * blocks)), laid out block by block: the b-th
+// m pieces of every split row stand together.
+//
+// A row's entries ascend by destination and the rows draw on the same
+// destinations, so the pieces of one block gather from one part of the
+// destinations' rows: of kBlockNodes nodes, 128 MB at 512 bytes a row, half of
+// the Infinity Cache.  Gathers of 512-byte rows run at 9.3 TB/s from 64 MB,
+// 7.2 from 256 MB and 4.5 from 2.5 GB and more; blocks of 128k and 512k nodes
+// measured 0-3 % slower.  A piece costs a float64 partial row written and read
+// (2 KB at d = 128), so a row is split only into pieces of kMinPiece entries
+// and more (16 and 32 measured 0-3 % slower).  Destinations that fit one block
+// are gathered from the cache as they are: rows are cut by length alone.
+struct PlanCut {
+  int32_t chunk, blocks, whole;
+};
+constexpr int64_t kBlockNodes = (int64_t)1 << 18;
+constexpr int32_t kMaxBlocks = 128;
+constexpr int32_t kMinPiece = 24;
+
+inline PlanCut plan_cut(int64_t E, int64_t ns) {
+  const int32_t chunk = plan_chunk(E);
+  const int32_t blocks = (int32_t)std::max<int64_t>(1, std::min<int64_t>(cdiv(ns, kBlockNodes), kMaxBlocks));
+  return {chunk, blocks, blocks == 1 ? chunk : kMinPiece * blocks - 1};
+}
+
 inline unsigned grid_for(int64_t n, int64_t cap = 16384) {
   int64_t b = cdiv(n > 0 ? n : 1, kBT);
   return (unsigned)(b < cap ? b : cap);
@@ -1531,7 +1558,7 @@ __global__ void k_gather_w(const int32_t* __restrict__ eid, const float* __restr
 // ---- execution plan -----------------------------------------------------------
 // Tiles of kPN consecutive nodes (kPN * R rows of the CSC: whole 64-row groups
 // of the slot table).  k_plan_count writes, per tile, the number of active
-// rows, work items, split rows and their chunks, the long destination rows and
+// rows, whole rows, split rows and their pieces per block, the long destination rows and
 // their chunks, and the active sources of every relation, as 6 + R streams of
 // one count per tile laid end to end; one scan of the whole turns a stream's
 // entry minus its first into the tile's offset (sums may wrap, differences do
@@ -1541,7 +1568,7 @@ __global__ void k_gather_w(const int32_t* __restrict__ eid, const float* __restr
 // partition by relation took 1.6 ms at 50M rows where this takes 0.3 ms.
 constexpr int kPN = kBT;
 constexpr int kPW = kPN / 64;
-enum : int { P_ACT = 0, P_ITEMS, P_HEAVY, P_PARTS, P_FHEAVY, P_FPARTS, P_REL };
+enum : int { P_ACT = 0, P_WHOLE, P_HEAVY, P_PARTS, P_FHEAVY, P_FPARTS, P_REL };
 
 __device__ __forceinline__ int wave_sum(int v) {
 #pragma unroll
@@ -1560,7 +1587,10 @@ __device__ __forceinline__ int wave_before(int v) {
   return inc - v;
 }
 
-__device__ __forceinline__ int chunks_of(int32_t len, int chunk) { return (len + chunk - 1) / chunk; }
+// Items of a row per block: 0 for a row that is one item or none.
+__device__ __forceinline__ int cuts_of(int32_t len, PlanCut k) {
+  return len > k.whole ? (len + k.chunk * k.blocks - 1) / (k.chunk * k.blocks) : 0;
+}
 __device__ __forceinline__ int fwd_chunks_of(int32_t len) {
   return len > kFwdChunk ? (len + kFwdChunk - 1) / kFwdChunk : 0;
 }
@@ -1570,27 +1600,27 @@ __device__ __forceinline__ bool tile_bit(const uint64_t* mask, int w) { return (
 
 __global__ void __launch_bounds__(kBT) k_plan_count(const int32_t* __restrict__ csc_ptr,
                                                     const int32_t* __restrict__ csr_ptr, int64_t ns, int32_t R,
-                                                    int chunk, int64_t tiles, int32_t* __restrict__ cnt) {
+                                                    PlanCut cut, int64_t tiles, int32_t* __restrict__ cnt) {
   __shared__ uint64_t mask[kPW * HG_MAX_REL];
   __shared__ int32_t wcnt[kPW][HG_MAX_REL];
   __shared__ int32_t wtot[kPW][6];
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
   const int64_t tile = blockIdx.x, nq = ns * R;
-  int act = 0, items = 0, heavy = 0, parts = 0;
+  int act = 0, whole = 0, heavy = 0, parts = 0;
   for (int g = 0; g < R; ++g) {  // the wave's 64 nodes: R groups of 64 rows
     const int64_t q = (tile * kPN + 64 * w) * R + 64 * g + l;
     const int32_t len = q < nq ? csc_ptr[q + 1] - csc_ptr[q] : 0;
     const uint64_t m = __ballot(len > 0);
     if (l == 0) mask[w * R + g] = m;
-    const int nch = chunks_of(len, chunk);
+    const int m_row = cuts_of(len, cut);
     act += len > 0;
-    items += nch;
-    heavy += nch > 1;
-    parts += nch > 1 ? nch : 0;
+    whole += len > 0 && m_row == 0;
+    heavy += m_row > 0;
+    parts += m_row;
   }
   const int64_t j = tile * kPN + threadIdx.x;
   const int fch = j < ns ? fwd_chunks_of(csr_ptr[(j + 1) * R] - csr_ptr[j * R]) : 0;
-  const int v[6] = {act, items, heavy, parts, fch > 0, fch};
+  const int v[6] = {act, whole, heavy, parts, fch > 0, fch};
 #pragma unroll
   for (int i = 0; i < 6; ++i) {
     const int t = wave_sum(v[i]);
@@ -1618,7 +1648,7 @@ struct PlanOut {
   SlotEnt* tab;
 };
 
-// Chunks of a split row by all lanes: item (x, begin, end, partial slot) c of
+// Chunks of a long destination row by all lanes: item (x, begin, end, partial slot) c of
 // the row at out[c].
 __device__ __forceinline__ void wave_chunks(int4* __restrict__ out, int32_t x, int32_t beg, int32_t end, int32_t so,
                                             int nch, int chunk) {
@@ -1628,9 +1658,23 @@ __device__ __forceinline__ void wave_chunks(int4* __restrict__ out, int32_t x, i
   }
 }
 
+// Pieces of a split CSC row by all lanes: piece c = b * m + i of its m * blocks
+// goes to place b * per_block + first + i of the items, its partial row is
+// first * blocks + c.
+__device__ __forceinline__ void wave_pieces(int4* __restrict__ items, int32_t per_block, int32_t sl, int32_t beg,
+                                            int32_t end, int32_t first, int m, int blocks) {
+  const int n = m * blocks;
+  const int64_t len = end - beg;
+  for (int c = threadIdx.x & 63; c < n; c += 64) {
+    const int b = c / m;
+    items[(int64_t)b * per_block + first + (c - b * m)] =
+        make_int4(sl, beg + (int32_t)(len * c / n), beg + (int32_t)(len * (c + 1) / n), first * blocks + c);
+  }
+}
+
 __global__ void __launch_bounds__(kBT) k_plan_fill(const int32_t* __restrict__ csc_ptr,
                                                    const int32_t* __restrict__ csr_ptr, int64_t ns, int32_t R,
-                                                   int chunk, int64_t tiles, const int32_t* __restrict__ S, PlanOut o,
+                                                   PlanCut cut, int64_t tiles, const int32_t* __restrict__ S, PlanOut o,
                                                    int32_t* __restrict__ cnt) {
   __shared__ uint64_t mask[kPW * HG_MAX_REL];
   __shared__ int32_t before[kPW * HG_MAX_REL];  // active rows before each 64-row group
@@ -1640,22 +1684,22 @@ __global__ void __launch_bounds__(kBT) k_plan_fill(const int32_t* __restrict__ c
   const uint64_t lt = (l == 0) ? 0ull : (~0ull >> (64 - l));
   const int64_t tile = blockIdx.x, nq = ns * R;
   const bool by_row = row_layout(nq, S[tiles] - S[0]);
-  int act = 0, items = 0, heavy = 0, parts = 0;
+  int act = 0, whole = 0, heavy = 0, parts = 0;
   for (int g = 0; g < R; ++g) {
     const int64_t q = (tile * kPN + 64 * w) * R + 64 * g + l;
     const int32_t len = q < nq ? csc_ptr[q + 1] - csc_ptr[q] : 0;
     const uint64_t m = __ballot(len > 0);
     if (l == 0) mask[w * R + g] = m;
-    const int nch = chunks_of(len, chunk);
+    const int m_row = cuts_of(len, cut);
     act += len > 0;
-    items += nch;
-    heavy += nch > 1;
-    parts += nch > 1 ? nch : 0;
+    whole += len > 0 && m_row == 0;
+    heavy += m_row > 0;
+    parts += m_row;
   }
   const int64_t j = tile * kPN + threadIdx.x;
   const int32_t fbeg = j < ns ? csr_ptr[j * R] : 0, fend = j < ns ? csr_ptr[(j + 1) * R] : 0;
   const int fch = fwd_chunks_of(fend - fbeg);
-  const int v[6] = {act, items, heavy, parts, fch > 0, fch};
+  const int v[6] = {act, whole, heavy, parts, fch > 0, fch};
 #pragma unroll
   for (int i = 0; i < 6; ++i) {
     const int t = wave_sum(v[i]);
@@ -1667,6 +1711,7 @@ __global__ void __launch_bounds__(kBT) k_plan_fill(const int32_t* __restrict__ c
     if (l == 0) wcnt[w][r] = (int32_t)__popcll(m);
   }
   __syncthreads();
+  const int32_t per_block = S[4 * tiles] - S[3 * tiles];  // pieces of each block
   int32_t at[6];  // the wave's offset in each stream
 #pragma unroll
   for (int i = 0; i < 6; ++i) {
@@ -1677,30 +1722,31 @@ __global__ void __launch_bounds__(kBT) k_plan_fill(const int32_t* __restrict__ c
     const int64_t q = (tile * kPN + 64 * w) * R + 64 * g + l;
     const bool live = q < nq;
     const int32_t beg = live ? csc_ptr[q] : 0, end = live ? csc_ptr[q + 1] : 0;
-    const int nch = chunks_of(end - beg, chunk);
-    const uint64_t m = __ballot(nch > 0), hm = __ballot(nch > 1);
+    const int mr = cuts_of(end - beg, cut);
+    const uint64_t m = __ballot(end > beg), hm = __ballot(mr > 0), om = m & ~hm;
     const int32_t rank = at[P_ACT] + (int32_t)__popcll(m & lt);
     const int32_t sl = by_row ? (int32_t)q : rank;
     if (l == 0) before[w * R + g] = at[P_ACT];
     if (!by_row) {
-      if (nch > 0) o.slot_q[rank] = (int32_t)q;
+      if (end > beg) o.slot_q[rank] = (int32_t)q;
       if (l == 0 && live) o.tab[q >> 6] = SlotEnt{m, at[P_ACT], 0};
     }
-    const int32_t io = at[P_ITEMS] + wave_before(nch);
-    if (nch == 1) o.items[io] = make_int4(sl, beg, end, -1);
+    // the pieces of the split rows come first, block by block
+    if (end > beg && mr == 0)
+      o.items[per_block * cut.blocks + at[P_WHOLE] + (int32_t)__popcll(om & lt)] = make_int4(sl, beg, end, -1);
     if (hm) {
-      const int32_t so = at[P_PARTS] + wave_before(nch > 1 ? nch : 0);
-      if (nch > 1) o.heavy[at[P_HEAVY] + (int32_t)__popcll(hm & lt)] = make_int4(sl, so, nch, 0);
+      const int32_t so = at[P_PARTS] + wave_before(mr);
+      if (mr > 0) o.heavy[at[P_HEAVY] + (int32_t)__popcll(hm & lt)] = make_int4(sl, so * cut.blocks, mr * cut.blocks, 0);
       for (uint64_t left = hm; left; left &= left - 1) {
         const int u = __ffsll((unsigned long long)left) - 1;
-        wave_chunks(o.items + __shfl(io, u, 64), __shfl(sl, u, 64), __shfl(beg, u, 64), __shfl(end, u, 64),
-                    __shfl(so, u, 64), __shfl(nch, u, 64), chunk);
+        wave_pieces(o.items, per_block, __shfl(sl, u, 64), __shfl(beg, u, 64), __shfl(end, u, 64), __shfl(so, u, 64),
+                    __shfl(mr, u, 64), cut.blocks);
       }
-      at[P_PARTS] += wave_sum(nch > 1 ? nch : 0);
+      at[P_PARTS] += wave_sum(mr);
       at[P_HEAVY] += (int32_t)__popcll(hm);
     }
     at[P_ACT] += (int32_t)__popcll(m);
-    at[P_ITEMS] += hm ? wave_sum(nch) : (int32_t)__popcll(m);
+    at[P_WHOLE] += (int32_t)__popcll(om);
   }
   // active sources of every relation, ascending, with their slots
   __builtin_amdgcn_wave_barrier();
@@ -1734,9 +1780,9 @@ __global__ void __launch_bounds__(kBT) k_plan_fill(const int32_t* __restrict__ c
       o.act_off[r] = o.act_off_copy[r] = S[(int64_t)(P_REL + r) * tiles] - S[(int64_t)P_REL * tiles];
     if (threadIdx.x == 0) {
       cnt[C_ASLOTS] = S[tiles] - S[0];
-      cnt[C_ITEMS] = S[2 * tiles] - S[tiles];
+      cnt[C_ITEMS] = S[2 * tiles] - S[tiles] + per_block * cut.blocks;
       cnt[C_HEAVY] = S[3 * tiles] - S[2 * tiles];
-      cnt[C_PARTS] = S[4 * tiles] - S[3 * tiles];
+      cnt[C_PARTS] = per_block * cut.blocks;
       cnt[C_FHEAVY] = S[5 * tiles] - S[4 * tiles];
       cnt[C_FPARTS] = S[6 * tiles] - S[5 * tiles];
     }
@@ -1836,8 +1882,10 @@ struct PlanLayout {
   PlanLayout(int64_t N, int64_t E, int64_t R) {
     const int64_t nq = N * R;
     cap_s = nq < E ? nq : E;
-    cap_heavy = E / plan_chunk(E) + 1;
-    cap_items = cap_s + cap_heavy;
+    // in blocks: a split row of L entries has 2 kMinPiece <= L, and at most L / kMinPiece + L / chunk pieces;
+    // in one: chunk < L, and less than 2 L / chunk
+    cap_heavy = E / std::min(plan_chunk(E), 2 * kMinPiece) + 1;
+    cap_items = cap_s + E / kMinPiece + 2 * (E / plan_chunk(E)) + 2;
     cap_tab = nq / 64 + 1;
     // a row of L > kFwdChunk entries has ceil(L / kFwdChunk) < 2 L / kFwdChunk chunks
     cap_fheavy = E / kFwdChunk + 1;
@@ -2206,6 +2254,7 @@ extern "C" int hg_build_csr(const hg_graph_desc* g, const hg_overlap_desc* o, hg
   SlotEnt* tab = reinterpret_cast<SlotEnt*>(pb + pl.tab_off);
   if (NQ > 0) {
     const int64_t tiles = cdiv(NS, kPN);
+    const PlanCut cut = plan_cut(E, NS);
     const PlanOut po{items,
                      heavy,
                      reinterpret_cast<int4*>(pb + pl.fitems_off),
@@ -2217,10 +2266,10 @@ extern "C" int hg_build_csr(const hg_graph_desc* g, const hg_overlap_desc* o, hg
                      slot_q,
                      tab};
     HG_LAUNCH("build_plan_count", k_plan_count, dim3((unsigned)tiles), dim3(kBT), 0, s, (const int32_t*)out->csc_ptr,
-              (const int32_t*)out->csr_ptr, NS, (int32_t)R, plan_chunk(E), tiles, w.pcnt);
+              (const int32_t*)out->csr_ptr, NS, (int32_t)R, cut, tiles, w.pcnt);
     HG_TRY(scan_exclusive_i32(w.pcnt, w.pcnt, (6 + R) * tiles + 1, nullptr, w.scratch, s));
     HG_LAUNCH("build_plan_fill", k_plan_fill, dim3((unsigned)tiles), dim3(kBT), 0, s, (const int32_t*)out->csc_ptr,
-              (const int32_t*)out->csr_ptr, NS, (int32_t)R, plan_chunk(E), tiles, (const int32_t*)w.pcnt, po, w.cnt);
+              (const int32_t*)out->csr_ptr, NS, (int32_t)R, cut, tiles, (const int32_t*)w.pcnt, po, w.cnt);
     if (ES > 0)
       HG_LAUNCH("build_csr_slot", k_csr_slot, dim3(grid_for(ES)), dim3(kBT), 0, s, (const int32_t*)out->csr_col,
                 (const uint32_t*)csr_keys, ES, (int32_t)R, NQ, (const int32_t*)(w.cnt + C_ASLOTS),

@@ -705,7 +705,8 @@ __global__ void k_dmu_rows(int64_t n_rows, int32_t R, int32_t T, const int32_t* 
 // two heads would spill there.
 template <int D, int S>
 __global__ void __launch_bounds__(kAttnThreads, S >= 4 ? 4 : 1) k_hgt_attn_bwd_src(
-    int64_t n_items, const int4* __restrict__ items, const int32_t* __restrict__ slot_q, int32_t R, int32_t T,
+    int64_t n_pieces, int64_t n_items, int32_t piece_blocks, const int4* __restrict__ items,
+    const int32_t* __restrict__ slot_q, int32_t R, int32_t T,
     const int32_t* __restrict__ type_off,
     const int32_t* __restrict__ csc_row, const float* __restrict__ Q, const float* __restrict__ Kt,
     const float* __restrict__ Vt, const float* __restrict__ dht, const float* __restrict__ ld,
@@ -714,9 +715,8 @@ __global__ void __launch_bounds__(kAttnThreads, S >= 4 ? 4 : 1) k_hgt_attn_bwd_s
   constexpr int LPR = D / 4, EPW = 64 / LPR, DK = D / S, LPH = DK / 4, U = 4;
   const int l = threadIdx.x & 63;
   const int slot = l / LPR, lr = l % LPR, c0 = lr * 4, head = lr / LPH;
-  const int64_t wave0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-  for (int64_t it = wave0; it < n_items; it += nwaves) {
+  const ItemRange ir = item_range(n_pieces, n_items, piece_blocks);
+  for (int64_t it = ir.at; it < ir.end; it += ir.step) {
     const int4 item = items[it];
     const int64_t srow = item.x;
     const int32_t qrow = slot_q ? slot_q[srow] : (int32_t)srow;
@@ -1263,6 +1263,7 @@ int hgt_bwd_impl(const hg_subgraph* s, const hg_hgt_desc* L, const float* Hin, c
                                          StoreRows<D, float>{w.dht, rows_contig(lo), nullptr, nullptr}, st)));
   }
   // (2) destination pass, (3) source pass
+  const ItemGrid ig = item_grid(s, 32);
   if (s->n_sub > 0) {
 #define HG_ATTN_BWD(S_)                                                                                               \
   do {                                                                                                                \
@@ -1280,8 +1281,8 @@ int hgt_bwd_impl(const hg_subgraph* s, const hg_hgt_desc* L, const float* Hin, c
                 (int64_t)s->plan_fwd_heavy, pv.fwd_heavy, (const float*)w.pdq, w.dQ);                                 \
     }                                                                                                                 \
     if (s->plan_items > 0)                                                                                            \
-      HG_LAUNCH("hgt_attn_bwd_src", (k_hgt_attn_bwd_src<D, S_>), dim3(attn_grid(s->plan_items)), dim3(kAttnThreads),  \
-                0, st, (int64_t)s->plan_items, pv.items, pv.slot_q, R, T, (const int32_t*)s->type_off,                \
+      HG_LAUNCH("hgt_attn_bwd_src", (k_hgt_attn_bwd_src<D, S_>), dim3((unsigned)ig.blocks), dim3(kAttnThreads),       \
+                0, st, (int64_t)s->plan_partials, (int64_t)s->plan_items, ig.pieces, pv.items, pv.slot_q, R, T, (const int32_t*)s->type_off,                \
                 (const int32_t*)s->csc_row, (const float*)sv.Q, Kt, Vt,                                               \
                 (const float*)w.dht, (const float*)w.ld, W->mu, inv_sqrt_dk, w.dKt, w.dVt,                            \
                 w.pk, w.pv);                                                                                          \

@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <cstdio>
 #include <string>
@@ -78,6 +79,38 @@ struct Sizer {
 };
 
 int num_cus();
+
+// Blocks (of four waves) of a pass over the plan's backward items: `pieces` of
+// them take the pieces of split rows, one wave each and in order, so that at
+// any time these waves gather from one block of destinations; the others, at
+// least per_cu per compute unit, take the whole rows in strides.  The two kinds
+// alternate in proportion (four row blocks to a piece block where there are
+// rows for that): the whole rows' gathers wait on HBM, the pieces' on the
+// Infinity Cache.  Mean backward over 200M edges of 10M nodes (d = 128,
+// float32): 36.0 ms with 1024-entry pieces in row order, 33.1 with the pieces
+// in blocks before the rows, 30.3 alternating.
+struct ItemGrid {
+  int32_t pieces, blocks;
+};
+inline ItemGrid item_grid(const hg_subgraph* s, int per_cu) {
+  const int64_t pb = std::min(cdiv(s->plan_partials, 4), (int64_t)1 << 20);
+  const int64_t rb = std::min(cdiv(s->plan_items - s->plan_partials, 4), std::max((int64_t)num_cus() * per_cu, 4 * pb));
+  return {(int32_t)pb, (int32_t)(pb + rb)};
+}
+
+// The items of this wave in such a launch: at, at + step, ... below end.
+struct ItemRange {
+  int64_t at, end, step;
+};
+__device__ __forceinline__ ItemRange item_range(int64_t n_pieces, int64_t n_items, int32_t piece_blocks) {
+  const int64_t w = threadIdx.x >> 6;
+  const uint32_t b = blockIdx.x, n = gridDim.x;
+  // piece blocks before b
+  const uint32_t pb = (uint32_t)((uint64_t)b * (uint32_t)piece_blocks / n);
+  const bool piece = (uint32_t)(((uint64_t)b + 1) * (uint32_t)piece_blocks / n) > pb;
+  if (piece) return {4 * (int64_t)pb + w, n_pieces, 4 * (int64_t)piece_blocks};
+  return {n_pieces + 4 * (int64_t)(b - pb) + w, n_items, 4 * ((int64_t)n - piece_blocks)};
+}
 
 // Slots of the relation transforms.  The active (source, relation) pairs --
 // the CSC rows q = i * R + r that hold at least one entry -- are numbered

@@ -237,7 +237,8 @@ __global__ void __launch_bounds__(256) k_spmm_fwd_merge(int64_t n_heavy, const i
 // accumulates in float64 (the kernel is bound by the gathers, not the adds);
 // split rows keep float64 partial rows.
 template <int D, class T, class TO>
-__global__ void __launch_bounds__(256, (sizeof(T) == 2 || D <= 128) ? 8 : 4) k_spmm_bwd(int64_t n_items, const int4* __restrict__ items,
+__global__ void __launch_bounds__(256, (sizeof(T) == 2 || D <= 128) ? 8 : 4) k_spmm_bwd(int64_t n_pieces, int64_t n_items, int32_t piece_blocks,
+                                                  const int4* __restrict__ items,
                                                   const int32_t* __restrict__ csc_row,
                                                   const float* __restrict__ csc_scale,
                                                   const T* __restrict__ dZ,
@@ -249,11 +250,10 @@ __global__ void __launch_bounds__(256, (sizeof(T) == 2 || D <= 128) ? 8 : 4) k_s
   const int l = threadIdx.x & 63;
   const int slot = l / LPR;
   const int c0 = (l % LPR) * EL;
-  const int64_t wave0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
+  const ItemRange ir = item_range(n_pieces, n_items, piece_blocks);
   if constexpr (sizeof(T) == 4) {
     // float32 rows: one float4 per lane, float64 accumulators (54 VGPRs)
-    for (int64_t it = wave0; it < n_items; it += nwaves) {
+    for (int64_t it = ir.at; it < ir.end; it += ir.step) {
       const int4 item = items[it];
       const int32_t beg = item.y, end = item.z;
       f64x4 acc = {0.0, 0.0, 0.0, 0.0};
@@ -308,7 +308,7 @@ __global__ void __launch_bounds__(256, (sizeof(T) == 2 || D <= 128) ? 8 : 4) k_s
   } else {
     // bf16 rows: the gathered chunks stay packed until the float64 adds
     // (<= 64 VGPRs, 8 waves per SIMD as for float32 rows)
-    for (int64_t it = wave0; it < n_items; it += nwaves) {
+    for (int64_t it = ir.at; it < ir.end; it += ir.step) {
       const int4 item = items[it];
       const int32_t beg = item.y, end = item.z;
       double acc[EL];
@@ -570,10 +570,12 @@ int layer_bwd_impl(const hg_subgraph* s, const hg_layer_desc* L, const T* Hin, c
     }
   }
   // (b) transposed SpMM into float32 dY
-  if (s->plan_items > 0)
-    HG_LAUNCH("spmm_bwd", (k_spmm_bwd<D, T, float>), dim3(wave_grid(s->plan_items)), dim3(256), 0, st,
-              (int64_t)s->plan_items, pv.items, (const int32_t*)s->csc_row, (const float*)s->csc_scale,
-              (const T*)w.dZ, w.dY, w.part);
+  if (s->plan_items > 0) {
+    const ItemGrid ig = item_grid(s, 64);
+    HG_LAUNCH("spmm_bwd", (k_spmm_bwd<D, T, float>), dim3((unsigned)ig.blocks), dim3(256), 0, st,
+              (int64_t)s->plan_partials, (int64_t)s->plan_items, ig.pieces, pv.items, (const int32_t*)s->csc_row,
+              (const float*)s->csc_scale, (const T*)w.dZ, w.dY, w.part);
+  }
   if (s->plan_heavy > 0)
     HG_LAUNCH("spmm_bwd_reduce", (k_heavy_reduce<D, float>), dim3(wave_grid(s->plan_heavy)), dim3(256), 0, st,
               (int64_t)s->plan_heavy, pv.heavy, (const double*)w.part, w.dY);
