@@ -9,10 +9,16 @@
 // registers in the MFMA output layout (lane (c, g) holds row c, columns
 // 16 b + 4 g .. + 3 of column block b), which is also the layout the MFMA
 // takes its row operand in, so one product feeds the next without a trip
-// through LDS.  The seven 64 x 64 weights sit in LDS row-major with a row
-// pitch of 68 floats: a lane reads a fragment of W as four 4-byte words
-// (op(W) = W) and a fragment of W^T as one 16-byte word (op(W) = W^T), both
-// without bank conflicts, so one copy serves products with W and with W^T.
+// through LDS.  The seven 64 x 64 weights sit in LDS as two fp16 planes each
+// (the high parts and the remainders), row-major with a row pitch of 72
+// halves.  A fragment of W^T is read along rows as 8-byte words, a fragment of
+// W down columns by the transposing 8-byte read of the LDS, both nearly free of
+// bank conflicts, so one copy serves products with W and with W^T and no
+// operand is regrouped by vector instructions: those, and not the matrix
+// cores, bounded the forward when a word held a weight's two parts (0.57 ms at
+// a million rows and w = 3, now 0.45; its rows take 0.26 at 5 TB/s).  A row
+// that several products share is split once.  The backward moves 23 rows of 256
+// bytes each, 1.2 ms at 5 TB/s (1.41 before, now 1.33).
 //
 // The backward recomputes the forward in registers (nothing is saved between
 // the two calls), forms dh, dHt and dC_k in the same pass and writes the gate
@@ -24,11 +30,12 @@ namespace hg {
 namespace {
 
 constexpr int kTD = 64;          // state width d
-constexpr int kTP = 68;          // LDS row pitch (floats) of a staged 64 x 64 matrix
+constexpr int kTP = 72;          // LDS row pitch (halves) of a plane of a staged 64 x 64 matrix
 constexpr int kTMaxW = 4;        // longest context
 constexpr int kTThreads = 512;
 constexpr int kTWaves = kTThreads / 64;
-constexpr int kTMat = kTD * kTP;
+constexpr int kTPlane = kTD * kTP;  // halves of a plane; a matrix is two, kTMat floats in all
+constexpr int kTMat = kTPlane;
 constexpr int kTVec = 7 * kTMat;  // then r, bi0 + bh0, bi1 + bh1, bi2, bh2
 constexpr int kTUnscale = kTVec + 5 * kTD;  // then the 7 matrices' unscale factors
 constexpr size_t kTLds = sizeof(float) * (7 * kTMat + 5 * kTD + 8);
@@ -47,9 +54,8 @@ struct TCtxOut {
 
 // LDS: Q, Wi[0..2], Wh[0..2] (row-major, pitch kTP), each scaled by the
 // power of two that brings its largest magnitude into [2^14, 2^15) and held
-// as split-fp16 pairs (one 32-bit word per weight: the fp16 high part, then
-// the fp16 remainder; see t_gemm), then the vectors, then the 7 factors that
-// undo the scalings.
+// as a plane of fp16 high parts and a plane of fp16 remainders (see t_mul),
+// then the vectors, then the 7 factors that undo the scalings.
 __device__ __forceinline__ void t_stage(float* lds, const TParams& p) {
   constexpr int kDD = kTD * kTD;
   __shared__ float wmax[kTWaves][7];
@@ -68,19 +74,21 @@ __device__ __forceinline__ void t_stage(float* lds, const TParams& p) {
     }
   }
   __syncthreads();
-  uint32_t* wl = reinterpret_cast<uint32_t*>(lds);
-  for (int e = threadIdx.x; e < 7 * kDD; e += kTThreads) {
+  uint16_t* wl = reinterpret_cast<uint16_t*>(lds);
+  for (int e = 2 * threadIdx.x; e < 7 * kDD; e += 2 * kTThreads) {  // two columns of a row
     const int m = e / kDD, ij = e - m * kDD;
     float mx = wmax[0][m];
 #pragma unroll
     for (int q = 1; q < kTWaves; ++q) mx = fmaxf(mx, wmax[q][m]);
-    // the scaled weight as its fp16 high part (low half) and the fp16
-    // remainder (high half), as split8 forms them
-    const float v = src_of(m)[ij] * split_scale(split_exp(mx));
-    const auto hp = __builtin_amdgcn_cvt_pkrtz(v, 0.f);
-    const auto lp = __builtin_amdgcn_cvt_pkrtz(v - (float)hp[0], 0.f);
-    wl[m * kTMat + (ij / kTD) * kTP + (ij % kTD)] =
-        (__builtin_bit_cast(uint32_t, hp) & 0xFFFFu) | (__builtin_bit_cast(uint32_t, lp) << 16);
+    // the scaled weight's fp16 high part and the fp16 remainder, as split8 forms them
+    const float sc = split_scale(split_exp(mx));
+    const float* w = src_of(m) + ij;
+    const float v0 = w[0] * sc, v1 = w[1] * sc;
+    const auto hp = __builtin_amdgcn_cvt_pkrtz(v0, v1);
+    const auto lp = __builtin_amdgcn_cvt_pkrtz(v0 - (float)hp[0], v1 - (float)hp[1]);
+    const int at = 2 * m * kTPlane + (ij / kTD) * kTP + (ij % kTD);
+    *reinterpret_cast<uint32_t*>(wl + at) = __builtin_bit_cast(uint32_t, hp);
+    *reinterpret_cast<uint32_t*>(wl + at + kTPlane) = __builtin_bit_cast(uint32_t, lp);
   }
   if (threadIdx.x < 7) {
     float mx = wmax[0][threadIdx.x];
@@ -101,26 +109,30 @@ __device__ __forceinline__ void t_stage(float* lds, const TParams& p) {
   __syncthreads();
 }
 
+// The vectors in LDS, by an address that the compiler cannot follow: the reads
+// would otherwise move out of the backward's loop over row tiles, and their 80
+// registers into scratch memory (152 bytes a lane at w = 3, now 92; the pass
+// over a million rows takes 1.33 ms, 1.44 with them).  The forward has the
+// registers (0.45 ms, 0.47 reading them for every tile).
+__device__ __forceinline__ const float* t_vectors(const float* lds) {
+  int at = kTVec;
+  asm volatile("" : "+s"(at));
+  return lds + at;
+}
+
 __device__ __forceinline__ f32x4 t_vec4(const float* v, int col) { return *reinterpret_cast<const f32x4*>(v + col); }
 
-// acc += x . op(M) for the 64 x 64 matrix M = matrix mat in LDS (scaled, see
-// t_stage; its factor undoes the scaling) on the split-fp16 MFMA (v_mfma_f32_16x16x32_f16,
-// three products per K block: the high parts of both factors and each
-// factor's remainder against the other's high part, as in the row GEMMs).
-// The row is scaled by the power of two of its largest magnitude (the four
-// lanes of row c agree by two xor shuffles).  K block kb2 of 32 takes the
-// lane's columns 16 (2 kb2) + 4 g .. + 3 (slots 0-3) and 16 (2 kb2 + 1) +
-// 4 g .. + 3 (slots 4-7); lane (c, g) supplies op(M)[k][16 nb + c] for the
-// same k and receives row c, columns 16 nb + 4 g .. + 3, the layout x is
-// held in, so one product feeds the next.  op(M) = M is read as 8 words
-// down a column, op(M) = M^T as two 16-byte words along a row (pitch 68:
-// neither conflicts); each word holds a weight's two fp16 parts, which are
-// regrouped into the MFMA's high-part and remainder operands.
-template <bool kTrans>
-__device__ __forceinline__ void t_gemm(const float* lds, int mat, const f32x4 (&x)[4], f32x4 (&acc)[4], int g,
-                                       int c) {
-  const uint32_t* M = reinterpret_cast<const uint32_t*>(lds) + mat * kTMat;
-  const float uw = lds[kTUnscale + mat];
+// A row operand of t_mul: the lane's 16 values of row c scaled by the power of
+// two of the row's largest magnitude (the four lanes of row c agree by two xor
+// shuffles) and split into fp16 high parts and remainders, and the factor that
+// undoes the scaling.  K block kb2 of 32 takes the lane's columns 16 (2 kb2) +
+// 4 g .. + 3 (slots 0-3) and 16 (2 kb2 + 1) + 4 g .. + 3 (slots 4-7).
+struct TRow {
+  uint4 h[2], l[2];
+  float un;
+};
+__device__ __forceinline__ TRow t_split(const f32x4 (&x)[4]) {
+  TRow r;
   float mx = 0.f;
 #pragma unroll
   for (int b = 0; b < 4; ++b)
@@ -129,8 +141,8 @@ __device__ __forceinline__ void t_gemm(const float* lds, int mat, const f32x4 (&
   mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
   mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
   const uint32_t ex = split_exp(mx);
-  const float sx = split_scale(ex), ux = split_unscale(ex);
-  uint4 xh[2], xl[2];
+  const float sx = split_scale(ex);
+  r.un = split_unscale(ex);
 #pragma unroll
   for (int kb2 = 0; kb2 < 2; ++kb2) {
     float v[8];
@@ -139,48 +151,66 @@ __device__ __forceinline__ void t_gemm(const float* lds, int mat, const f32x4 (&
       v[q] = x[2 * kb2][q] * sx;
       v[4 + q] = x[2 * kb2 + 1][q] * sx;
     }
-    split8(v, xh[kb2], xl[kb2]);
+    split8(v, r.h[kb2], r.l[kb2]);
   }
+  return r;
+}
+
+typedef short t_s16x4 __attribute__((ext_vector_type(4)));
+
+// Eight halves of a plane for lane (c, g): op(M)[k][16 nb + c] for the K block
+// kb2's slots.  op(M) = M^T: two 8-byte words along row 16 nb + c.  op(M) = M:
+// two transposing reads, each of 4 rows x 16 columns by the 16 lanes of g
+// (lane c names 4 columns of row c / 4 and receives column c of the 4 rows).
+template <bool kTrans>
+__device__ __forceinline__ uint4 t_frag(const uint16_t* M, int kb2, int nb, int g, int c) {
+  if constexpr (kTrans) {
+    const uint16_t* q = M + (16 * nb + c) * kTP + 32 * kb2 + 4 * g;
+    const uint2 a = *reinterpret_cast<const uint2*>(q), b = *reinterpret_cast<const uint2*>(q + 16);
+    return uint4{a.x, a.y, b.x, b.y};
+  } else {
+    typedef __attribute__((address_space(3))) t_s16x4* lds_ptr;
+    const uint16_t* q = M + (32 * kb2 + 4 * g + (c >> 2)) * kTP + 16 * nb + 4 * (c & 3);
+    const uint2 a = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(q)));
+    const uint2 b = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(q + 16 * kTP)));
+    return uint4{a.x, a.y, b.x, b.y};
+  }
+}
+
+// acc += x . op(M) for the 64 x 64 matrix M = matrix mat in LDS (scaled, see
+// t_stage; its factor undoes the scaling) on the split-fp16 MFMA (v_mfma_f32_16x16x32_f16,
+// three products per K block: the high parts of both factors and each
+// factor's remainder against the other's high part, as in the row GEMMs).
+// Lane (c, g) receives row c, columns 16 nb + 4 g .. + 3, the layout x is held
+// in, so one product feeds the next.
+template <bool kTrans>
+__device__ __forceinline__ void t_mul(const float* lds, int mat, const TRow& x, f32x4 (&acc)[4], int g, int c) {
+  const uint16_t* M = reinterpret_cast<const uint16_t*>(lds) + 2 * mat * kTPlane;
+  const float uw = lds[kTUnscale + mat];
   f32x4 t[4];
 #pragma unroll
   for (int nb = 0; nb < 4; ++nb) t[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int kb2 = 0; kb2 < 2; ++kb2) {
 #pragma unroll
-    for (int nb = 0; nb < 4; ++nb) {
-      // each fragment is read and split right before its MFMAs (hoisting
-      // them all would exhaust the registers)
+    for (int nb = 0; nb < 4; nb += 2) {
+      // two fragments are read right before their MFMAs, whose chains
+      // alternate (hoisting them all would exhaust the registers)
       __builtin_amdgcn_sched_barrier(0);
-      uint32_t w[8];
-      if constexpr (kTrans) {
-        const uint32_t* q = M + (16 * nb + c) * kTP + 32 * kb2 + 4 * g;
-        const uint4 a = *reinterpret_cast<const uint4*>(q), b = *reinterpret_cast<const uint4*>(q + 16);
-        w[0] = a.x; w[1] = a.y; w[2] = a.z; w[3] = a.w;
-        w[4] = b.x; w[5] = b.y; w[6] = b.z; w[7] = b.w;
-      } else {
-        const uint32_t* q = M + (32 * kb2 + 4 * g) * kTP + 16 * nb + c;
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          w[s] = q[s * kTP];
-          w[4 + s] = q[(16 + s) * kTP];
-        }
-      }
-      uint32_t h[4], r[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        h[q] = (w[2 * q] & 0xFFFFu) | (w[2 * q + 1] << 16);
-        r[q] = (w[2 * q] >> 16) | (w[2 * q + 1] & 0xFFFF0000u);
-      }
-      const uint4 wh{h[0], h[1], h[2], h[3]}, wl{r[0], r[1], r[2], r[3]};
-      t[nb] = mfma_f16(wh, xh[kb2], t[nb]);
-      t[nb] = mfma_f16(wh, xl[kb2], t[nb]);
-      t[nb] = mfma_f16(wl, xh[kb2], t[nb]);
+      const uint4 h0 = t_frag<kTrans>(M, kb2, nb, g, c), l0 = t_frag<kTrans>(M + kTPlane, kb2, nb, g, c);
+      const uint4 h1 = t_frag<kTrans>(M, kb2, nb + 1, g, c), l1 = t_frag<kTrans>(M + kTPlane, kb2, nb + 1, g, c);
+      t[nb] = mfma_f16(h0, x.h[kb2], t[nb]);
+      t[nb + 1] = mfma_f16(h1, x.h[kb2], t[nb + 1]);
+      t[nb] = mfma_f16(h0, x.l[kb2], t[nb]);
+      t[nb + 1] = mfma_f16(h1, x.l[kb2], t[nb + 1]);
+      t[nb] = mfma_f16(l0, x.h[kb2], t[nb]);
+      t[nb + 1] = mfma_f16(l1, x.h[kb2], t[nb + 1]);
     }
   }
 #pragma unroll
   for (int nb = 0; nb < 4; ++nb)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) acc[nb][v] += (t[nb][v] * ux) * uw;
+    for (int v = 0; v < 4; ++v) acc[nb][v] += (t[nb][v] * x.un) * uw;
 }
 
 template <class T>
@@ -235,7 +265,7 @@ __device__ __forceinline__ void t_attend(const float* lds, const float* rv, cons
     for (int k = 0; k < W; ++k) {
       f32x4 acc[4];
       t_zero(acc);
-      t_gemm<true>(lds, 0, cx[k], acc, g, c);
+      t_mul<true>(lds, 0, t_split(cx[k]), acc, g, c);
       float part = 0.f;
 #pragma unroll
       for (int b = 0; b < 4; ++b) {
@@ -274,13 +304,15 @@ __device__ __forceinline__ void t_gates(const float* lds, const f32x4 (&x)[4], c
   t_zero(az);
   t_zero(ain);
   t_zero(ahn);
-  t_gemm<false>(lds, 1, x, ar, g, c);
-  t_gemm<false>(lds, 2, x, az, g, c);
-  t_gemm<false>(lds, 3, x, ain, g, c);
+  const TRow xs = t_split(x);
+  t_mul<false>(lds, 1, xs, ar, g, c);
+  t_mul<false>(lds, 2, xs, az, g, c);
+  t_mul<false>(lds, 3, xs, ain, g, c);
   if constexpr (W > 0) {
-    t_gemm<false>(lds, 4, ht, ar, g, c);
-    t_gemm<false>(lds, 5, ht, az, g, c);
-    t_gemm<false>(lds, 6, ht, ahn, g, c);
+    const TRow hs = t_split(ht);
+    t_mul<false>(lds, 4, hs, ar, g, c);
+    t_mul<false>(lds, 5, hs, az, g, c);
+    t_mul<false>(lds, 6, hs, ahn, g, c);
   }
 }
 
@@ -339,7 +371,6 @@ __global__ void __launch_bounds__(kTThreads) k_temporal_bwd(int64_t n, const T* 
   extern __shared__ float lds[];
   __shared__ f32x4 red[kTWaves][16];
   t_stage(lds, p);
-  const float* vec = lds + kTVec;
   const int l = lane64(), g = l >> 4, c = l & 15;
   const int wv = threadIdx.x >> 6;
   const int64_t ntiles = (n + 15) / 16;
@@ -350,6 +381,7 @@ __global__ void __launch_bounds__(kTThreads) k_temporal_bwd(int64_t n, const T* 
     const int64_t i = 16 * t + c;
     const bool live = i < n;
     const int64_t ri = live ? i : n - 1;
+    const float* vec = t_vectors(lds);
     f32x4 x[4], cx[WA][4], ht[4], dy[4];
     float a[WA];
     t_load(h, ri, g, x);
@@ -392,14 +424,20 @@ __global__ void __launch_bounds__(kTThreads) k_temporal_bwd(int64_t n, const T* 
     }
     f32x4 acc[4];
     t_zero(acc);
-    t_gemm<true>(lds, 1, ar, acc, g, c);
-    t_gemm<true>(lds, 2, az, acc, g, c);
-    t_gemm<true>(lds, 3, ain, acc, g, c);
+    {
+      const TRow s = t_split(ar);
+      t_mul<true>(lds, 1, s, acc, g, c);
+      if constexpr (W > 0) t_mul<true>(lds, 4, s, dht, g, c);
+    }
+    {
+      const TRow s = t_split(az);
+      t_mul<true>(lds, 2, s, acc, g, c);
+      if constexpr (W > 0) t_mul<true>(lds, 5, s, dht, g, c);
+    }
+    t_mul<true>(lds, 3, t_split(ain), acc, g, c);
     if (live) t_store(dh, i, g, acc);
     if constexpr (W > 0) {
-      t_gemm<true>(lds, 4, ar, dht, g, c);
-      t_gemm<true>(lds, 5, az, dht, g, c);
-      t_gemm<true>(lds, 6, ahn, dht, g, c);
+      t_mul<true>(lds, 6, t_split(ahn), dht, g, c);
       // softmax backward: da_k = dHt . c_k, ds_k = a_k (da_k - sum_j a_j da_j).
       // The context rows are read again here and u_k = tanh(c_k Q^T) is
       // recomputed, rather than both kept live through the products above
@@ -425,7 +463,7 @@ __global__ void __launch_bounds__(kTThreads) k_temporal_bwd(int64_t n, const T* 
         const float dsl = live ? ds : 0.f;
         f32x4 dp[4];
         t_zero(dp);
-        t_gemm<true>(lds, 0, cx[k], dp, g, c);
+        t_mul<true>(lds, 0, t_split(cx[k]), dp, g, c);
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
           const f32x4 r4 = t_vec4(vec, 16 * b + 4 * g);
@@ -442,7 +480,7 @@ __global__ void __launch_bounds__(kTThreads) k_temporal_bwd(int64_t n, const T* 
           t_load(dC.c[k], ri, g, o);
 #pragma unroll
           for (int b = 0; b < 4; ++b) o[b] += a[k] * dht[b];
-          t_gemm<false>(lds, 0, dp, o, g, c);
+          t_mul<false>(lds, 0, t_split(dp), o, g, c);
           if (live) t_store(dC.c[k], i, g, o);
         }
       }
