@@ -712,12 +712,12 @@ __device__ __forceinline__ void hindex_add(const int32_t* __restrict__ ptr, cons
   int32_t low[kLow];
 #pragma unroll
   for (int t = 0; t < kLow; ++t) low[t] = 0;
-  for (int32_t p0 = beg; p0 < end; p0 += kHiBT * kU) {
+  HG_ROW_WALK(p0, beg, end, kHiBT * kU) {
     int32_t x[kU];
 #pragma unroll
     for (int j = 0; j < kU; ++j) {
-      const int64_t p = (int64_t)p0 + j * kHiBT + threadIdx.x;
-      x[j] = p < end ? col[p] : -1;
+      const row_pos p = p0 + j * kHiBT + threadIdx.x;
+      x[j] = p < (row_pos)end ? col[p] : -1;
     }
 #pragma unroll
     for (int j = 0; j < kU; ++j) x[j] = x[j] >= 0 ? deg_of(ptr, x[j]) - base : -1;

@@ -9,6 +9,7 @@
 #include <string>
 
 #include "../../include/hg.h"
+#include "hg_rows.h"
 
 namespace hg {
 
