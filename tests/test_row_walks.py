@@ -34,3 +34,23 @@ def test_walks_end(tmp_path):
     for (b, e, s), (n, last) in zip(WALKS, run_cpp(tmp_path, body)):
         steps = list(range(b, e, s))
         assert (n, last) == (len(steps), steps[-1] if steps else 0), (b, e, s)
+
+
+@pytest.mark.parametrize("lo,hi", [(2**31 - 1 - 65, 2**31 - 1), (2**31 - 1 - 16_384, 2**31 - 1),
+                                   (2**31 - 1 - 40_000, 2**31 - 1), (2**31 - 300, 2**31 - 1), (7, 7 + 16_385)])
+def test_gap_rows_written_once(tmp_path, lo, hi):
+    """The threads of the blocks that fill a gap write each of its rows once and no other."""
+    (row,) = run_cpp(tmp_path, f"""
+  long long n = 0, sum = 0, out = 0;
+  for (int i = 0; i < gap_pieces({lo}, {hi}); ++i) {{
+    const RowRange g = gap_piece({lo}, {hi}, i);
+    for (unsigned t = 0; t < 256; ++t) {{
+      HG_ROW_WALK(q, g.beg + t, g.end, 256) {{
+        if ((long long)(int32_t)q < {lo} || (long long)(int32_t)q >= {hi}) {{ ++out; break; }}
+        ++n;
+        sum += q;
+      }}
+    }}
+  }}
+  printf("%lld %lld %lld\\n", n, sum, out);""")
+    assert row == [hi - lo, (lo + hi - 1) * (hi - lo) // 2, 0]
