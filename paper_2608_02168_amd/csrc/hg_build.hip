@@ -28,44 +28,6 @@ namespace hg {
 namespace {
 
 constexpr int kBT = 256;  // threads per block for the elementwise passes
-// Most CSC entries that one backward work item (one wave) handles.  A wave walks
-// its entries serially, 16 or more rows in flight, so a hub's items are the
-// pass's tail: 1024 entries take about 45 us, which is all of the pass on a
-// graph whose edges would give each of the chip's 8192 waves a few dozen
-// (100k edges: 50 us at 1024, 14 at 64), and nothing beside it at 200M, where
-// short items would only cost partial rows.  E: the input graph's edges (the
-// plan's capacity follows from them).
-__host__ __device__ inline int plan_chunk(int64_t E) {
-  return E < ((int64_t)1 << 20) ? 64 : (E < ((int64_t)1 << 23) ? 256 : 1024);
-}
-
-// How the long rows of the CSC are cut into work items.  A row of up to
-// `whole` entries is one item; one of more is m * blocks pieces of equal
-// length, m = ceil(len / (chunk * blocks)), laid out block by block: the b-th
-// m pieces of every split row stand together.
-//
-// A row's entries ascend by destination and the rows draw on the same
-// destinations, so the pieces of one block gather from one part of the
-// destinations' rows: of kBlockNodes nodes, 128 MB at 512 bytes a row, half of
-// the Infinity Cache.  Gathers of 512-byte rows run at 9.3 TB/s from 64 MB,
-// 7.2 from 256 MB and 4.5 from 2.5 GB and more; blocks of 128k and 512k nodes
-// measured 0-3 % slower.  A piece costs a float64 partial row written and read
-// (2 KB at d = 128), so a row is split only into pieces of kMinPiece entries
-// and more (16 and 32 measured 0-3 % slower).  Destinations that fit one block
-// are gathered from the cache as they are: rows are cut by length alone.
-struct PlanCut {
-  int32_t chunk, blocks, whole;
-};
-constexpr int64_t kBlockNodes = (int64_t)1 << 18;
-constexpr int32_t kMaxBlocks = 128;
-constexpr int32_t kMinPiece = 24;
-
-inline PlanCut plan_cut(int64_t E, int64_t ns) {
-  const int32_t chunk = plan_chunk(E);
-  const int32_t blocks = (int32_t)std::max<int64_t>(1, std::min<int64_t>(cdiv(ns, kBlockNodes), kMaxBlocks));
-  return {chunk, blocks, blocks == 1 ? chunk : kMinPiece * blocks - 1};
-}
-
 inline unsigned grid_for(int64_t n, int64_t cap = 16384) {
   int64_t b = cdiv(n > 0 ? n : 1, kBT);
   return (unsigned)(b < cap ? b : cap);
@@ -1586,14 +1548,6 @@ __device__ __forceinline__ int wave_before(int v) {
   return inc - v;
 }
 
-// Items of a row per block: 0 for a row that is one item or none.
-__device__ __forceinline__ int cuts_of(int32_t len, PlanCut k) {
-  return len > k.whole ? (len + k.chunk * k.blocks - 1) / (k.chunk * k.blocks) : 0;
-}
-__device__ __forceinline__ int fwd_chunks_of(int32_t len) {
-  return len > kFwdChunk ? (len + kFwdChunk - 1) / kFwdChunk : 0;
-}
-
 // Bit of tile row w (w = node * R + r inside the tile) in the tile's masks.
 __device__ __forceinline__ bool tile_bit(const uint64_t* mask, int w) { return (mask[w >> 6] >> (w & 63)) & 1ull; }
 
@@ -1663,11 +1617,10 @@ __device__ __forceinline__ void wave_chunks(int4* __restrict__ out, int32_t x, i
 __device__ __forceinline__ void wave_pieces(int4* __restrict__ items, int32_t per_block, int32_t sl, int32_t beg,
                                             int32_t end, int32_t first, int m, int blocks) {
   const int n = m * blocks;
-  const int64_t len = end - beg;
   for (int c = threadIdx.x & 63; c < n; c += 64) {
     const int b = c / m;
-    items[(int64_t)b * per_block + first + (c - b * m)] =
-        make_int4(sl, beg + (int32_t)(len * c / n), beg + (int32_t)(len * (c + 1) / n), first * blocks + c);
+    const RowRange r = row_piece(beg, end, c, n);
+    items[(int64_t)b * per_block + first + (c - b * m)] = make_int4(sl, r.beg, r.end, first * blocks + c);
   }
 }
 

@@ -153,10 +153,6 @@ struct PlanView {
   const int4* fwd_heavy;    // long destination rows (j, first partial slot, number of slots, 0)
 };
 
-// Destination rows (all relations of one node j in the CSR) longer than
-// this are not walked by one wave: the plan cuts them into chunks of this
-// many entries whose partial results are merged in chunk order.
-constexpr int32_t kFwdChunk = 2048;
 PlanView plan_view(const hg_subgraph* s);
 
 // Rows of the relation transforms: A (compact) or n_sub * R (row-indexed).

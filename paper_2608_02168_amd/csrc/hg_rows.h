@@ -3,6 +3,7 @@
 // sizes of which no graph is built for a test.
 #pragma once
 
+#include <algorithm>
 #include <cstdint>
 
 namespace hg {
@@ -26,5 +27,60 @@ constexpr RowRange gap_piece(int32_t lo, int32_t hi, int32_t i) {
   const int32_t beg = lo + i * kRpPiece;
   return {beg, hi - beg < kRpPiece ? hi : beg + kRpPiece};
 }
+
+// Most CSC entries that one backward work item (one wave) handles.  A wave walks
+// its entries serially, 16 or more rows in flight, so a hub's items are the
+// pass's tail: 1024 entries take about 45 us, which is all of the pass on a
+// graph whose edges would give each of the chip's 8192 waves a few dozen
+// (100k edges: 50 us at 1024, 14 at 64), and nothing beside it at 200M, where
+// short items would only cost partial rows.  E: the input graph's edges (the
+// plan's capacity follows from them).
+constexpr int32_t plan_chunk(int64_t E) {
+  return E < ((int64_t)1 << 20) ? 64 : (E < ((int64_t)1 << 23) ? 256 : 1024);
+}
+
+// How the long rows of the CSC are cut into work items.  A row of up to
+// `whole` entries is one item; one of more is m * blocks pieces of equal
+// length, m = ceil(len / (chunk * blocks)), laid out block by block: the b-th
+// m pieces of every split row stand together.
+//
+// A row's entries ascend by destination and the rows draw on the same
+// destinations, so the pieces of one block gather from one part of the
+// destinations' rows: of kBlockNodes nodes, 128 MB at 512 bytes a row, half of
+// the Infinity Cache.  Gathers of 512-byte rows run at 9.3 TB/s from 64 MB,
+// 7.2 from 256 MB and 4.5 from 2.5 GB and more; blocks of 128k and 512k nodes
+// measured 0-3 % slower.  A piece costs a float64 partial row written and read
+// (2 KB at d = 128), so a row is split only into pieces of kMinPiece entries
+// and more (16 and 32 measured 0-3 % slower).  Destinations that fit one block
+// are gathered from the cache as they are: rows are cut by length alone.
+struct PlanCut {
+  int32_t chunk, blocks, whole;
+};
+constexpr int64_t kBlockNodes = (int64_t)1 << 18;
+constexpr int32_t kMaxBlocks = 128;
+constexpr int32_t kMinPiece = 24;
+
+constexpr PlanCut plan_cut(int64_t E, int64_t ns) {
+  const int32_t chunk = plan_chunk(E);
+  const int32_t blocks = (int32_t)std::max<int64_t>(1, std::min<int64_t>((ns - 1) / kBlockNodes + 1, kMaxBlocks));
+  return {chunk, blocks, blocks == 1 ? chunk : kMinPiece * blocks - 1};
+}
+
+// Pieces of a row per block of destinations: 0 for a row that is one item or none.
+constexpr int32_t cuts_of(int32_t len, PlanCut k) {
+  return len > k.whole ? (len - 1) / (k.chunk * k.blocks) + 1 : 0;
+}
+
+// Entries of piece c of the n of row [beg, end).
+constexpr RowRange row_piece(int32_t beg, int32_t end, int32_t c, int32_t n) {
+  const int64_t len = end - beg;
+  return {beg + (int32_t)(len * c / n), beg + (int32_t)(len * (c + 1) / n)};
+}
+
+// Destination rows (all relations of one node j in the CSR) longer than
+// this are not walked by one wave: the plan cuts them into chunks of this
+// many entries whose partial results are merged in chunk order.
+constexpr int32_t kFwdChunk = 2048;
+constexpr int32_t fwd_chunks_of(int32_t len) { return len > kFwdChunk ? (len - 1) / kFwdChunk + 1 : 0; }
 
 }  // namespace hg

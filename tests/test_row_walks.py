@@ -54,3 +54,31 @@ def test_gap_rows_written_once(tmp_path, lo, hi):
   }}
   printf("%lld %lld %lld\\n", n, sum, out);""")
     assert row == [hi - lo, (lo + hi - 1) * (hi - lo) // 2, 0]
+
+
+LENGTHS = [0, 1, 23, 24, 47, 48, 64, 65, 256, 257, 1_024, 1_025, 2_048, 2_049, 100_003, 2**31 - 131_072,
+           2**31 - 2_049, 2**31 - 1_024, 2**31 - 1]
+
+
+@pytest.mark.parametrize("edges,nodes", [(10**5, 10**4), (2**31 - 1, 10**4), (2**31 - 1, 10**6), (2**31 - 1, 2**31 - 2)])
+def test_pieces_cover_long_rows(tmp_path, edges, nodes):
+    """A row's pieces per block and the chunks of a destination row, up to the longest row, and the row
+    covered once by pieces of at most a chunk."""
+    body = f"const PlanCut k = plan_cut({edges}, {nodes});\n"
+    body += 'printf("%d %d %d\\n", k.chunk, k.blocks, k.whole);\n'
+    for n in LENGTHS:
+        body += f"""{{ const int m = cuts_of({n}, k), p = m * k.blocks;
+  int at = 0, most = 0, holes = 0;
+  for (int c = 0; c < p; ++c) {{
+    const RowRange r = row_piece(0, {n}, c, p);
+    holes += r.beg != at || r.end <= r.beg;
+    at = r.end;
+    most = r.end - r.beg > most ? r.end - r.beg : most;
+  }}
+  printf("%d %d %d %d %d\\n", m, fwd_chunks_of({n}), at, most, holes); }}
+"""
+    (chunk, blocks, whole), *rows = run_cpp(tmp_path, body)
+    for n, (m, fwd, at, most, holes) in zip(LENGTHS, rows):
+        assert m == (-(-n // (chunk * blocks)) if n > whole else 0), n
+        assert fwd == (-(-n // 2_048) if n > 2_048 else 0), n
+        assert (at, holes) == (n if m else 0, 0) and most <= chunk, n
