@@ -121,18 +121,18 @@ __device__ __forceinline__ void attn_fwd_range(int64_t j, int tj, int32_t R, int
   m = -INFINITY;
   ls = 0.f;
   acc = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int32_t base = beg; base < end; base += 64) {
-    const int32_t pos = base + l;
+  HG_ROW_WALK(base, beg, end, 64) {
+    const row_pos pos = base + l;
     int32_t rowi = 0;
     float cf = 0.f;
-    if (pos < end) {
+    if (pos < (row_pos)end) {
       const int32_t src = csr_col[pos];
       int r = 0;
-      for (int t = 1; t < R; ++t) r += (csr_ptr[rb + t] <= pos) ? 1 : 0;
+      for (int t = 1; t < R; ++t) r += (csr_ptr[rb + t] <= (int32_t)pos) ? 1 : 0;
       rowi = csr_slot ? csr_slot[pos] : src * R + r;
       cf = mu[((int64_t)type_of(src, T, type_off) * R + r) * T + tj] * inv_sqrt_dk;
     }
-    const int cnt = (end - base) < 64 ? (end - base) : 64;
+    const int cnt = wave_entries(base, end);
     for (int e = 0; e < cnt; e += EPW * U) {
       f32x4 kv[U], vv[U];
       float cc[U];
@@ -524,18 +524,18 @@ __device__ __forceinline__ void attn_bwd_dst_range(int64_t j, int tj, int32_t R,
   const int slot = l / LPR, lr = l % LPR, c0 = lr * 4;
   const bool head_lead = (lr % LPH) == 0;
   const int64_t rb = j * R;
-  for (int32_t base = beg; base < end; base += 64) {
-    const int32_t pos = base + l;
+  HG_ROW_WALK(base, beg, end, 64) {
+    const row_pos pos = base + l;
     int32_t rowi = 0;
     float cf = 0.f;
-    if (pos < end) {
+    if (pos < (row_pos)end) {
       const int32_t src = csr_col[pos];
       int r = 0;
-      for (int t = 1; t < R; ++t) r += (csr_ptr[rb + t] <= pos) ? 1 : 0;
+      for (int t = 1; t < R; ++t) r += (csr_ptr[rb + t] <= (int32_t)pos) ? 1 : 0;
       rowi = csr_slot ? csr_slot[pos] : src * R + r;
       cf = mu[((int64_t)type_of(src, T, type_off) * R + r) * T + tj] * inv_sqrt_dk;
     }
-    const int cnt = (end - base) < 64 ? (end - base) : 64;
+    const int cnt = wave_entries(base, end);
     for (int e = 0; e < cnt; e += EPW * U) {
       f32x4 kv[U], vv[U];
       float cc[U];
@@ -725,15 +725,15 @@ __global__ void __launch_bounds__(kAttnThreads, S >= 4 ? 4 : 1) k_hgt_attn_bwd_s
     const f32x4 kt = *reinterpret_cast<const f32x4*>(Kt + srow * D + c0);
     const f32x4 vt = *reinterpret_cast<const f32x4*>(Vt + srow * D + c0);
     f64x4 dk = {0.0, 0.0, 0.0, 0.0}, dv = {0.0, 0.0, 0.0, 0.0};
-    for (int32_t base = item.y; base < item.z; base += 64) {
-      const int32_t pos = base + l;
+    HG_ROW_WALK(base, item.y, item.z, 64) {
+      const row_pos pos = base + l;
       int32_t jj = 0;
       float cf = 0.f;
-      if (pos < item.z) {
+      if (pos < (row_pos)item.z) {
         jj = csc_row[pos];
         cf = mu[((int64_t)ti * R + r) * T + type_of(jj, T, type_off)] * inv_sqrt_dk;
       }
-      const int cnt = (item.z - base) < 64 ? (item.z - base) : 64;
+      const int cnt = wave_entries(base, item.z);
       for (int e = 0; e < cnt; e += EPW * U) {
         f32x4 qv[U], gv[U];
         float cc[U], lj[U], dj[U];
@@ -866,7 +866,7 @@ __global__ void __launch_bounds__(kDmuThreads) k_dmu_heavy(int64_t n_heavy, cons
     for (int32_t r = 0; r < R; ++r) {
       const int64_t q = j * R + r;
       float acc[kMaxTypesBwd] = {0.f, 0.f, 0.f, 0.f};
-      for (int32_t p = csr_ptr[q] + tid; p < csr_ptr[q + 1]; p += kDmuThreads) {
+      HG_ROW_WALK(p, csr_ptr[q] + (row_pos)tid, csr_ptr[q + 1], kDmuThreads) {
         const int ti = type_of(csr_col[p], T, type_off);
         const float v = contrib[p];
 #pragma unroll

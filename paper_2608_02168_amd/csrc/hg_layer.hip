@@ -51,15 +51,15 @@ __device__ __forceinline__ void fwd_gather(int64_t rb, int32_t R, int32_t p0, in
   constexpr int EL = Elt<T>::EL;
   constexpr int EPW = 64 / (D / EL);
   constexpr int U = 4;
-  for (int32_t base = beg; base < end; base += 64) {
-    const int32_t pos = base + l;
+  HG_ROW_WALK(base, beg, end, 64) {
+    const row_pos pos = base + l;
     int32_t rowi = 0;
     float wgt = 0.f;
-    if (pos < end) {
+    if (pos < (row_pos)end) {
       int32_t lo = p0, hi = pe, r = 0;
       for (int t = 1; t < R; ++t) {
         const int32_t pt = csr_ptr[rb + t];
-        if (pt <= pos) {
+        if (pt <= (int32_t)pos) {
           lo = pt;
           r = t;
         } else if (pt < hi) {
@@ -69,7 +69,7 @@ __device__ __forceinline__ void fwd_gather(int64_t rb, int32_t R, int32_t p0, in
       rowi = csr_slot ? csr_slot[pos] : csr_col[pos] * R + r;
       wgt = (csr_w ? csr_w[pos] : 1.0f) / (float)(hi - lo);
     }
-    const int cnt = (end - base) < 64 ? (end - base) : 64;
+    const int cnt = wave_entries(base, end);
     for (int e = 0; e < cnt; e += EPW * U) {
       typename Elt<T>::rawv_t v[U];
       float ww[U];
@@ -257,15 +257,15 @@ __global__ void __launch_bounds__(256, (sizeof(T) == 2 || D <= 128) ? 8 : 4) k_s
       const int4 item = items[it];
       const int32_t beg = item.y, end = item.z;
       f64x4 acc = {0.0, 0.0, 0.0, 0.0};
-      for (int32_t base = beg; base < end; base += 64) {
-        const int32_t pos = base + l;
+      HG_ROW_WALK(base, beg, end, 64) {
+        const row_pos pos = base + l;
         int32_t dst = 0;
         float sc = 0.f;
-        if (pos < end) {
+        if (pos < (row_pos)end) {
           dst = csc_row[pos];
           sc = csc_scale[pos];
         }
-        const int cnt = (end - base) < 64 ? (end - base) : 64;
+        const int cnt = wave_entries(base, end);
         for (int e = 0; e < cnt; e += EPW * U) {
           f32x4 v[U];
           float ww[U];
@@ -314,15 +314,15 @@ __global__ void __launch_bounds__(256, (sizeof(T) == 2 || D <= 128) ? 8 : 4) k_s
       double acc[EL];
 #pragma unroll
       for (int k = 0; k < EL; ++k) acc[k] = 0.0;
-      for (int32_t base = beg; base < end; base += 64) {
-        const int32_t pos = base + l;
+      HG_ROW_WALK(base, beg, end, 64) {
+        const row_pos pos = base + l;
         int32_t dst = 0;
         float sc = 0.f;
-        if (pos < end) {
+        if (pos < (row_pos)end) {
           dst = csc_row[pos];
           sc = csc_scale[pos];
         }
-        const int cnt = (end - base) < 64 ? (end - base) : 64;
+        const int cnt = wave_entries(base, end);
         for (int e = 0; e < cnt; e += EPW * U) {
           typename Elt<T>::rawv_t v[U];
           float ww[U];

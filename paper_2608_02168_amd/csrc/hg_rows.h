@@ -16,6 +16,9 @@ typedef uint32_t row_pos;
 #define HG_ROW_WALK(p, beg, end, step) \
   for (::hg::row_pos p = (::hg::row_pos)(beg); p < (::hg::row_pos)(end); p += (::hg::row_pos)(step))
 
+// Entries that a wave takes at base: 64, or those left.
+constexpr int wave_entries(row_pos base, row_pos end) { return end - base < 64 ? (int)(end - base) : 64; }
+
 // Stretches of rows without entries, in pieces of kRpPiece rows that blocks
 // fill on their own; hi is at most 2^31 - 1.
 constexpr int32_t kRpPiece = 16384;

@@ -36,6 +36,27 @@ def test_walks_end(tmp_path):
         assert (n, last) == (len(steps), steps[-1] if steps else 0), (b, e, s)
 
 
+@pytest.mark.parametrize("beg,end", [(2**31 - 66, 2**31 - 1), (2**31 - 65, 2**31 - 1), (2**31 - 2, 2**31 - 1), (5, 200)])
+def test_wave_takes_each_entry_once(tmp_path, beg, end):
+    """The gathers of a row by a wave: lane l at base + l, 64 entries a round."""
+    (row,) = run_cpp(tmp_path, f"""
+  long long n = 0, sum = 0, cnt = 0;
+  int rounds = 0;
+  HG_ROW_WALK(base, {beg}, {end}, 64) {{
+    cnt += wave_entries(base, {end});
+    for (int l = 0; l < 64; ++l) {{
+      const row_pos pos = base + l;
+      if (pos < (row_pos){end}) {{
+        ++n;
+        sum += pos;
+      }}
+    }}
+    if (++rounds > 9) break;
+  }}
+  printf("%lld %lld %lld\\n", n, sum, cnt);""")
+    assert row == [end - beg, (beg + end - 1) * (end - beg) // 2, end - beg]
+
+
 @pytest.mark.parametrize("lo,hi", [(2**31 - 1 - 65, 2**31 - 1), (2**31 - 1 - 16_384, 2**31 - 1),
                                    (2**31 - 1 - 40_000, 2**31 - 1), (2**31 - 300, 2**31 - 1), (7, 7 + 16_385)])
 def test_gap_rows_written_once(tmp_path, lo, hi):
