@@ -1374,11 +1374,11 @@ int hgt_bwd_impl(const hg_subgraph* s, const hg_hgt_desc* L, const float* Hin, c
     }
     // dW_K, dW_Q and dW_V read the same rows of H: one group; dW_agg beside it
     HG_TRY(bproj.group(hi - lo, 4));
+    bproj.add(LoadRows<D, float>{sv.ht, rows_contig(lo)}, LoadRows<D, float>{w.dZ, rows_contig(lo)}, dW->W_agg + wo,
+              dW->b_agg ? dW->b_agg + bo : nullptr, acc);
     for (int k = 0; k < 3; ++k)
       bproj.add(LoadRows<D, float>{Hin, rows_contig(lo)}, LoadRows<D, float>{srcs[k], rows_contig(lo)}, dWs[k] + wo,
                 dbs[k] ? dbs[k] + bo : nullptr, acc);
-    bproj.add(LoadRows<D, float>{sv.ht, rows_contig(lo)}, LoadRows<D, float>{w.dZ, rows_contig(lo)}, dW->W_agg + wo,
-              dW->b_agg ? dW->b_agg + bo : nullptr, acc);
   }
   HG_TRY(bproj.run());
   // (6) dmu: per CSR row by source type, then per meta relation over each type range

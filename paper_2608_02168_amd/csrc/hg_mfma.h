@@ -1475,10 +1475,10 @@ struct TnOuts {
   TnOut o[kTnJobs];
 };
 template <int D>
-__global__ void __launch_bounds__(256) k_tn_reduce(const TnOuts outs, const float* __restrict__ partial,
+__global__ void __launch_bounds__(256) k_tn_reduce(const TnOuts outs, int first, const float* __restrict__ partial,
                                                    const float* __restrict__ colsum) {
   __shared__ f32x4 red[kSplitGroups][16];
-  const TnOut o = outs.o[blockIdx.y];
+  const TnOut o = outs.o[first + blockIdx.y];
   const bool cs = blockIdx.x >= D * D / 64;
   if (cs && !o.colsum) return;
   const int e = threadIdx.x & 15, grp = threadIdx.x >> 4;
@@ -1757,8 +1757,11 @@ inline int64_t tn_rows(int D, int64_t chunks) {
 
 // Collects the products of a launch: group() starts a group of jobs over n
 // rows, add() adds A^T B to it, into out (and B's column sums into out_colsum,
-// if given); jobs added one after another with the same out are summed.  run()
-// launches what is there.  partial and colsum hold `rows` partial rows.
+// if given), add_more() adds A^T B to the last one's out.  run() launches what
+// is there.  partial and colsum hold `rows` partial rows.
+// A caller may name one buffer for several gradients (tied weights summed with
+// accumulate = 1): outputs that overlap are reduced one launch after another, in
+// the order they were added, as if each product were a call of its own.
 template <int D, class TA, class TB, bool kListA, bool kListB>
 struct TnBatch {
   const char* name;
@@ -1789,19 +1792,21 @@ struct TnBatch {
     return HG_OK;
   }
   void add(LoadRows<D, TA> la, LoadRows<D, TB> lb, float* out, float* out_colsum, int accumulate) {
-    const int64_t c = tn_chunks(group_n);
-    if (n_out > 0 && outs.o[n_out - 1].out == out) {
-      outs.o[n_out - 1].c1 += (int32_t)c;
-    } else {
-      outs.o[n_out++] = TnOut{out, out_colsum, (int32_t)used, (int32_t)(used + c), accumulate};
-      any_colsum |= out_colsum != nullptr;
-    }
+    outs.o[n_out++] = TnOut{out, out_colsum, (int32_t)used, (int32_t)used, accumulate};
+    any_colsum |= out_colsum != nullptr;
+    add_more(la, lb);
+  }
+  void add_more(LoadRows<D, TA> la, LoadRows<D, TB> lb) {
     if (group_n <= 0) return;
     J.la[jobs] = la;
     J.lb[jobs] = lb;
     J.chunk0[jobs] = (int32_t)used;
-    used += c;
+    used += tn_chunks(group_n);
+    outs.o[n_out - 1].c1 = (int32_t)used;
     J.job0[J.groups] = ++jobs;
+  }
+  static bool overlap(const float* a, const float* b, int64_t n) {
+    return a && b && (a < b ? b - a : a - b) < n;
   }
   int run() {
     constexpr int T = D == 256 ? 4 : 1;
@@ -1819,9 +1824,13 @@ struct TnBatch {
         HG_LAUNCH(name, (k_gemm_tn_bf<D, TA, TB, kListA, kListB>), dim3((unsigned)blocks), dim3(256), 0, s, J, partial, cs);
       }
     }
-    if (n_out > 0)
-      HG_LAUNCH("splitk_reduce", k_tn_reduce<D>, dim3(D * D / 64 + (any_colsum ? D / 64 : 0), (unsigned)n_out), dim3(256),
-                0, s, outs, (const float*)partial, (const float*)colsum);
+    for (int b = 0, e = 0; b < n_out; b = e) {
+      for (bool apart = true; e < n_out && apart; e += apart)
+        for (int k = b; k < e; ++k)
+          apart &= !overlap(outs.o[k].out, outs.o[e].out, D * D) && !overlap(outs.o[k].colsum, outs.o[e].colsum, D);
+      HG_LAUNCH("splitk_reduce", k_tn_reduce<D>, dim3(D * D / 64 + (any_colsum ? D / 64 : 0), (unsigned)(e - b)),
+                dim3(256), 0, s, outs, b, (const float*)partial, (const float*)colsum);
+    }
     J.groups = 0;
     jobs = n_out = 0;
     used = 0;
@@ -1846,7 +1855,7 @@ int launch_gemm_tn(const char* name, int64_t n_rows, LA la, LB lb, float* partia
       HG_LAUNCH(name, (k_gemm_tn<D, LA, LB, false, false>), grid, dim3(256), 0, s, n_rows, kc, la, lb, partial, cs);
     }
   }
-  HG_LAUNCH("splitk_reduce", k_tn_reduce<D>, dim3(D * D / 64 + (cs ? D / 64 : 0), 1), dim3(256), 0, s, outs,
+  HG_LAUNCH("splitk_reduce", k_tn_reduce<D>, dim3(D * D / 64 + (cs ? D / 64 : 0), 1), dim3(256), 0, s, outs, 0,
             (const float*)partial, (const float*)colsum);
   return HG_OK;
 }

@@ -643,10 +643,11 @@ int temporal_bwd_impl(int64_t n, int w, const T* h, const void* const* C, const 
   // dQ = sum_k dpre_k^T C_k
   TnBatch<kTD, float, T, false, false> bq("temporal_dQ", wk.splitk, wk.colsum, wk.tn, st);
   HG_TRY(bq.group(w > 0 ? n : 0, w > 0 ? w : 1));
-  for (int k = 0; k < w; ++k)
-    bq.add(LoadRows<kTD, float>{wk.dpre + (int64_t)k * n * kTD, rows_contig(0)},
-           LoadRows<kTD, T>{static_cast<const T*>(C[k]), rows_contig(0)}, G->Q, nullptr, accumulate);
-  if (w == 0) bq.add(LoadRows<kTD, float>{}, LoadRows<kTD, T>{}, G->Q, nullptr, accumulate);
+  bq.add(LoadRows<kTD, float>{wk.dpre, rows_contig(0)}, LoadRows<kTD, T>{w > 0 ? static_cast<const T*>(C[0]) : nullptr, rows_contig(0)},
+         G->Q, nullptr, accumulate);
+  for (int k = 1; k < w; ++k)
+    bq.add_more(LoadRows<kTD, float>{wk.dpre + (int64_t)k * n * kTD, rows_contig(0)},
+                LoadRows<kTD, T>{static_cast<const T*>(C[k]), rows_contig(0)});
   HG_TRY(bq.run());
   const int64_t blocks = n > 0 ? t_grid(n) : 0;
   HG_LAUNCH("temporal_dr", k_temporal_dr, dim3(1), dim3(kTD * kDrGroups), 0, st, (const float*)wk.dr_part, blocks, G->r,
