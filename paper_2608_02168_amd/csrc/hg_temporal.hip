@@ -642,10 +642,11 @@ int temporal_bwd_impl(int64_t n, int w, const T* h, const void* const* C, const 
   if (!kOne) HG_TRY(bh.run());
   // dQ = sum_k dpre_k^T C_k
   TnBatch<kTD, float, T, false, false> bq("temporal_dQ", wk.splitk, wk.colsum, wk.tn, st);
-  HG_TRY(bq.group(w > 0 ? n : 0, w > 0 ? w : 1));
-  bq.add(LoadRows<kTD, float>{wk.dpre, rows_contig(0)}, LoadRows<kTD, T>{w > 0 ? static_cast<const T*>(C[0]) : nullptr, rows_contig(0)},
-         G->Q, nullptr, accumulate);
-  for (int k = 1; k < w; ++k)
+  const int wq = n > 0 ? w : 0;  // C may be null when there are no rows
+  HG_TRY(bq.group(wq > 0 ? n : 0, wq > 0 ? wq : 1));
+  bq.add(LoadRows<kTD, float>{wk.dpre, rows_contig(0)},
+         LoadRows<kTD, T>{wq > 0 ? static_cast<const T*>(C[0]) : nullptr, rows_contig(0)}, G->Q, nullptr, accumulate);
+  for (int k = 1; k < wq; ++k)
     bq.add_more(LoadRows<kTD, float>{wk.dpre + (int64_t)k * n * kTD, rows_contig(0)},
                 LoadRows<kTD, T>{static_cast<const T*>(C[k]), rows_contig(0)});
   HG_TRY(bq.run());
