@@ -857,11 +857,14 @@ int hindex_keys(const int32_t* src, const int32_t* dst, int64_t N, int64_t E, co
 // histogram and that into the state's; the block that finishes last picks the
 // digit holding the k_rem-th smallest and narrows the range.  The first launch
 // also finds the candidates (their list is in no order: the search needs only
-// the set).  With keys below 2047 two hash digits leave about a candidate in
-// four million, so kSelSteps launches and the ranking of a small range end
-// every search of real sizes; k_select_finish goes on by itself if they don't.
-// 8 launches of about 4 us where 16 digits of 8 bits took 33.
-constexpr int kSelSteps = 5;
+// the set).  Two hash digits leave about a candidate in four million, and one
+// more launch lists that small range for the ranking: of up to 10^9 candidates
+// the search ends in three launches where the boundary's key is below 2047 and
+// in six where most candidates share a larger one (three key digits come first).
+// With five, k_select_finish's one block went on with the list: 26 ms at 10M
+// equal keys, where the build takes 3.2 with small ones.  8 launches of about 4
+// us where 16 digits of 8 bits took 33; one with nothing left to do takes 2.
+constexpr int kSelSteps = 6;
 constexpr int kSelBT = 256;
 constexpr int kSelItems = 8;
 
