@@ -571,9 +571,18 @@ int bits_for(int64_t nvals) {
 //   - up to kHiBlock by one block, longer rows by blocks of kHiPart neighbours
 //     each (parts): a histogram of the degrees below kHiBins (values below 8, most of
 //     them, counted by ballots), whose suffix sums meet h.
-// A row whose h is kHiBins or more is walked once more per kHiBins values.
+// A row with kHiBins neighbours of degree kHiBins and more has its h above the
+// histogram (parallel edges to hubs count each, so h may be as large as the row).
+// Ranges of 2^s degrees up to the row's length are counted beside it; the range
+// that holds h is found the same way, and further walks, by the parts again,
+// count its values, kHiSplit bits at a time: one walk more for rows of up to
+// 2.7M neighbours, two for all others.  A walk per kHiBins values of h, in one
+// block, took 70 ms for a row of 50M neighbours with h = 9000.
 constexpr int kHiSmall = 16, kHiWave = 1024, kHiBlock = 16384, kHiPart = 8192;
 constexpr int kHiBins = 4096;
+constexpr int kHiRanges = 1344, kHiSplit = 11;
+// a row's histogram: degrees below kHiBins, the count of the others, their ranges
+constexpr int kHiWords = kHiBins + 1 + kHiRanges;
 constexpr int kHiBT = 1024;
 
 __device__ __forceinline__ int32_t deg_of(const int32_t* __restrict__ ptr, int32_t v) { return ptr[v + 1] - ptr[v]; }
@@ -665,14 +674,12 @@ __global__ void __launch_bounds__(kBT) k_hindex_rows(const int32_t* __restrict__
   }
 }
 
-// Adds the degrees of neighbours [beg, end) into the block's histogram of
-// min(x - base, kHiBins) (values below base are left out).
-__device__ __forceinline__ void hindex_add(const int32_t* __restrict__ ptr, const int32_t* __restrict__ col,
-                                           int32_t beg, int32_t end, int32_t base, int32_t* lh) {
-  constexpr int kU = 4, kLow = 8;
-  int32_t low[kLow];
-#pragma unroll
-  for (int t = 0; t < kLow; ++t) low[t] = 0;
+// Calls f with the degrees of neighbours [beg, end), kU of each thread at a time
+// (-1 past the end), in all threads of the block.
+template <class F>
+__device__ __forceinline__ void hindex_walk(const int32_t* __restrict__ ptr, const int32_t* __restrict__ col,
+                                            int32_t beg, int32_t end, F f) {
+  constexpr int kU = 4;
   HG_ROW_WALK(p0, beg, end, kHiBT * kU) {
     int32_t x[kU];
 #pragma unroll
@@ -681,70 +688,116 @@ __device__ __forceinline__ void hindex_add(const int32_t* __restrict__ ptr, cons
       x[j] = p < (row_pos)end ? col[p] : -1;
     }
 #pragma unroll
-    for (int j = 0; j < kU; ++j) x[j] = x[j] >= 0 ? deg_of(ptr, x[j]) - base : -1;
+    for (int j = 0; j < kU; ++j) x[j] = x[j] >= 0 ? deg_of(ptr, x[j]) : -1;
 #pragma unroll
-    for (int j = 0; j < kU; ++j) {
-#pragma unroll
-      for (int t = 0; t < kLow; ++t) low[t] += (int32_t)__popcll(__ballot(x[j] == t));
-      if (x[j] >= kLow) atomicAdd(&lh[x[j] < kHiBins ? x[j] : kHiBins], 1);
-    }
+    for (int j = 0; j < kU; ++j) f(x[j]);
   }
+}
+
+// Bits of the ranges' width in a row of n neighbours, -1 for one too short to
+// need ranges.  The last range takes the degrees past the row's length, so h is
+// never in it.
+__device__ __forceinline__ int hindex_shift(int32_t n) {
+  if (n < kHiBins) return -1;
+  int s = 0;
+  while ((n - kHiBins) >> s >= kHiRanges - 1) ++s;
+  return s;
+}
+
+// Adds the degrees of neighbours [beg, end) into the block's histogram.
+__device__ __forceinline__ void hindex_add(const int32_t* __restrict__ ptr, const int32_t* __restrict__ col,
+                                           int32_t beg, int32_t end, int shift, int32_t* lh) {
+  constexpr int kLow = 8;
+  int32_t low[kLow], many = 0;
+#pragma unroll
+  for (int t = 0; t < kLow; ++t) low[t] = 0;
+  hindex_walk(ptr, col, beg, end, [&](int32_t x) {
+#pragma unroll
+    for (int t = 0; t < kLow; ++t) low[t] += (int32_t)__popcll(__ballot(x == t));
+    many += (int32_t)__popcll(__ballot(x >= kHiBins));
+    if (x >= kHiBins) {
+      if (shift < 0) return;
+      const int r = (x - kHiBins) >> shift;
+      atomicAdd(&lh[kHiBins + 1 + (r < kHiRanges ? r : kHiRanges - 1)], 1);
+    } else if (x >= kLow) {
+      atomicAdd(&lh[x], 1);
+    }
+  });
   if ((threadIdx.x & 63) == 0) {
 #pragma unroll
     for (int t = 0; t < kLow; ++t)
       if (low[t]) atomicAdd(&lh[t], low[t]);
+    if (many) atomicAdd(&lh[kHiBins], many);
   }
 }
 
-// The largest t in [1, kHiBins] with #{x >= t + base} >= t + base, or 0, from
-// the histogram (to all threads of the block).
-__device__ __forceinline__ int hindex_meet(const int32_t* lh, int32_t base, int32_t* red, int* best) {
+// Degrees [lo, lo + 2^shift) hold h, and `above` neighbours have degrees past
+// them; h is lo once shift is 0.
+struct HiRange {
+  uint32_t lo, above;
+  int shift;
+};
+
+// Bits of the bins in which a range is walked again, and their number.
+__device__ __forceinline__ int hindex_bin_shift(const HiRange& r) { return r.shift > kHiSplit ? r.shift - kHiSplit : 0; }
+__device__ __forceinline__ int hindex_bins(const HiRange& r) { return 1 << (r.shift - hindex_bin_shift(r)); }
+
+// The last of n <= kHiBins bins, of 2^shift degrees from lo on, whose first
+// degree t has #{x >= t} >= t (the first bin has), to all threads of the block.
+__device__ __forceinline__ HiRange hindex_meet(const int32_t* bins, int n, uint32_t lo, int shift, uint32_t above,
+                                               uint32_t* red, int* best) {
   constexpr int kPer = kHiBins / kHiBT;
-  int32_t c[kPer], sum = 0;
+  uint32_t c[kPer], sum = 0;
 #pragma unroll
-  for (int i = kPer - 1; i >= 0; --i) {  // thread's values t = kPer tid + i + 1: counts of x >= t
-    sum += lh[threadIdx.x * kPer + i + 1];
+  for (int i = kPer - 1; i >= 0; --i) {  // neighbours of bin kPer tid + i and the thread's later ones
+    const int b = (int)threadIdx.x * kPer + i;
+    sum += b < n ? (uint32_t)bins[b] : 0u;
     c[i] = sum;
   }
   red[threadIdx.x] = sum;
   if (threadIdx.x == 0) *best = 0;
   __syncthreads();
   for (int o = 1; o < kHiBT; o <<= 1) {  // inclusive suffix sums
-    const int32_t u = threadIdx.x + o < kHiBT ? red[threadIdx.x + o] : 0;
+    const uint32_t u = threadIdx.x + o < kHiBT ? red[threadIdx.x + o] : 0u;
     __syncthreads();
     red[threadIdx.x] += u;
     __syncthreads();
   }
-  const int32_t after = red[threadIdx.x] - sum;
+  const uint32_t later = above + (red[threadIdx.x] - sum);
 #pragma unroll
   for (int i = 0; i < kPer; ++i) {
-    const int t = (int)threadIdx.x * kPer + i + 1;
-    if (c[i] + after >= t + base) atomicMax(best, t);
+    const int b = (int)threadIdx.x * kPer + i;
+    if (b < n && c[i] + later >= lo + ((uint32_t)b << shift)) atomicMax(best, b);
   }
   __syncthreads();
-  return *best;
+  const int b = *best;
+  // the thread of bin b leaves the neighbours past it in red[0]
+  if (b / kPer == (int)threadIdx.x) {
+    uint32_t past = later;
+#pragma unroll
+    for (int i = 1; i < kPer; ++i)
+      if (i == b % kPer + 1) past = c[i] + later;
+    red[0] = past;
+  }
+  __syncthreads();
+  return {lo + ((uint32_t)b << shift), red[0], shift};
 }
 
-// h of one row by a block, starting from a histogram that already holds the
-// whole row with base 0.
-__device__ __forceinline__ void hindex_finish(const int32_t* __restrict__ ptr, const int32_t* __restrict__ col,
-                                              int32_t v, int32_t* lh, int32_t* red, int* best,
-                                              int32_t* __restrict__ key) {
-  int32_t base = 0;
-  for (;;) {
-    const int t = hindex_meet(lh, base, red, best);
-    if (t < kHiBins) {  // also 0: h is the base itself
-      if (threadIdx.x == 0) key[v] = base + t;
-      __syncthreads();
-      return;
-    }
-    base += kHiBins;  // at most n_edges / kHiBins windows
-    __syncthreads();
-    for (int i = threadIdx.x; i <= kHiBins; i += kHiBT) lh[i] = 0;
-    __syncthreads();
-    hindex_add(ptr, col, ptr[v], ptr[v + 1], base, lh);
-    __syncthreads();
-  }
+// h, or the range that holds it, from a row's histogram.
+__device__ __forceinline__ HiRange hindex_first(const int32_t* lh, int shift, uint32_t* red, int* best) {
+  const int32_t many = lh[kHiBins];
+  if (many < kHiBins) return hindex_meet(lh, kHiBins, 0, 0, (uint32_t)many, red, best);
+  return hindex_meet(lh + kHiBins + 1, kHiRanges, kHiBins, shift, 0, red, best);
+}
+
+// Counts the neighbours [beg, end) of a range by its bins.
+__device__ __forceinline__ void hindex_add_range(const int32_t* __restrict__ ptr, const int32_t* __restrict__ col,
+                                                 int32_t beg, int32_t end, const HiRange& r, int32_t* bins) {
+  const int shift = hindex_bin_shift(r);
+  hindex_walk(ptr, col, beg, end, [&](int32_t x) {
+    const uint32_t at = (uint32_t)x - r.lo;  // past the range for a degree below it
+    if (at >> r.shift == 0) atomicAdd(&bins[at >> shift], 1);
+  });
 }
 
 __global__ void __launch_bounds__(kHiBT) k_hindex_block(const int32_t* __restrict__ ptr,
@@ -752,25 +805,63 @@ __global__ void __launch_bounds__(kHiBT) k_hindex_block(const int32_t* __restric
                                                         const int32_t* __restrict__ list,
                                                         const int32_t* __restrict__ n_list,
                                                         int32_t* __restrict__ key) {
-  __shared__ int32_t lh[kHiBins + 1];
-  __shared__ int32_t red[kHiBT];
+  __shared__ int32_t lh[kHiWords];
+  __shared__ uint32_t red[kHiBT];
   __shared__ int best;
   const int32_t n = n_list[0];
   for (int32_t i = blockIdx.x; i < n; i += gridDim.x) {
-    const int32_t v = list[i];
-    for (int b = threadIdx.x; b <= kHiBins; b += kHiBT) lh[b] = 0;
+    const int32_t v = list[i], beg = ptr[v], end = ptr[v + 1];
+    const int shift = hindex_shift(end - beg);
+    for (int b = threadIdx.x; b < (shift < 0 ? kHiBins + 1 : kHiWords); b += kHiBT) lh[b] = 0;
     __syncthreads();
-    hindex_add(ptr, col, ptr[v], ptr[v + 1], 0, lh);
+    hindex_add(ptr, col, beg, end, shift, lh);
     __syncthreads();
-    hindex_finish(ptr, col, v, lh, red, &best, key);
+    HiRange r = hindex_first(lh, shift, red, &best);
+    while (r.shift > 0) {
+      for (int b = threadIdx.x; b < hindex_bins(r); b += kHiBT) lh[b] = 0;
+      __syncthreads();
+      hindex_add_range(ptr, col, beg, end, r, lh);
+      __syncthreads();
+      r = hindex_meet(lh, hindex_bins(r), r.lo, hindex_bin_shift(r), r.above, red, &best);
+    }
+    if (threadIdx.x == 0) key[v] = (int32_t)r.lo;
+    __syncthreads();
   }
 }
 
-// Long rows: their parts' histograms added into one of kHiBins + 1 words per
-// row (zeroed here first: phase 0), then met by a block per row.
+// Long rows: their parts' histograms added into one of kHiWords words per row
+// (zeroed here first), then met by a block per row, which writes the key or
+// leaves the range that holds it, with zeroed bins, in the row's words (a first
+// word of 0: done).  The parts are then walked by those bins, and met again.
+enum : int { HI_LO = 0, HI_ABOVE, HI_SHIFT, HI_BIN };
+static_assert(HI_BIN + (1 << kHiSplit) <= kHiWords, "a range's bins in the row's words");
+
 __global__ void __launch_bounds__(kHiBT) k_hindex_zero(const int32_t* __restrict__ n_list, int32_t* __restrict__ hist) {
-  const int64_t n = (int64_t)n_list[1] * (kHiBins + 1);
+  const int64_t n = (int64_t)n_list[1] * kHiWords;
   GRID_STRIDE(i, n) hist[i] = 0;
+}
+
+__device__ __forceinline__ RowRange hindex_part(const int32_t* __restrict__ ptr, int32_t v, int part) {
+  const int32_t end = ptr[v + 1], p = ptr[v] + part * kHiPart;
+  return {p, end - p < kHiPart ? end : p + kHiPart};
+}
+
+__device__ __forceinline__ HiRange hindex_left(const int32_t* row) {
+  return {(uint32_t)row[HI_LO], (uint32_t)row[HI_ABOVE], row[HI_SHIFT]};
+}
+
+// Ends a row or leaves its range (all threads of a block; the row's words have
+// been read).
+__device__ __forceinline__ void hindex_leave(const HiRange& r, int32_t* __restrict__ row, int32_t* __restrict__ key) {
+  const bool more = r.shift > 0;
+  if (threadIdx.x == 0) {
+    row[HI_LO] = more ? (int32_t)r.lo : 0;
+    row[HI_ABOVE] = (int32_t)r.above;
+    row[HI_SHIFT] = r.shift;
+    if (!more) *key = (int32_t)r.lo;
+  }
+  if (more)
+    for (int b = threadIdx.x; b < hindex_bins(r); b += kHiBT) row[HI_BIN + b] = 0;
 }
 
 __global__ void __launch_bounds__(kHiBT) k_hindex_parts(const int32_t* __restrict__ ptr,
@@ -779,34 +870,82 @@ __global__ void __launch_bounds__(kHiBT) k_hindex_parts(const int32_t* __restric
                                                         const int2* __restrict__ parts,
                                                         const int32_t* __restrict__ n_list,
                                                         int32_t* __restrict__ hist) {
-  __shared__ int32_t lh[kHiBins + 1];
+  __shared__ int32_t lh[kHiWords];
   const int32_t n = n_list[2];
   for (int32_t i = blockIdx.x; i < n; i += gridDim.x) {
     const int2 pt = parts[i];
-    const int32_t v = list[pt.x], end = ptr[v + 1], p = ptr[v] + pt.y * kHiPart;
-    for (int b = threadIdx.x; b <= kHiBins; b += kHiBT) lh[b] = 0;
+    const int32_t v = list[pt.x];
+    const RowRange p = hindex_part(ptr, v, pt.y);
+    for (int b = threadIdx.x; b < kHiWords; b += kHiBT) lh[b] = 0;
     __syncthreads();
-    hindex_add(ptr, col, p, end - p < kHiPart ? end : p + kHiPart, 0, lh);
+    hindex_add(ptr, col, p.beg, p.end, hindex_shift(deg_of(ptr, v)), lh);
     __syncthreads();
-    for (int b = threadIdx.x; b <= kHiBins; b += kHiBT)
-      if (lh[b]) atomicAdd(&hist[(int64_t)pt.x * (kHiBins + 1) + b], lh[b]);
+    for (int b = threadIdx.x; b < kHiWords; b += kHiBT)
+      if (lh[b]) atomicAdd(&hist[(int64_t)pt.x * kHiWords + b], lh[b]);
     __syncthreads();
   }
 }
 
+// exact: a key of kHiBins or more may not come out as any other such key.
 __global__ void __launch_bounds__(kHiBT) k_hindex_long(const int32_t* __restrict__ ptr,
-                                                       const int32_t* __restrict__ col,
                                                        const int32_t* __restrict__ list,
-                                                       const int32_t* __restrict__ n_list,
-                                                       const int32_t* __restrict__ hist, int32_t* __restrict__ key) {
-  __shared__ int32_t lh[kHiBins + 1];
-  __shared__ int32_t red[kHiBT];
+                                                       const int32_t* __restrict__ n_list, bool exact,
+                                                       int32_t* __restrict__ hist, int32_t* __restrict__ key) {
+  __shared__ int32_t lh[kHiWords];
+  __shared__ uint32_t red[kHiBT];
   __shared__ int best;
   const int32_t n = n_list[1];
   for (int32_t i = blockIdx.x; i < n; i += gridDim.x) {
-    for (int b = threadIdx.x; b <= kHiBins; b += kHiBT) lh[b] = hist[(int64_t)i * (kHiBins + 1) + b];
+    int32_t* row = hist + (int64_t)i * kHiWords;
+    const int32_t v = list[i];
+    for (int b = threadIdx.x; b < kHiWords; b += kHiBT) lh[b] = row[b];
     __syncthreads();
-    hindex_finish(ptr, col, list[i], lh, red, &best, key);
+    HiRange r = hindex_first(lh, hindex_shift(deg_of(ptr, v)), red, &best);
+    if (!exact) r.shift = 0;
+    hindex_leave(r, row, key + v);
+    __syncthreads();
+  }
+}
+
+__global__ void __launch_bounds__(kHiBT) k_hindex_range_parts(const int32_t* __restrict__ ptr,
+                                                              const int32_t* __restrict__ col,
+                                                              const int32_t* __restrict__ list,
+                                                              const int2* __restrict__ parts,
+                                                              const int32_t* __restrict__ n_list,
+                                                              int32_t* __restrict__ hist) {
+  __shared__ int32_t lh[1 << kHiSplit];
+  const int32_t n = n_list[2];
+  for (int32_t i = blockIdx.x; i < n; i += gridDim.x) {
+    const int2 pt = parts[i];
+    int32_t* row = hist + (int64_t)pt.x * kHiWords;
+    const HiRange r = hindex_left(row);
+    if (r.lo == 0) continue;  // the whole block
+    const RowRange p = hindex_part(ptr, list[pt.x], pt.y);
+    for (int b = threadIdx.x; b < hindex_bins(r); b += kHiBT) lh[b] = 0;
+    __syncthreads();
+    hindex_add_range(ptr, col, p.beg, p.end, r, lh);
+    __syncthreads();
+    for (int b = threadIdx.x; b < hindex_bins(r); b += kHiBT)
+      if (lh[b]) atomicAdd(&row[HI_BIN + b], lh[b]);
+    __syncthreads();
+  }
+}
+
+__global__ void __launch_bounds__(kHiBT) k_hindex_range(const int32_t* __restrict__ list,
+                                                        const int32_t* __restrict__ n_list,
+                                                        int32_t* __restrict__ hist, int32_t* __restrict__ key) {
+  __shared__ int32_t lh[1 << kHiSplit];
+  __shared__ uint32_t red[kHiBT];
+  __shared__ int best;
+  const int32_t n = n_list[1];
+  for (int32_t i = blockIdx.x; i < n; i += gridDim.x) {
+    int32_t* row = hist + (int64_t)i * kHiWords;
+    const HiRange r = hindex_left(row);
+    if (r.lo == 0) continue;  // the whole block
+    for (int b = threadIdx.x; b < hindex_bins(r); b += kHiBT) lh[b] = row[HI_BIN + b];
+    __syncthreads();
+    hindex_leave(hindex_meet(lh, hindex_bins(r), r.lo, hindex_bin_shift(r), r.above, red, &best), row, key + list[i]);
+    __syncthreads();
   }
 }
 
@@ -823,11 +962,12 @@ struct HindexBufs {
 inline int64_t hindex_list_b(int64_t E) { return E / kHiWave + 1; }
 inline int64_t hindex_list_l(int64_t E) { return E / kHiBlock + 1; }
 inline int64_t hindex_parts(int64_t E) { return E / kHiPart + hindex_list_l(E); }
-inline int64_t hindex_hist_elems(int64_t E) { return hindex_list_l(E) * (kHiBins + 1); }
+inline int64_t hindex_hist_elems(int64_t E) { return hindex_list_l(E) * kHiWords; }
 
 // key[v] for every node with first[v] < n_edges (every node if first is
-// null); keys above theta may come out as any value above it.  err: device flag, non-zero when an endpoint is out of range (the
-// keys are then unspecified, and nothing is read or written out of bounds).
+// null); keys above theta may come out as any value above it.  err: device flag,
+// non-zero when an endpoint is out of range (the keys are then unspecified, and
+// nothing is read or written out of bounds).
 int hindex_keys(const int32_t* src, const int32_t* dst, int64_t N, int64_t E, const int32_t* first, int32_t theta,
                 int32_t* key, const HindexBufs& b, const int32_t* err, hipStream_t s) {
   uint32_t* ko;
@@ -843,11 +983,23 @@ int hindex_keys(const int32_t* src, const int32_t* dst, int64_t N, int64_t E, co
     HG_LAUNCH("hindex_block", k_hindex_block, dim3(2 * cus), dim3(kHiBT), 0, s, (const int32_t*)b.ptr,
               (const int32_t*)col, (const int32_t*)b.list_b, (const int32_t*)b.n_list, key);
   if (E > kHiBlock) {
-    HG_LAUNCH("hindex_zero", k_hindex_zero, dim3(cus), dim3(kHiBT), 0, s, (const int32_t*)b.n_list, b.hist);
-    HG_LAUNCH("hindex_parts", k_hindex_parts, dim3(2 * cus), dim3(kHiBT), 0, s, (const int32_t*)b.ptr,
-              (const int32_t*)col, (const int32_t*)b.list_l, (const int2*)b.parts, (const int32_t*)b.n_list, b.hist);
-    HG_LAUNCH("hindex_long", k_hindex_long, dim3(cus), dim3(kHiBT), 0, s, (const int32_t*)b.ptr,
-              (const int32_t*)col, (const int32_t*)b.list_l, (const int32_t*)b.n_list, (const int32_t*)b.hist, key);
+    // a block per part and per row, as far as there can be any
+    const dim3 gp((unsigned)std::min<int64_t>(2 * cus, hindex_parts(E)));
+    const dim3 gl((unsigned)std::min<int64_t>(cus, hindex_list_l(E)));
+    HG_LAUNCH("hindex_zero", k_hindex_zero, gl, dim3(kHiBT), 0, s, (const int32_t*)b.n_list, b.hist);
+    HG_LAUNCH("hindex_parts", k_hindex_parts, gp, dim3(kHiBT), 0, s, (const int32_t*)b.ptr, (const int32_t*)col,
+              (const int32_t*)b.list_l, (const int2*)b.parts, (const int32_t*)b.n_list, b.hist);
+    const bool exact = theta >= kHiBins;
+    HG_LAUNCH("hindex_long", k_hindex_long, gl, dim3(kHiBT), 0, s, (const int32_t*)b.ptr, (const int32_t*)b.list_l,
+              (const int32_t*)b.n_list, exact, b.hist, key);
+    // the walks that narrow a row's ranges to one degree: bits of its widest range by kHiSplit
+    const int walks = !exact ? 0 : (E - kHiBins < ((int64_t)(kHiRanges - 1) << kHiSplit) ? 1 : 2);
+    for (int k = 0; k < walks; ++k) {
+      HG_LAUNCH("hindex_range_parts", k_hindex_range_parts, gp, dim3(kHiBT), 0, s, (const int32_t*)b.ptr,
+                (const int32_t*)col, (const int32_t*)b.list_l, (const int2*)b.parts, (const int32_t*)b.n_list, b.hist);
+      HG_LAUNCH("hindex_range", k_hindex_range, gl, dim3(kHiBT), 0, s, (const int32_t*)b.list_l,
+                (const int32_t*)b.n_list, b.hist, key);
+    }
   }
   return HG_OK;
 }
