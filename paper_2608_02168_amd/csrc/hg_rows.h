@@ -38,13 +38,14 @@ constexpr RowRange gap_piece(int32_t lo, int32_t hi, int32_t i) {
 // (100k edges: 50 us at 1024, 14 at 64), and nothing beside it at 200M, where
 // short items would only cost partial rows.  E: the input graph's edges (the
 // plan's capacity follows from them).
+constexpr int32_t kMaxChunk = 1024;
 constexpr int32_t plan_chunk(int64_t E) {
-  return E < ((int64_t)1 << 20) ? 64 : (E < ((int64_t)1 << 23) ? 256 : 1024);
+  return E < ((int64_t)1 << 20) ? 64 : (E < ((int64_t)1 << 23) ? 256 : kMaxChunk);
 }
 
 // How the long rows of the CSC are cut into work items.  A row of up to
 // `whole` entries is one item; one of more is m * blocks pieces of equal
-// length, m = ceil(len / (chunk * blocks)), laid out block by block: the b-th
+// length, m = ceil(len / (row_chunk * blocks)), laid out block by block: the b-th
 // m pieces of every split row stand together.
 //
 // A row's entries ascend by destination and the rows draw on the same
@@ -69,9 +70,21 @@ constexpr PlanCut plan_cut(int64_t E, int64_t ns) {
   return {chunk, blocks, blocks == 1 ? chunk : kMinPiece * blocks - 1};
 }
 
+// Most entries of a piece of a row of len: a row of more than kMostPieces chunks
+// takes longer ones, up to kMaxChunk entries.  One wave adds a row's partial rows
+// in order, at 25 to 70 ns each, so a row's pieces beyond some hundreds cost more
+// there than they save in the pass: a row of 500k of a million edges in pieces
+// of 64 had 340 us (d = 128; 1083 at d = 256) added up behind a pass of 37 us,
+// where 512 take 12 to 30.  256 and 128 pieces measured up to 10 % slower.
+constexpr int32_t kMostPieces = 512;
+constexpr int32_t row_chunk(int32_t len, PlanCut k) {
+  const int32_t c = len / kMostPieces;
+  return c <= k.chunk ? k.chunk : (c < kMaxChunk ? c : kMaxChunk);
+}
+
 // Pieces of a row per block of destinations: 0 for a row that is one item or none.
 constexpr int32_t cuts_of(int32_t len, PlanCut k) {
-  return len > k.whole ? (len - 1) / (k.chunk * k.blocks) + 1 : 0;
+  return len > k.whole ? (len - 1) / (row_chunk(len, k) * k.blocks) + 1 : 0;
 }
 
 // Entries of piece c of the n of row [beg, end).
