@@ -1673,18 +1673,19 @@ __global__ void k_gather_w(const int32_t* __restrict__ eid, const float* __restr
 
 // ---- execution plan -----------------------------------------------------------
 // Tiles of kPN consecutive nodes (kPN * R rows of the CSC: whole 64-row groups
-// of the slot table).  k_plan_count writes, per tile, the number of active
-// rows, whole rows, split rows and their pieces per block, the long destination rows and
-// their chunks, and the active sources of every relation, as 6 + R streams of
-// one count per tile laid end to end; one scan of the whole turns a stream's
-// entry minus its first into the tile's offset (sums may wrap, differences do
-// not).  k_plan_fill forms the in-tile ranks again from ballots and writes the
-// plan.  Two reads of csc_ptr and the plan's own bytes bound it; digits, counts
-// and source ids per row (17 bytes a row) with four scans over all rows and a
-// partition by relation took 1.6 ms at 50M rows where this takes 0.3 ms.
+// of the slot table).  k_plan_count writes, per tile, the number of active rows,
+// the long destination rows and their chunks, the split rows and their pieces per
+// block of both cuts, the entries split by blocks, and the active sources of every
+// relation, as P_REL + R streams of one count per tile laid end to end; one scan
+// of the whole turns a stream's entry minus its first into the tile's offset
+// (sums may wrap, differences do not).  k_plan_fill takes the cut that pays, forms
+// the in-tile ranks again from ballots and writes the plan.  Two reads of csc_ptr
+// and the plan's own bytes bound it; digits, counts and source ids per row (17
+// bytes a row) with four scans over all rows and a partition by relation took 1.6
+// ms at 50M rows where this takes 0.6 ms.
 constexpr int kPN = kBT;
 constexpr int kPW = kPN / 64;
-enum : int { P_ACT = 0, P_WHOLE, P_HEAVY, P_PARTS, P_FHEAVY, P_FPARTS, P_REL };
+enum : int { P_ACT = 0, P_FHEAVY, P_FPARTS, P_HEAVY, P_PARTS, P_LHEAVY, P_LPARTS, P_SPLIT, P_REL };
 
 __device__ __forceinline__ int wave_sum(int v) {
 #pragma unroll
@@ -1711,26 +1712,29 @@ __global__ void __launch_bounds__(kBT) k_plan_count(const int32_t* __restrict__ 
                                                     PlanCut cut, int64_t tiles, int32_t* __restrict__ cnt) {
   __shared__ uint64_t mask[kPW * HG_MAX_REL];
   __shared__ int32_t wcnt[kPW][HG_MAX_REL];
-  __shared__ int32_t wtot[kPW][6];
+  __shared__ int32_t wtot[kPW][P_REL];
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
   const int64_t tile = blockIdx.x, nq = ns * R;
-  int act = 0, whole = 0, heavy = 0, parts = 0;
+  const PlanCut len_cut = by_length(cut);
+  int act = 0, heavy = 0, parts = 0, lheavy = 0, lparts = 0, split = 0;
   for (int g = 0; g < R; ++g) {  // the wave's 64 nodes: R groups of 64 rows
     const int64_t q = (tile * kPN + 64 * w) * R + 64 * g + l;
     const int32_t len = q < nq ? csc_ptr[q + 1] - csc_ptr[q] : 0;
     const uint64_t m = __ballot(len > 0);
     if (l == 0) mask[w * R + g] = m;
-    const int m_row = cuts_of(len, cut);
+    const int m_row = cuts_of(len, cut), l_row = cuts_of(len, len_cut);
     act += len > 0;
-    whole += len > 0 && m_row == 0;
     heavy += m_row > 0;
     parts += m_row;
+    split += m_row > 0 ? len : 0;
+    lheavy += l_row > 0;
+    lparts += l_row;
   }
   const int64_t j = tile * kPN + threadIdx.x;
   const int fch = j < ns ? fwd_chunks_of(csr_ptr[(j + 1) * R] - csr_ptr[j * R]) : 0;
-  const int v[6] = {act, whole, heavy, parts, fch > 0, fch};
+  const int v[P_REL] = {act, fch > 0, fch, heavy, parts, lheavy, lparts, split};
 #pragma unroll
-  for (int i = 0; i < 6; ++i) {
+  for (int i = 0; i < P_REL; ++i) {
     const int t = wave_sum(v[i]);
     if (l == 0) wtot[w][i] = t;
   }
@@ -1741,13 +1745,13 @@ __global__ void __launch_bounds__(kBT) k_plan_count(const int32_t* __restrict__ 
     if (l == 0) wcnt[w][r] = (int32_t)__popcll(m);
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < 6 + R; i += kBT) {
+  for (int i = threadIdx.x; i < P_REL + R; i += kBT) {
     int32_t t = 0;
 #pragma unroll
-    for (int q = 0; q < kPW; ++q) t += i < 6 ? wtot[q][i] : wcnt[q][i - 6];
+    for (int q = 0; q < kPW; ++q) t += i < P_REL ? wtot[q][i] : wcnt[q][i - P_REL];
     cnt[(int64_t)i * tiles + tile] = t;
   }
-  if (tile == 0 && threadIdx.x == 0) cnt[(int64_t)(6 + R) * tiles] = 0;  // the scan's end: the grand total
+  if (tile == 0 && threadIdx.x == 0) cnt[(int64_t)(P_REL + R) * tiles] = 0;  // the scan's end: the grand total
 }
 
 struct PlanOut {
@@ -1781,17 +1785,22 @@ __device__ __forceinline__ void wave_pieces(int4* __restrict__ items, int32_t pe
 
 __global__ void __launch_bounds__(kBT) k_plan_fill(const int32_t* __restrict__ csc_ptr,
                                                    const int32_t* __restrict__ csr_ptr, int64_t ns, int32_t R,
-                                                   PlanCut cut, int64_t tiles, const int32_t* __restrict__ S, PlanOut o,
+                                                   PlanCut want, int64_t tiles, const int32_t* __restrict__ S, PlanOut o,
                                                    int32_t* __restrict__ cnt) {
   __shared__ uint64_t mask[kPW * HG_MAX_REL];
   __shared__ int32_t before[kPW * HG_MAX_REL];  // active rows before each 64-row group
   __shared__ int32_t wcnt[kPW][HG_MAX_REL];
-  __shared__ int32_t wtot[kPW][6];
+  __shared__ int32_t wtot[kPW][P_PARTS + 1];
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
   const uint64_t lt = (l == 0) ? 0ull : (~0ull >> (64 - l));
   const int64_t tile = blockIdx.x, nq = ns * R;
-  const bool by_row = row_layout(nq, S[tiles] - S[0]);
-  int act = 0, whole = 0, heavy = 0, parts = 0;
+  const auto total = [&](int stream) { return S[(stream + 1) * tiles] - S[stream * tiles]; };
+  const bool by_row = row_layout(nq, total(P_ACT));
+  const bool in_blocks =
+      want.blocks > 1 && blocks_pay(want, csr_ptr[nq], (int64_t)total(P_PARTS) * want.blocks, total(P_SPLIT));
+  const PlanCut cut = in_blocks ? want : by_length(want);
+  const int cut_at = in_blocks ? 0 : P_LHEAVY - P_HEAVY;  // streams of the cut taken
+  int act = 0, heavy = 0, parts = 0;
   for (int g = 0; g < R; ++g) {
     const int64_t q = (tile * kPN + 64 * w) * R + 64 * g + l;
     const int32_t len = q < nq ? csc_ptr[q + 1] - csc_ptr[q] : 0;
@@ -1799,16 +1808,15 @@ __global__ void __launch_bounds__(kBT) k_plan_fill(const int32_t* __restrict__ c
     if (l == 0) mask[w * R + g] = m;
     const int m_row = cuts_of(len, cut);
     act += len > 0;
-    whole += len > 0 && m_row == 0;
     heavy += m_row > 0;
     parts += m_row;
   }
   const int64_t j = tile * kPN + threadIdx.x;
   const int32_t fbeg = j < ns ? csr_ptr[j * R] : 0, fend = j < ns ? csr_ptr[(j + 1) * R] : 0;
   const int fch = fwd_chunks_of(fend - fbeg);
-  const int v[6] = {act, whole, heavy, parts, fch > 0, fch};
+  const int v[P_PARTS + 1] = {act, fch > 0, fch, heavy, parts};
 #pragma unroll
-  for (int i = 0; i < 6; ++i) {
+  for (int i = 0; i <= P_PARTS; ++i) {
     const int t = wave_sum(v[i]);
     if (l == 0) wtot[w][i] = t;
   }
@@ -1818,11 +1826,12 @@ __global__ void __launch_bounds__(kBT) k_plan_fill(const int32_t* __restrict__ c
     if (l == 0) wcnt[w][r] = (int32_t)__popcll(m);
   }
   __syncthreads();
-  const int32_t per_block = S[4 * tiles] - S[3 * tiles];  // pieces of each block
-  int32_t at[6];  // the wave's offset in each stream
+  const int32_t per_block = total(P_PARTS + cut_at);  // pieces of each block
+  int32_t at[P_PARTS + 1];  // the wave's offset in each stream
 #pragma unroll
-  for (int i = 0; i < 6; ++i) {
-    at[i] = S[i * tiles + tile] - S[i * tiles];
+  for (int i = 0; i <= P_PARTS; ++i) {
+    const int64_t p = i < P_HEAVY ? i : i + cut_at;
+    at[i] = S[p * tiles + tile] - S[p * tiles];
     for (int q = 0; q < w; ++q) at[i] += wtot[q][i];
   }
   for (int g = 0; g < R; ++g) {
@@ -1839,8 +1848,9 @@ __global__ void __launch_bounds__(kBT) k_plan_fill(const int32_t* __restrict__ c
       if (l == 0 && live) o.tab[q >> 6] = SlotEnt{m, at[P_ACT], 0};
     }
     // the pieces of the split rows come first, block by block
-    if (end > beg && mr == 0)
-      o.items[per_block * cut.blocks + at[P_WHOLE] + (int32_t)__popcll(om & lt)] = make_int4(sl, beg, end, -1);
+    if (end > beg && mr == 0)  // after the whole rows, i.e. active ones not split, before it
+      o.items[per_block * cut.blocks + at[P_ACT] - at[P_HEAVY] + (int32_t)__popcll(om & lt)] =
+          make_int4(sl, beg, end, -1);
     if (hm) {
       const int32_t so = at[P_PARTS] + wave_before(mr);
       if (mr > 0) o.heavy[at[P_HEAVY] + (int32_t)__popcll(hm & lt)] = make_int4(sl, so * cut.blocks, mr * cut.blocks, 0);
@@ -1853,7 +1863,6 @@ __global__ void __launch_bounds__(kBT) k_plan_fill(const int32_t* __restrict__ c
       at[P_HEAVY] += (int32_t)__popcll(hm);
     }
     at[P_ACT] += (int32_t)__popcll(m);
-    at[P_WHOLE] += (int32_t)__popcll(om);
   }
   // active sources of every relation, ascending, with their slots
   __builtin_amdgcn_wave_barrier();
@@ -1886,12 +1895,12 @@ __global__ void __launch_bounds__(kBT) k_plan_fill(const int32_t* __restrict__ c
     for (int r = threadIdx.x; r <= R; r += kBT)
       o.act_off[r] = o.act_off_copy[r] = S[(int64_t)(P_REL + r) * tiles] - S[(int64_t)P_REL * tiles];
     if (threadIdx.x == 0) {
-      cnt[C_ASLOTS] = S[tiles] - S[0];
-      cnt[C_ITEMS] = S[2 * tiles] - S[tiles] + per_block * cut.blocks;
-      cnt[C_HEAVY] = S[3 * tiles] - S[2 * tiles];
+      cnt[C_ASLOTS] = total(P_ACT);
+      cnt[C_HEAVY] = total(P_HEAVY + cut_at);
       cnt[C_PARTS] = per_block * cut.blocks;
-      cnt[C_FHEAVY] = S[5 * tiles] - S[4 * tiles];
-      cnt[C_FPARTS] = S[6 * tiles] - S[5 * tiles];
+      cnt[C_ITEMS] = cnt[C_ASLOTS] - cnt[C_HEAVY] + cnt[C_PARTS];
+      cnt[C_FHEAVY] = total(P_FHEAVY);
+      cnt[C_FPARTS] = total(P_FPARTS);
     }
   }
 }
@@ -1912,8 +1921,8 @@ __global__ void k_csr_slot(const int32_t* __restrict__ csr_col, const uint32_t* 
 // destinations fit in 24 bits.
 constexpr int64_t kPackedMaxNodes = (int64_t)1 << 24;
 
-// Counts of the plan's tiles: 6 + R streams and the end of the scan.
-inline int64_t plan_counts(int64_t n, int64_t R) { return (6 + R) * cdiv(n > 0 ? n : 1, kPN) + 1; }
+// Counts of the plan's tiles: P_REL + R streams and the end of the scan.
+inline int64_t plan_counts(int64_t n, int64_t R) { return (P_REL + R) * cdiv(n > 0 ? n : 1, kPN) + 1; }
 
 // Workspace layout, shared by the sizing and the run.
 template <class A>
@@ -2374,7 +2383,7 @@ extern "C" int hg_build_csr(const hg_graph_desc* g, const hg_overlap_desc* o, hg
                      tab};
     HG_LAUNCH("build_plan_count", k_plan_count, dim3((unsigned)tiles), dim3(kBT), 0, s, (const int32_t*)out->csc_ptr,
               (const int32_t*)out->csr_ptr, NS, (int32_t)R, cut, tiles, w.pcnt);
-    HG_TRY(scan_exclusive_i32(w.pcnt, w.pcnt, (6 + R) * tiles + 1, nullptr, w.scratch, s));
+    HG_TRY(scan_exclusive_i32(w.pcnt, w.pcnt, (P_REL + R) * tiles + 1, nullptr, w.scratch, s));
     HG_LAUNCH("build_plan_fill", k_plan_fill, dim3((unsigned)tiles), dim3(kBT), 0, s, (const int32_t*)out->csc_ptr,
               (const int32_t*)out->csr_ptr, NS, (int32_t)R, cut, tiles, (const int32_t*)w.pcnt, po, w.cnt);
     if (ES > 0)

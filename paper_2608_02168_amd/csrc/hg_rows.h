@@ -54,9 +54,10 @@ constexpr int32_t plan_chunk(int64_t E) {
 // the Infinity Cache.  Gathers of 512-byte rows run at 9.3 TB/s from 64 MB,
 // 7.2 from 256 MB and 4.5 from 2.5 GB and more; blocks of 128k and 512k nodes
 // measured 0-3 % slower.  A piece costs a float64 partial row written and read
-// (2 KB at d = 128), so a row is split only into pieces of kMinPiece entries
-// and more (16 and 32 measured 0-3 % slower).  Destinations that fit one block
-// are gathered from the cache as they are: rows are cut by length alone.
+// (2 KB at d = 128, 0.4 ns of the whole chip), so a row is split only into pieces
+// of kMinPiece entries and more (16 and 32 measured 0-3 % slower).  Destinations
+// that fit one block are gathered from the cache as they are: rows are cut by
+// length alone.
 struct PlanCut {
   int32_t chunk, blocks, whole;
 };
@@ -68,6 +69,26 @@ constexpr PlanCut plan_cut(int64_t E, int64_t ns) {
   const int32_t chunk = plan_chunk(E);
   const int32_t blocks = (int32_t)std::max<int64_t>(1, std::min<int64_t>((ns - 1) / kBlockNodes + 1, kMaxBlocks));
   return {chunk, blocks, blocks == 1 ? chunk : kMinPiece * blocks - 1};
+}
+
+// The cut by length alone.
+constexpr PlanCut by_length(PlanCut k) { return {k.chunk, 1, k.chunk}; }
+
+// Whether the cut by blocks pays in a subgraph of e edges, of which it splits
+// rows of `split` entries into `pieces`.  Blocks gain where hubs' long pieces run
+// beside many short rows: Zipf sources of 20 edges a node have 150 to 480 edges to
+// a piece and 0.2 to 0.9 of them in split rows, and their backward takes up to 17 %
+// less at 2.5M nodes and more and 0 to 3 % at a million.  Where all rows are alike
+// and long the waves walk the destinations in step, and blocks only cost the
+// partial rows: 0.3M to 2M nodes of 50 to 200 edges in one relation take 2 to 17 %
+// more in blocks (25 to 100 edges to a piece, all split), 4M and 10M nodes whose
+// edges leave a few rows of 400 to 1000 up to 16 %, a million nodes of 60 edges
+// (log-normal, 120 to a piece) 2 to 5 %.  The bound also keeps the partial rows
+// below a hundredth of the edges.
+constexpr int32_t kFewBlocks = 8;
+constexpr int64_t kEdgesPerPiece = 100, kEdgesPerPieceFew = 200;
+constexpr bool blocks_pay(PlanCut k, int64_t e, int64_t pieces, int64_t split) {
+  return pieces * (k.blocks <= kFewBlocks ? kEdgesPerPieceFew : kEdgesPerPiece) <= e && 16 * split <= 15 * e;
 }
 
 // Most entries of a piece of a row of len: a row of more than kMostPieces chunks
