@@ -1,0 +1,105 @@
+"""Backward of the mean layer on graphs whose long rows are cut with chunks of
+256 and 1024 entries, by destination blocks and by length, and where every
+active row is cut; all storage types and widths, against float64 products and
+sums by plain torch: 1e-4 of the value or the RMS for float32, 2e-2 for
+bfloat16, as for all layers, beside the bound that the library states for its
+split products (a hub's row of dH is a hundred times the RMS, and its products
+are exact to about d 2^-21 of the row's largest term, not of each value)."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2608_02168_amd import api, synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _err(got, ref, allowance=0.0):
+    """The largest difference, less the allowance, over the value or the RMS."""
+    ref = ref.double()
+    return float((((got.double() - ref).abs() - allowance) / torch.maximum(ref.abs(), ref.pow(2).mean().sqrt())).max())
+
+
+def _graph(n, lengths, per_row, seed):
+    """Hubs of these lengths in two relations, and per_row entries in every other row."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    hubs = torch.randperm(n, generator=g, device="cuda")[:len(lengths)].to(torch.int32)
+    count = torch.tensor(lengths, device="cuda")
+    src, rel = [torch.repeat_interleave(hubs, count)], [torch.repeat_interleave(torch.arange(len(lengths), device="cuda") % 2, count)]
+    if per_row:
+        src.append(torch.arange(n, device="cuda", dtype=torch.int32).repeat(2 * per_row))
+        rel.append(torch.arange(2, device="cuda").repeat_interleave(n * per_row))
+    src, rel = torch.cat(src), torch.cat(rel).to(torch.uint8)
+    dst = torch.randint(0, n, src.shape, generator=g, device="cuda", dtype=torch.int32)
+    return src, dst, rel, hubs
+
+
+def _reference(n, R, src, dst, rel, hubs, H, G, W_rel, W_self):
+    """dH, dW_rel and dW_self in float64, for ReLU masks of ones and the residual, and the bound that the
+    library states for the products of a row with W: d 2^-21 of the row's largest term times W's."""
+    H, G, W_rel, W_self = H.double(), G.double(), W_rel.double(), W_self.double()
+    dH, dW = G + G @ W_self[0].T, torch.empty_like(W_rel)
+    bound = G.abs().amax(1) * W_self.abs().max()
+    is_hub = torch.zeros(n, dtype=torch.bool, device="cuda")
+    is_hub[hubs.long()] = True
+    for r in range(R):
+        m = rel == r
+        s, t = src[m].long(), dst[m].long()
+        scale = 1.0 / torch.bincount(t, minlength=n).double()
+        dY = torch.zeros_like(G)
+        light = ~is_hub[s]
+        sl, tl = s[light], t[light]
+        for at in range(0, sl.numel(), 1 << 20):
+            k = slice(at, at + (1 << 20))
+            dY.index_add_(0, sl[k], G[tl[k]] * scale[tl[k], None])
+        for h in hubs.long():  # summed apart: millions of additions into one row are slow
+            th = t[s == h]
+            for at in range(0, th.numel(), 1 << 20):
+                k = slice(at, at + (1 << 20))
+                dY[h] += (G[th[k]] * scale[th[k], None]).sum(0)
+        bound += dY.abs().amax(1) * W_rel[r].abs().max()
+        dH += dY @ W_rel[r].T
+        dW[r] = H.T @ dY
+    return dH, dW, (H.T @ G)[None], (bound * (G.shape[1] * 2.0**-21))[:, None]
+
+
+# name: nodes, hubs' lengths, entries of every other row, blocks of destinations that the plan cuts by
+LENGTHS = (71, 72, 73, 255, 256, 257, 768, 769, 1_536, 1_537, 5_000, 20_000, 131_071, 131_073, 200_001)
+CASES = {
+    "chunk256_blocks": (600_001, LENGTHS, 1, 3),
+    "chunk1024_blocks": (600_001, LENGTHS + (1_023, 1_025, 3_072, 3_073, 500_000, 3_000_000), 4, 3),
+    "chunk1024_length": (200_001, LENGTHS + (1_023, 1_025, 2_048, 2_049, 500_000, 3_000_000), 12, 1),
+    "pieces_only": (70_001, (65, 128, 129, 5_000, 9_001), 0, 1),
+}
+
+
+@pytest.mark.parametrize("d,dtype", [(64, "f32"), (128, "f32"), (256, "f32"), (64, "bf16"), (128, "bf16"), (256, "bf16")])
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_long_rows(name, d, dtype):
+    n, lengths, per_row, blocks = CASES[name]
+    src, dst, rel, hubs = _graph(n, list(lengths), per_row, 3)
+    e = src.numel()
+    chunk = 64 if e < 1 << 20 else (256 if e < 1 << 23 else 1_024)
+    z = torch.zeros(n, dtype=torch.uint8, device="cuda")
+    sub = api.hg_build_csr(src, dst, rel, z, z.to(torch.int32), 0, 2, 1, 0)
+    length = np.diff(sub.view("csc_ptr").cpu().numpy())
+    split = length[length > (chunk if blocks == 1 else 24 * blocks - 1)]
+    size = np.maximum(chunk, np.minimum(1_024, split // 512))
+    pieces = int((-(-split // (size * blocks)) * blocks).sum())
+    assert (sub.c.plan_heavy, sub.c.plan_partials) == (split.size, pieces)
+    assert sub.c.plan_items == np.count_nonzero(length) - split.size + pieces
+    dt, tol = (torch.float32, 1e-4) if dtype == "f32" else (torch.bfloat16, 2e-2)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    H = torch.randn((n, d), generator=g, device="cuda").to(dt)
+    G = torch.randn((n, d), generator=g, device="cuda").to(dt)
+    w = synth.layer_weights(3, 0, 2, 1, d, 0.0)
+    W_rel, W_self = torch.from_numpy(w.w_rel).cuda(), torch.from_numpy(w.w_self).cuda()
+    mask = torch.full((n, d // 32), -1, dtype=torch.int32, device="cuda")
+    got = api.hg_layer_bwd(sub, H, W_rel, W_self, mask, G)
+    *ref, bound = _reference(n, 2, src, dst, rel, hubs, H, G, W_rel, W_self)
+    for x, y, what in zip(got, ref, ("dH", "dW_rel", "dW_self")):
+        err = _err(x, y, bound if what == "dH" else 0.0)
+        assert err <= tol, (what, err)
