@@ -202,7 +202,6 @@ int bucket_partition(const uint8_t* digit, const int32_t* val, int64_t n, int nb
 
 // Fill helpers (used instead of hipMemsetAsync so the kernels can be captured).
 int fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);
-int fill_u8(uint8_t* p, uint8_t v, int64_t n, hipStream_t s);
 int fill_f32(float* p, float v, int64_t n, hipStream_t s);
 
 }  // namespace hg

@@ -1005,34 +1005,12 @@ int launch_gemm_rows_bf16(const char* name, int64_t n_rows, const float* W, ALoa
 }
 
 // ---- gemm_tn split-K ----------------------------------------------------------
-// Split-K block -> (chunk, output tile).  At d = 256 the output is four
-// 128 x 128 tiles (ti, tj) that read the same rows of a chunk: the four blocks
-// of a chunk are 8 apart in groups of 32 consecutive blocks, so they go to the
-// same XCD (blocks are dealt round-robin over the 8) at about the same time
-// and the rows come from HBM once, then from that XCD's L2.  The grid covers
-// the chunk count rounded up to 8; a block past the last chunk has no rows.
-template <int D>
-__device__ __forceinline__ void tn_block(int64_t& chunk, int& ti, int& tj) {
-  if constexpr (D == 256) {
-    const unsigned b = blockIdx.x;
-    const int t = (int)((b >> 3) & 3u);
-    chunk = (int64_t)(((b >> 5) << 3) | (b & 7u));
-    ti = t >> 1;
-    tj = t & 1;
-  } else {
-    chunk = blockIdx.x;
-    ti = tj = 0;
-  }
-}
-inline unsigned tn_grid(int D, int64_t chunks) {
-  return (unsigned)(D == 256 ? 4 * cdiv(chunks, 8) * 8 : chunks);
-}
-
 // Weight gradients of one launch: up to kTnJobs products A^T B of the same
 // storage types, in groups of jobs with the same row count (products that read
 // the same rows: the gates of one state, the projections of one input).  A
-// group takes T q blocks per chunk (T output tiles, q jobs), 8 apart in block
-// index, so they run on one XCD at about the same time and a row that several
+// group takes T q blocks per chunk (T output tiles, q jobs; four 128 x 128 tiles
+// at d = 256), 8 apart in block index, so they run on one XCD (blocks are dealt
+// round-robin over the 8) at about the same time and a row that several
 // of them read comes from HBM once.  Chunk c of a job writes partial row
 // chunk0[job] + c.
 constexpr int kTnJobs = 24;
@@ -1085,22 +1063,18 @@ template <int D, class LA, class LB, bool kListA, bool kListB>
 __global__ void __launch_bounds__(256) k_gemm_tn(int64_t n_rows, int64_t kc, LA la, LB lb,
                                                  float* __restrict__ partial,
                                                  float* __restrict__ colsum) {
-  static_assert(D == 64 || D == 128 || D == 256, "gemm_tn: d must be 64, 128 or 256");
+  static_assert(D == 64 || D == 128, "gemm_tn: d must be 64 or 128");
   constexpr bool kQuad = (D >= 128);
   const int w = threadIdx.x >> 6;
   const int l = lane64();
   const int g = l >> 4, c = l & 15;
-  int64_t chunk;
-  int ti, tj;
-  tn_block<D>(chunk, ti, tj);
-  const int64_t k_beg = chunk * kc;
-  if (k_beg >= n_rows) return;  // a padding block (the whole block)
+  const int64_t chunk = blockIdx.x, k_beg = chunk * kc;
   const int64_t k_end = (k_beg + kc < n_rows) ? k_beg + kc : n_rows;
   const int qi = kQuad ? (w >> 1) : 0;
   const int qj = kQuad ? (w & 1) : 0;
   const int64_t step0 = kQuad ? 0 : 4 * w;
   const int64_t stride = kQuad ? 4 : 16;
-  const int ca = 128 * ti + 64 * qi + 4 * c, cb = 128 * tj + 64 * qj + 4 * c;
+  const int ca = 64 * qi + 4 * c, cb = 64 * qj + 4 * c;
   f32x4 acc[4][4];
   f32x4 bs = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -1189,13 +1163,13 @@ __global__ void __launch_bounds__(256) k_gemm_tn(int64_t n_rows, int64_t kc, LA 
     for (int bi = 0; bi < 4; ++bi)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int64_t i = 128 * ti + 64 * qi + 4 * (4 * g + v) + bi;
+        const int64_t i = 64 * qi + 4 * (4 * g + v) + bi;
         f32x4 row4;
 #pragma unroll
         for (int bj = 0; bj < 4; ++bj) row4[bj] = acc[bi][bj][v];
         *reinterpret_cast<f32x4*>(out + i * D + cb) = row4;
       }
-    if (colsum && ti == 0 && qi == 0 && g == 0) *reinterpret_cast<f32x4*>(colsum + chunk * D + cb) = bs;
+    if (colsum && qi == 0 && g == 0) *reinterpret_cast<f32x4*>(colsum + chunk * D + cb) = bs;
   } else {
     __shared__ float red[64 * 64];
     __shared__ float cred[64];
@@ -1848,7 +1822,7 @@ int launch_gemm_tn(const char* name, int64_t n_rows, LA la, LB lb, float* partia
   outs.o[0] = TnOut{out, out_colsum, 0, (int32_t)chunks, accumulate};
   float* cs = out_colsum ? colsum : nullptr;
   if (chunks > 0) {
-    const dim3 grid(tn_grid(D, chunks));
+    const dim3 grid((unsigned)chunks);
     if (la.map.list) {
       HG_LAUNCH(name, (k_gemm_tn<D, LA, LB, true, false>), grid, dim3(256), 0, s, n_rows, kc, la, lb, partial, cs);
     } else {

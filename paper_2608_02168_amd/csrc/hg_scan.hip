@@ -497,7 +497,6 @@ int bucket_partition(const uint8_t* digit, const int32_t* val, int64_t n, int nb
 }
 
 int fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s) { return fill_impl(p, v, n, s); }
-int fill_u8(uint8_t* p, uint8_t v, int64_t n, hipStream_t s) { return fill_impl(p, v, n, s); }
 int fill_f32(float* p, float v, int64_t n, hipStream_t s) { return fill_impl(p, v, n, s); }
 
 }  // namespace hg
