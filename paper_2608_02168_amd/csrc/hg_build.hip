@@ -312,20 +312,21 @@ struct LdsAgg {
   }
 };
 
-// Launch shape of the aggregation passes: blocks of 512 threads, three per
-// compute unit (the edge pass's three tables take 48 KB of LDS), each working
-// through a long stretch of edges before it flushes its table.
-constexpr int kAggBT = 512;
-inline unsigned agg_grid(int64_t n, int per_cu = 3) {
-  const int64_t b = cdiv(n > 0 ? n : 1, kAggBT), cap = (int64_t)num_cus() * per_cu;
+// Launch shape of the aggregation passes: blocks of 512 threads, two per
+// compute unit (the edge pass's three tables and the base summary take 56 KB of
+// LDS, the out-degree table 64), each working through a long stretch of edges
+// before it flushes its tables.
+constexpr int kAggBT = 512, kAggPerCu = 2;
+inline unsigned agg_grid(int64_t n) {
+  const int64_t b = cdiv(n > 0 ? n : 1, kAggBT), cap = (int64_t)num_cus() * kAggPerCu;
   return (unsigned)(b < cap ? b : cap);
 }
 
 // The out-degree counts: every edge adds 1 to its source, and with Zipf
 // sources a few thousand hubs take most of the edges.  A table of 2^13 slots
-// (64 KB, two blocks per compute unit) keeps far more of them than the
-// 2^11-slot tables of the passes that hold several tables at once.
-constexpr int kDegBits = 13, kDegSlots = 1 << kDegBits, kDegPerCu = 2;
+// keeps far more of them than the 2^11-slot tables of the pass that holds
+// several tables at once.
+constexpr int kDegBits = 13, kDegSlots = 1 << kDegBits;
 constexpr int kEpItems = 4;
 
 // Range checks and the candidates C_k: every node outside V_k joined to V_k
@@ -1941,34 +1942,36 @@ struct BuildWs {
   uint32_t *kcsr, *kcsc, *kalt, *bbits, *mbits;
   RankEnt* rt;
   int32_t* tile_cnt;
-  void layout(A& a, int64_t N, int64_t E, int64_t R, bool hindex, bool weighted) {
+  void layout(A& a, int64_t N, int64_t E, int64_t R, int64_t T, bool hindex, bool weighted) {
     const int64_t NQ = N * R + 1;
+    const bool ranks = T <= 2;              // local ids from the rank table, keep as a bit per edge
+    const int64_t NT = ranks ? 0 : N;       // the buffers of more node types
     cnt = a.template take<int32_t>(C_COUNT + HG_MAX_NTYPE + 1 + HG_MAX_REL + 1);
     bcnt = a.template take<uint32_t>(16384);  // block counts of k_init_nodes (grid_for caps it there)
     outdeg = a.template take<int32_t>(N);
     first = a.template take<int32_t>(N);
     key = a.template take<int32_t>(N);
-    flag = a.template take<int32_t>(N + 1);
-    pos = a.template take<int32_t>(N + 1);
+    flag = a.template take<int32_t>(NT);
+    pos = a.template take<int32_t>(NT);
     list = a.template take<int32_t>(N);
-    iota = a.template take<int32_t>(N);
+    iota = a.template take<int32_t>(NT);
     hptr = a.template take<int32_t>(hindex ? N + 1 : 0);
     list_b = a.template take<int32_t>(hindex ? hindex_list_b(E) : 0);
     list_l = a.template take<int32_t>(hindex ? hindex_list_l(E) : 0);
     parts = a.template take<int2>(hindex ? hindex_parts(E) : 0);
     hist = a.template take<int32_t>(hindex ? hindex_hist_elems(E) : 0);
-    sel = a.template take<uint8_t>(N);
+    sel = a.template take<uint8_t>(NT);
     bbits = a.template take<uint32_t>(N / 32 + 2);
     bsum = a.template take<uint2>(kSumGroups / 32);
-    mbits = a.template take<uint32_t>(2 * (N / 64 + 1));
+    mbits = a.template take<uint32_t>(ranks ? 0 : 2 * (N / 64 + 1));
     // rank groups: cdiv(N, 64) * 2 <= N / 32 + 2
     rt = a.template take<RankEnt>(N / kRankGroup + 2);
     sel_bits = a.template take<uint64_t>(N / 64 + 1);
     tcnt = a.template take<int32_t>(4 * cdiv(N, kNTile) + 1);
     tile_cnt = a.template take<int32_t>(E / kETile + 2);
-    digit = a.template take<uint8_t>(N);
+    digit = a.template take<uint8_t>(NT);
     st = a.template take<SelectState>(1);
-    keep = a.template take<int32_t>(E + 1);
+    keep = a.template take<int32_t>(ranks ? 2 * cdiv(E, 64) : E + 1);
     kcsr = a.template take<uint32_t>(E);
     kcsc = a.template take<uint32_t>(E);
     kalt = a.template take<uint32_t>(E);
@@ -2144,7 +2147,7 @@ extern "C" int hg_node_keys(const hg_graph_desc* g, int32_t key, int32_t* keys, 
                         w.parts, w.gaps, w.cnt + C_GAP_HI, w.cnt + C_HI_BLOCK};
     HG_TRY(hindex_keys(g->src, g->dst, N, E, nullptr, HG_THETA_NONE, keys, hb, w.cnt + C_ERR, s));
   } else if (E > 0) {
-    HG_LAUNCH("keys_outdeg", k_all_outdeg, dim3(agg_grid(E, kDegPerCu)), dim3(kAggBT), 0, s, g->src, g->dst, g->rel, N, E,
+    HG_LAUNCH("keys_outdeg", k_all_outdeg, dim3(agg_grid(E)), dim3(kAggBT), 0, s, g->src, g->dst, g->rel, N, E,
               g->n_rel, keys, w.cnt);
   }
   int32_t herr = 0;
@@ -2158,7 +2161,7 @@ extern "C" size_t hg_build_csr_workspace_size(const hg_graph_desc* g, const hg_o
   if (validate_build(g, o) != HG_OK) return 0;
   Sizer sz;
   BuildWs<Sizer> w;
-  w.layout(sz, g->n_nodes, g->n_edges, g->n_rel, o->key == HG_KEY_HINDEX, g->edge_w != nullptr);
+  w.layout(sz, g->n_nodes, g->n_edges, g->n_rel, g->n_ntype, o->key == HG_KEY_HINDEX, g->edge_w != nullptr);
   return sz.used + 256;
 }
 
@@ -2185,7 +2188,7 @@ extern "C" int hg_build_csr(const hg_graph_desc* g, const hg_overlap_desc* o, hg
 
   Arena arena(ws, ws_bytes);
   BuildWs<Arena> w;
-  w.layout(arena, N, E, R, hindex, g->edge_w != nullptr);
+  w.layout(arena, N, E, R, T, hindex, g->edge_w != nullptr);
   if (!arena.ok()) return fail(HG_ERR_CAPACITY, "workspace layout overflow");
 
   const unsigned gN = grid_for(N), gE = grid_for(E);
@@ -2204,7 +2207,7 @@ extern "C" int hg_build_csr(const hg_graph_desc* g, const hg_overlap_desc* o, hg
   HG_LAUNCH("build_base_summary", k_base_summary, dim3((unsigned)cdiv(((N - 1) >> sshift) + 1, kBT)), dim3(kBT), 0, s,
             (const uint32_t*)w.bbits, N, sshift, w.bsum);
   if (E > 0)
-    HG_LAUNCH("build_edges_pass", k_edges_pass, dim3(agg_grid(E, kDegPerCu)), dim3(kAggBT), 0, s, g->src, g->dst,
+    HG_LAUNCH("build_edges_pass", k_edges_pass, dim3(agg_grid(E)), dim3(kAggBT), 0, s, g->src, g->dst,
               g->rel, (const uint32_t*)w.bbits, N, E, (int32_t)R, (!hindex && !o->node_key) ? 1 : 0,
               o->budget_M, (const uint2*)w.bsum, sshift, w.outdeg, w.first, w.cnt);
   // 2. keys: the caller's, when given (they do not depend on k); the h-index;
