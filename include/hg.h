@@ -35,7 +35,8 @@
  *    (hg_timing_*) and the static device scratch of
  *    hg_align_loss_fwd_bwd_noalloc.  Calls on disjoint buffers are re-entrant.
  *  - `stream` is a hipStream_t passed as void* (NULL = the default stream).
- *    Everything except hg_build_csr is asynchronous on that stream.
+ *    Everything except hg_build_csr and hg_node_keys is asynchronous on that
+ *    stream.
  *  - Return value: HG_OK (0) or a negative HG_ERR_* code.  Arguments are
  *    validated on the host before any device work; on error nothing is
  *    launched (except HG_ERR_RANGE / HG_ERR_HIP, see hg_build_csr) and
@@ -218,8 +219,9 @@ size_t hg_plan_size(int64_t n_nodes, int64_t n_edges, int32_t n_rel);
 size_t hg_build_csr_workspace_size(const hg_graph_desc* g, const hg_overlap_desc* o);
 
 /* Build the overlapping subgraph of partition g->k.  SYNCHRONOUS: it
- * synchronises `stream` once at the end, checks the device-side range flag
- * and fills the host fields of *out.  Returns HG_ERR_RANGE if any src/dst is
+ * synchronises `stream` twice (once the counts that size the sorts are there,
+ * with the device-side range flag, and at the end) and fills the host fields
+ * of *out.  Returns HG_ERR_RANGE if any src/dst is
  * outside [0, n_nodes), rel >= n_rel or ntype >= n_ntype (device arrays are
  * then unspecified).  ws: ws_bytes >= hg_build_csr_workspace_size(). */
 int hg_build_csr(const hg_graph_desc* g, const hg_overlap_desc* o, hg_subgraph* out,
@@ -296,8 +298,9 @@ typedef struct hg_hgt_weights {
   const float *W_agg, *b_agg;
 } hg_hgt_weights;
 
-/* Gradients, same shapes as hg_hgt_weights; all OVERWRITTEN.  A bias
- * gradient may be NULL (not computed). */
+/* Gradients, same shapes as hg_hgt_weights; OVERWRITTEN or added into (see
+ * hg_hgt_bwd).  A bias gradient may be NULL (not computed).  Names may share
+ * a buffer (tied weights): with accumulate = 1 it collects all of them. */
 typedef struct hg_hgt_grads {
   float *W_K, *b_K, *W_Q, *b_Q, *W_V, *b_V;
   float *W_att, *W_msg, *mu;
@@ -356,7 +359,7 @@ int hg_align_loss_fwd_bwd(int64_t M, int32_t d, int32_t dtype, int64_t n_rows,
  * array of hg_align_noalloc_scratch_size() bytes (48 MiB) that every device
  * the library runs on holds until the process ends; it covers every batch
  * size at d <= 256 (the workspace of hg_align_loss_fwd_bwd is at most about
- * 43 MiB), and a call that would need more returns HG_ERR_CAPACITY.  The
+ * 46 MiB), and a call that would need more returns HG_ERR_CAPACITY.  The
  * call allocates nothing.  Arguments, results and errors are those of
  * hg_align_loss_fwd_bwd, bit for bit.  All calls on one device share its
  * scratch, which keeps the last call's contents (nothing in it has to start
@@ -418,7 +421,7 @@ int hg_adam_step(int64_t n, float* param, const float* grad, float* m, float* v,
  * block of a GRU cell's stacked input weight, likewise Wh -- and bi, bh
  * [3, d] (either may be NULL = 0).  Rows (h, every c_k, H, dH, dh, dC_k) are
  * [n, d] in dtype (float32 or bfloat16).  C and dC are HOST arrays of w
- * DEVICE pointers.  Requires d = 64 and 0 <= w <= 4. */
+ * DEVICE pointers (C may be NULL when w = 0 or n = 0).  Requires d = 64 and 0 <= w <= 4. */
 typedef struct hg_temporal_weights {
   const float *Q, *r, *Wi, *bi, *Wh, *bh;
 } hg_temporal_weights;
