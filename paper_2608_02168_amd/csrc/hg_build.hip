@@ -1010,14 +1010,15 @@ int hindex_keys(const int32_t* src, const int32_t* dst, int64_t N, int64_t E, co
 // histogram and that into the state's; the block that finishes last picks the
 // digit holding the k_rem-th smallest and narrows the range.  The first launch
 // also finds the candidates (their list is in no order: the search needs only
-// the set).  Two hash digits leave about a candidate in four million, and one
-// more launch lists that small range for the ranking: of up to 10^9 candidates
-// the search ends in three launches where the boundary's key is below 2047 and
-// in six where most candidates share a larger one (three key digits come first).
-// With five, k_select_finish's one block went on with the list: 26 ms at 10M
-// equal keys, where the build takes 3.2 with small ones.  8 launches of about 4
-// us where 16 digits of 8 bits took 33; one with nothing left to do takes 2.
-constexpr int kSelSteps = 6;
+// the set).  Two hash digits leave about a candidate in four million, one a
+// range small enough to rank where there are up to 2^18, and one more launch
+// lists that range for the ranking.  Candidates that share a key of 2047 or more
+// need three key digits before those, so five launches end the search among up to
+// 2^18 candidates and six among 10^9.  With five for all, k_select_finish's one
+// block went on with the list: 26 ms at 10M equal keys, where the build takes 3.2
+// with small ones.  8 launches of about 4 us where 16 digits of 8 bits took 33;
+// one with nothing left to do takes 2.
+inline int select_steps(int64_t n) { return n <= ((int64_t)1 << 18) ? 5 : 6; }
 constexpr int kSelBT = 256;
 constexpr int kSelItems = 8;
 
@@ -2224,7 +2225,7 @@ extern "C" int hg_build_csr(const hg_graph_desc* g, const hg_overlap_desc* o, hg
   const unsigned gS = (unsigned)std::min<int64_t>(cdiv(N, kSelBT * kSelItems), 2 * (int64_t)num_cus());
   HG_LAUNCH("build_candidates", k_candidates, dim3(gS), dim3(kSelBT), 0, s, (const int32_t*)w.first, key, N,
             (int32_t)E, o->theta, o->budget_M, w.list, w.cnt, w.st);
-  for (int p = 0; p < kSelSteps; ++p)
+  for (int p = 0, steps = select_steps(N); p < steps; ++p)
     HG_LAUNCH("build_select_step", k_select_step, dim3(gS), dim3(kSelBT), 0, s, w.st, (const int32_t*)w.list,
               (const int32_t*)w.cnt, key, o->seed);
   HG_LAUNCH("build_select_finish", k_select_finish, dim3(1), dim3(kSelBT), 0, s, w.st, (const int32_t*)w.list,
