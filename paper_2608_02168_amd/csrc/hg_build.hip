@@ -7,11 +7,12 @@
 //      direction) -- a node is a candidate of C_k iff that index exists;
 //   2. node keys: out-degree, or the h-index of the out-neighbour multiset
 //      (edges sorted by source);
-//   3. C'_k = candidates with key <= theta, compacted in gid order;
-//   4. TopM: an exact radix select of the min(M, |C'_k|) smallest 128-bit
-//      composites (key, splitmix64(seed ^ gid), gid) -- unique by gid, so the
-//      selected set is unique;
-//   5. local ids in (node type, gid) order by a stable bucket partition;
+//   3. C'_k = candidates with key <= theta, listed in no order;
+//   4. TopM: an exact search by digits for the last of the min(M, |C'_k|)
+//      smallest composites (key, splitmix64(seed ^ gid)) -- the hash is a
+//      bijection of gid, so composites are unique and so is the selected set;
+//   5. local ids in (node type, gid) order from tile counts and ballots (more
+//      than two node types: by a stable bucket partition);
 //   6. induced-subgraph edge compaction in original edge order (local ids
 //      from a 32-byte-per-64-nodes rank table, per-tile counts, ballots);
 //   7. stable LSD radix sorts by (dst, r) and (src, r) give the CSR and CSC;
