@@ -27,7 +27,8 @@ def _graph(n, lengths, per_row, seed):
     g.manual_seed(seed)
     hubs = torch.randperm(n, generator=g, device="cuda")[:len(lengths)].to(torch.int32)
     count = torch.tensor(lengths, device="cuda")
-    src, rel = [torch.repeat_interleave(hubs, count)], [torch.repeat_interleave(torch.arange(len(lengths), device="cuda") % 2, count)]
+    src = [torch.repeat_interleave(hubs, count)]
+    rel = [torch.repeat_interleave(torch.arange(len(lengths), device="cuda") % 2, count)]
     if per_row:
         src.append(torch.arange(n, device="cuda", dtype=torch.int32).repeat(2 * per_row))
         rel.append(torch.arange(2, device="cuda").repeat_interleave(n * per_row))

@@ -30,7 +30,8 @@ def _check(run, order, tied):
 
 
 @pytest.mark.parametrize("name", ["tiny_d64_h4", "tiny_d128_h4"])
-@pytest.mark.parametrize("tied", [("W_K", "W_V"), ("W_Q", "W_V"), ("W_K", "W_Q", "W_V"), ("W_agg", "W_K"), ("b_K", "b_V")])
+@pytest.mark.parametrize("tied", [("W_K", "W_V"), ("W_Q", "W_V"), ("W_K", "W_Q", "W_V"), ("W_agg", "W_K"),
+                                  ("b_K", "b_V")])
 def test_attention(name, tied):
     cfg, d, heads = CFGS[name]
     ref, sub, X, w = setup(cfg, d, heads)

@@ -77,8 +77,8 @@ def test_gap_rows_written_once(tmp_path, lo, hi):
     assert row == [hi - lo, (lo + hi - 1) * (hi - lo) // 2, 0]
 
 
-LENGTHS = [0, 1, 23, 24, 47, 48, 64, 65, 256, 257, 1_024, 1_025, 2_048, 2_049, 32_768, 33_280, 100_003, 524_288, 600_001, 2**31 - 131_072,
-           2**31 - 2_049, 2**31 - 1_024, 2**31 - 1]
+LENGTHS = [0, 1, 23, 24, 47, 48, 64, 65, 256, 257, 1_024, 1_025, 2_048, 2_049, 32_768, 33_280, 100_003, 524_288,
+           600_001, 2**31 - 131_072, 2**31 - 2_049, 2**31 - 1_024, 2**31 - 1]
 
 
 @pytest.mark.parametrize("edges,nodes", [(10**5, 10**4), (2**31 - 1, 10**4), (2**31 - 1, 10**6), (2**31 - 1, 2**31 - 2)])
